@@ -8,12 +8,12 @@
 //
 // All spans of a call, of any length, are processed together (CSR offsets):
 //   1. GEMM1  G1 = GELU(emb[row_idx] W_kv^T + b_kv)   row-gathered A operand,
-//             bf16 matrix cores (v_mfma_f32_16x16x32_bf16), fp32 accumulate
+//             matrix cores (v_mfma_f32_32x32x16_bf16), fp32 accumulate
 //   2. pool   one workgroup per span: exact LN_kv row statistics, the h
 //             head scores, softmax over the span, pooled row c_s
 //   3. GEMM2  Y = GELU(c W_o^T + b_o)                 (fp32 out)
 //   4. LN_o   z_s = LN_o(Y_s)
-// The fp32 dtype runs the same four steps with a vector-ALU GEMM.
+// The fp32 dtype runs the same four steps on v_mfma_f32_32x32x2_f32.
 #include "common.hpp"
 
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
@@ -25,7 +25,8 @@ namespace sm {
 // gathered through `gather`.  128x128 tile per workgroup, K step 64, four
 // waves each owning a 64x64 quadrant (4x4 MFMA tiles of 16x16).  The next
 // K step is fetched into registers while the current one is multiplied from
-// LDS (double-buffered LDS, one barrier per step).
+// LDS (double-buffered LDS, one barrier per step).  Only operands that are
+// not 16-byte aligned still take it: its loads are plain ones.
 
 constexpr int kBM = 128, kBN = 128, kBK = 64;
 constexpr int kPitch = kBK + 8;  // bf16 elements per LDS row (16-byte pad)
@@ -144,6 +145,422 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_nt_gelu(const uint16_t *__re
 }
 
 // ---------------------------------------------------------------------------
+// GEMM for everything between one row and the 256-tile GEMM's first full
+// wave of tiles, bf16 and fp32, same contract: C[M][N] = GELU(A[M][K] .
+// B[N][K]^T + bias[N]), A rows optionally gathered.  A BM x BN tile per
+// workgroup over the whole of K; the four waves split K, not the tile: of
+// each 128-byte-deep k-tile, wave w multiplies the w-th quarter for all
+// BM x BN outputs, and the four partial tiles are added through LDS at the
+// end.  Why:
+//  * a few hundred rows make too few tiles to fill 256 compute units, so
+//    the tile is small (BM and BN come from plan_gemm's cost rule); a small
+//    tile divided among the waves would have every wave read most of both
+//    operands from LDS again (64 x 64 on 2 x 2 waves: each fragment read
+//    twice), while with K split every fragment is read once;
+//  * a wave needs only BM / 32 + BN / 32 fragments per k-tile, so the next
+//    k-tile's are read into a second register set while this one is
+//    multiplied, and one barrier per k-tile is enough.
+// K-tiles come through a ring of S LDS stages filled by direct-to-LDS loads
+// (S - 1 k-tiles ahead; 64-160 KB in flight per compute unit, which is what
+// streaming the weights of a small call is bound by).  LDS layout, swizzle
+// and fragment addressing are those of the 256-tile GEMM (below).  fp32 runs
+// the same loop on v_mfma_f32_32x32x2_f32, four per 16-byte fragment.
+//
+// Bound (bf16): the rate at which a compute unit fills its LDS, about 30
+// bytes per cycle however many units run (32 x 32 and 160 x 64 tiles alike;
+// a rotated K walk changes nothing), not the matrix cores.  Measured against
+// the kernels it took over from, us per call: 609 rows, K = N = 4096: 31
+// (160 x 64) against 64 (128 x 128 tiles, register-staged); 128 rows, 3584:
+// 11.4 (32 x 64) against 51; 64 rows, 4096: 9.6 (32 x 32) against 28.7 (16
+// columns per workgroup, operands straight to registers).  fp32, 153 rows,
+// 256: 4.9 against 16 (64 x 64 on the vector ALU); 1500 rows, 1024: 35, 90
+// TFLOP/s, bound by the fp32 matrix rate.
+
+__device__ __forceinline__ int lds_swz(int row) { return (row >> 1) & 7; }
+
+// s_waitcnt with vmcnt = N, lgkmcnt = 0, expcnt left open
+template <int N>
+__device__ __forceinline__ void wait_vmcnt_lgkm0() {
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
+}
+
+__device__ __forceinline__ void load_to_lds16(const void *src, uint8_t *lds) {
+  __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)src,
+                                   (void __attribute__((address_space(3))) *)lds, 16, 0, 0);
+}
+
+template <typename OutT>
+struct Store4;
+template <>
+struct Store4<float> {
+  static __device__ __forceinline__ void put(float *p, float a, float b, float c, float d) {
+    *(f32x4_t *)p = f32x4_t{a, b, c, d};
+  }
+};
+template <>
+struct Store4<uint16_t> {
+  static __device__ __forceinline__ void put(uint16_t *p, float a, float b, float c, float d) {
+    *(uint2 *)p = make_uint2(pack_bf16x2(a, b), pack_bf16x2(c, d));
+  }
+};
+
+template <typename T>
+__device__ __forceinline__ f32x16_t mfma_frag(u32x4_t b, u32x4_t a, f32x16_t c);
+template <>
+__device__ __forceinline__ f32x16_t mfma_frag<uint16_t>(u32x4_t b, u32x4_t a, f32x16_t c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(b), as_bf16x8(a), c, 0, 0, 0);
+}
+template <>
+__device__ __forceinline__ f32x16_t mfma_frag<float>(u32x4_t b, u32x4_t a, f32x16_t c) {
+  // element e of the two lane halves' fragments: inputs 4 h2 + e of the wave's eight
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(b[e]), __uint_as_float(a[e]), c, 0, 0, 0);
+  return c;
+}
+
+constexpr int kTThreads = 256;
+
+template <typename T, typename OutT, int BM, int BN, int S>
+__global__ __launch_bounds__(kTThreads, 1) void gemm_ksplit_nt_gelu(
+    const T *__restrict__ A, const int32_t *__restrict__ gather, int64_t a_rows, const T *__restrict__ B,
+    const T *__restrict__ bias, OutT *__restrict__ C, int M, int N, int K, int tiles_m, int tiles_n, int per_xcd,
+    int32_t *err) {
+  constexpr int FA = BM / 32, FB = BN / 32;    // fragments of a k-tile per wave
+  constexpr int NL = FA + FB;                  // direct-to-LDS loads per thread and k-tile
+  constexpr int KE = 128 / (int)sizeof(T);     // inputs per k-tile
+  constexpr int EPC = 16 / (int)sizeof(T);     // elements of a 16-byte chunk
+  constexpr int STAGE = (BM + BN) * 128;
+  static_assert(BM % 32 == 0 && BN % 32 == 0 && (S - 2) * NL < 64, "tile of 32 x 32 blocks; vmcnt holds 6 bits");
+  extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  // XCD x takes a contiguous range of tiles, all row tiles of a column tile
+  // in turn, so its L2 reads each weight row once
+  const int t = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (t >= tiles_m * tiles_n) return;
+  const int tn = t / tiles_m, tm = t - tn * tiles_m;
+  const int m0 = tm * BM, n0 = tn * BN;
+  const int nk = K / KE;
+
+  // load q of wave w: rows 32 q + 8 w + lane / 8 of A (q < FA) or of B
+  const T *pa[FA];
+  const int lrow = 8 * w + (lane >> 3);
+  const int lchunk = ((lane & 7) ^ lds_swz(lrow)) * EPC;  // (32 q does not change the swizzle)
+#pragma unroll
+  for (int q = 0; q < FA; ++q) {
+    int64_t arow = m0 + 32 * q + lrow;
+    if (gather) {
+      int gi = (arow < M) ? gather[arow] : 0;
+      if (gi < 0 || gi >= a_rows) {
+        set_err(err, SM_ERR_EINVAL);
+        gi = 0;
+      }
+      arow = gi;
+    } else if (arow >= M) {
+      arow = M - 1;
+    }
+    pa[q] = A + arow * K + lchunk;
+  }
+  const T *pb = B + (int64_t)(n0 + lrow) * K + lchunk;
+  const int64_t bstep = (int64_t)32 * K;
+  auto load_q = [&](int kt, int stage, int q) {
+    const int ko = kt * KE;
+    uint8_t *dst = lds + stage * STAGE + (4 * q + w) * 1024;
+    if (q < FA) load_to_lds16(pa[q < FA ? q : 0] + ko, dst);
+    else load_to_lds16(pb + (q - FA) * bstep + ko, dst);
+  };
+
+  // this wave's quarter of a k-tile row: chunks 2 w + lane / 32
+  const int r32 = lane & 31, h2 = lane >> 5;
+  const uint8_t *fbase = lds + r32 * 128 + (((2 * w + h2) ^ lds_swz(r32)) * 16);
+  f32x16_t acc[FA][FB];
+#pragma unroll
+  for (int i = 0; i < FA; ++i)
+#pragma unroll
+    for (int j = 0; j < FB; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  u32x4_t f[2][FA + FB];
+#pragma unroll
+  for (int q = 0; q < FA + FB; ++q) f[1][q] = u32x4_t{0u, 0u, 0u, 0u};  // "k-tile -1": adds nothing
+
+#pragma unroll
+  for (int kt = 0; kt < S - 1; ++kt)
+#pragma unroll
+    for (int q = 0; q < NL; ++q) load_q(min(kt, nk - 1), kt, q);
+
+  // One k-tile kt (fragment set P): this wave's loads of kt and its fragment
+  // reads of kt - 1 are done; barrier: kt is in LDS and stage kt - 1 is free.
+  // Then the products of kt - 1, with the fragment reads of kt and the loads
+  // of kt + S - 1 (into the free stage) spread between them.  Past the end
+  // of K the last k-tile is loaded again (never read), so that every wait
+  // counts the same loads.
+  int st_r = 0, st_w = S - 1;
+#define SM_KS_TILE(P)                                                                       \
+  {                                                                                         \
+    wait_vmcnt_lgkm0<(S - 2) * NL>();                                                       \
+    __builtin_amdgcn_s_barrier();                                                           \
+    __builtin_amdgcn_sched_barrier(0);                                                      \
+    const int kn_ = min(kt + S - 1, nk - 1);                                                \
+    constexpr int NM_ = FA * FB, NP_ = 2 * NL, PER_ = (NP_ + NM_ - 1) / NM_;                \
+    _Pragma("unroll") for (int g = 0; g < NM_; ++g) {                                       \
+      acc[g / FB][g % FB] = mfma_frag<T>(f[(P) ^ 1][FA + g % FB], f[(P) ^ 1][g / FB],       \
+                                         acc[g / FB][g % FB]);                              \
+      _Pragma("unroll") for (int p = g * PER_; p < (g + 1) * PER_ && p < NP_; ++p) {        \
+        if (p < NL) f[P][p] = *(const u32x4_t *)(fbase + st_r * STAGE + p * 4096);          \
+        else load_q(kn_, st_w, p - NL);                                                     \
+      }                                                                                     \
+      __builtin_amdgcn_sched_barrier(0);                                                    \
+    }                                                                                       \
+    st_r = st_r + 1 == S ? 0 : st_r + 1;                                                    \
+    st_w = st_w + 1 == S ? 0 : st_w + 1;                                                    \
+  }
+  for (int kt = 0; kt < nk; ++kt) {  // nk is even
+    SM_KS_TILE(0);
+    ++kt;
+    SM_KS_TILE(1);
+  }
+#undef SM_KS_TILE
+#pragma unroll
+  for (int g = 0; g < FA * FB; ++g)
+    acc[g / FB][g % FB] = mfma_frag<T>(f[1][FA + g % FB], f[1][g / FB], acc[g / FB][g % FB]);
+  wait_vmcnt_lgkm0<0>();
+  __syncthreads();  // the ring is free
+
+  // Epilogue, 32 rows at a time: register 4 g + e of block (i, j) is row
+  // 32 i + r32, column 32 j + 8 g + 4 h2 + e.  The waves' partial rows go to
+  // LDS (two buffers, rows padded by 16 bytes against bank conflicts), then
+  // every thread adds the four partials of BN / 8 columns of a row in a
+  // fixed order, applies bias and GELU and stores 16 or 32 bytes and more.
+  constexpr int PITCH = BN * 4 + 16, BUF = 4 * 32 * PITCH, CT = BN / 8;  // columns per thread
+  const int erow = tid >> 3, ecol = (tid & 7) * CT;
+  float bv[CT];
+#pragma unroll
+  for (int e = 0; e < CT; ++e) bv[e] = Elem<T>::load(bias + n0 + ecol + e);
+#pragma unroll
+  for (int i = 0; i < FA; ++i) {
+    uint8_t *buf = lds + (i & 1) * BUF;
+#pragma unroll
+    for (int j = 0; j < FB; ++j)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *(f32x4_t *)(buf + (w * 32 + r32) * PITCH + (32 * j + 8 * g + 4 * h2) * 4) =
+            f32x4_t{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+    __syncthreads();
+    const int row = m0 + 32 * i + erow;
+    float v[CT];
+#pragma unroll
+    for (int c = 0; c < CT; c += 4) {
+      f32x4_t s = *(const f32x4_t *)(buf + erow * PITCH + (ecol + c) * 4);
+#pragma unroll
+      for (int k = 1; k < 4; ++k) s += *(const f32x4_t *)(buf + (k * 32 + erow) * PITCH + (ecol + c) * 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[c + e] = gelu_erf(s[e] + bv[c + e]);
+    }
+    if (row < M) {
+      OutT *dst = C + (int64_t)row * N + n0 + ecol;
+#pragma unroll
+      for (int c = 0; c < CT; c += 4) Store4<OutT>::put(dst + c, v[c], v[c + 1], v[c + 2], v[c + 3]);
+    }
+  }
+}
+
+template <typename T, typename OutT, int BM, int BN, int S>
+static hipError_t launch_ksplit_shape(const T *A, const int32_t *gather, int64_t a_rows, const T *B, const T *bias,
+                                      OutT *C, int M, int N, int K, int32_t *err, hipStream_t stream) {
+  constexpr int ring = S * (BM + BN) * 128, epi = 2 * 4 * 32 * (BN * 4 + 16);
+  constexpr int lds = ring > epi ? ring : epi;
+  // dynamic LDS above 64 KB has to be enabled for the kernel (cheap; done
+  // on every launch so that it holds on whichever device is current)
+  const hipError_t e = hipFuncSetAttribute((const void *)gemm_ksplit_nt_gelu<T, OutT, BM, BN, S>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (e != hipSuccess) return e;
+  const int tiles_m = (M + BM - 1) / BM, tiles_n = N / BN;
+  const int per_xcd = (tiles_m * tiles_n + 7) / 8;
+  hipLaunchKernelGGL((gemm_ksplit_nt_gelu<T, OutT, BM, BN, S>), dim3(8 * per_xcd), dim3(kTThreads), lds, stream, A,
+                     gather, a_rows, B, bias, C, M, N, K, tiles_m, tiles_n, per_xcd, err);
+  return hipGetLastError();
+}
+
+template <typename T, typename OutT>
+static hipError_t launch_ksplit(int shape, const T *A, const int32_t *gather, int64_t a_rows, const T *B,
+                                const T *bias, OutT *C, int M, int N, int K, int32_t *err, hipStream_t stream) {
+#define SM_KT_CASE(I, BM, BN, S) \
+  case I:                        \
+    return launch_ksplit_shape<T, OutT, BM, BN, S>(A, gather, a_rows, B, bias, C, M, N, K, err, stream);
+  switch (shape) {
+    SM_KT_CASE(0, 32, 32, 8) SM_KT_CASE(1, 32, 64, 8) SM_KT_CASE(2, 64, 64, 8) SM_KT_CASE(3, 96, 64, 7)
+    SM_KT_CASE(4, 128, 64, 6) SM_KT_CASE(5, 160, 64, 5) SM_KT_CASE(6, 192, 64, 4)
+  }
+#undef SM_KT_CASE
+  return hipErrorInvalidValue;
+}
+
+// ---------------------------------------------------------------------------
+// bf16 GEMM of 256 x 128 tiles, same contract: for row counts whose
+// 256 x 256 tiles would leave half of the compute units idle and whose
+// smaller tiles load too much.  What bounds these GEMMs is the rate at which
+// a compute unit fills its LDS (about 30 bytes per cycle, see below), so the
+// largest tile that still gives every unit one is the fastest: 48 KB per
+// 64-deep k-tile for 4.2 MFLOP against 28 KB for 1.3 MFLOP of the 160 x 64
+// tile.  Four waves of 128 x 64, three LDS stages of 48 KB, one barrier per
+// k-tile: k steps 0-2 multiply while the next step's fragments are read;
+// before k step 3 each wave waits for its loads of the next k-tile and for
+// its last fragment reads of this one, and after the barrier this stage is
+// refilled (4 loads in k step 3, 4 each in k steps 0 and 1 of the next
+// k-tile) with the k-tile three ahead.  1700 rows at K = N = 4096: 67 us, 850
+// TFLOP/s, against 94 (256 x 256) and 95 (160 x 64).
+
+constexpr int kWM = 256, kWN = 128, kWStages = 3, kWStageBytes = (kWM + kWN) * 128;
+constexpr int kWLdsBytes = kWStages * kWStageBytes;
+
+template <typename OutT>
+__global__ __launch_bounds__(256, 1) void gemm_wide_bf16_nt_gelu(
+    const uint16_t *__restrict__ A, const int32_t *__restrict__ gather, int64_t a_rows,
+    const uint16_t *__restrict__ B, const uint16_t *__restrict__ bias, OutT *__restrict__ C, int M, int N, int K,
+    int tiles_m, int tiles_n, int per_xcd, int32_t *err) {
+  extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int wm = w >> 1, wn = w & 1;  // this wave's 128 x 64 block of the tile
+  const int xcd = blockIdx.x & 7;
+  const int t = xcd * per_xcd + (blockIdx.x >> 3);
+  if (t >= tiles_m * tiles_n) return;
+  const int tn = t / tiles_m, tm = t - tn * tiles_m;  // a column tile's row tiles share its weights in one L2
+  const int m0 = tm * kWM, n0 = tn * kWN;
+  const int nk = K / 64;
+  const int rot = (tn + xcd * (nk / 8)) % nk;  // as in the 256-tile GEMM
+
+  // load q of wave w: rows 32 q + 8 w + lane / 8 of A (q < 8) or of B
+  const uint16_t *pa[8];
+  const int lrow = 8 * w + (lane >> 3);
+  const int lchunk = ((lane & 7) ^ lds_swz(lrow)) * 8;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    int64_t arow = m0 + 32 * q + lrow;
+    if (gather) {
+      int gi = (arow < M) ? gather[arow] : 0;
+      if (gi < 0 || gi >= a_rows) {
+        set_err(err, SM_ERR_EINVAL);
+        gi = 0;
+      }
+      arow = gi;
+    } else if (arow >= M) {
+      arow = M - 1;
+    }
+    pa[q] = A + arow * K + lchunk;
+  }
+  const uint16_t *pb = B + (int64_t)(n0 + lrow) * K + lchunk;
+  const int64_t bstep = (int64_t)32 * K;
+  auto load_q = [&](int kt, int stage, int q) {
+    const int kr = min(kt, nk - 1) + rot, ko = (kr >= nk ? kr - nk : kr) * 64;
+    uint8_t *dst = lds + stage * kWStageBytes + (4 * q + w) * 1024;
+    if (q < 8) load_to_lds16(pa[q < 8 ? q : 0] + ko, dst);
+    else load_to_lds16(pb + (q - 8) * bstep + ko, dst);
+  };
+  const int r32 = lane & 31, h2 = lane >> 5;
+  int fo[4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) fo[ks] = r32 * 128 + (((2 * ks + h2) ^ lds_swz(r32)) * 16);
+  const int a_off = wm * 128 * 128, b_off = kWM * 128 + wn * 64 * 128;
+  auto frag = [&](int stage, int ks, int p) {  // fragment p of k step ks: A blocks 0-3, B blocks 0-1
+    return *(const u32x4_t *)(lds + stage * kWStageBytes + (p < 4 ? a_off + p * 4096 : b_off + (p - 4) * 4096) + fo[ks]);
+  };
+
+  f32x16_t acc[4][2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+
+  // k-tiles 0 and 1 and the first four loads of k-tile 2
+#pragma unroll
+  for (int q = 0; q < 12; ++q) load_q(0, 0, q);
+#pragma unroll
+  for (int q = 0; q < 12; ++q) load_q(1, 1, q);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) load_q(2, 2, q);
+  wait_vmcnt_lgkm0<16>();
+  __builtin_amdgcn_s_barrier();
+  u32x4_t f[2][6];
+#pragma unroll
+  for (int p = 0; p < 6; ++p) f[0][p] = frag(0, 0, p);
+
+  // k step KS of k-tile kt (stage s0; s1, s2 hold kt + 1, kt + 2): 8 MFMAs,
+  // after them the next k step's fragment reads and up to four loads
+#define SM_WIDE_STEP(KS)                                                                                  \
+  _Pragma("unroll") for (int g = 0; g < 8; ++g) {                                                         \
+    acc[g >> 1][g & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(f[(KS) & 1][4 + (g & 1)]),     \
+                                                                 as_bf16x8(f[(KS) & 1][g >> 1]),          \
+                                                                 acc[g >> 1][g & 1], 0, 0, 0);            \
+    if (g < 6) f[((KS) & 1) ^ 1][g] = (KS) < 3 ? frag(s0, ((KS) + 1) & 3, g) : frag(s1, 0, g);            \
+    if ((KS) != 2 && (g & 1)) {                                                                           \
+      if ((KS) == 3) load_q(kt + 3, s0, g >> 1);                                                          \
+      else load_q(kt + 2, s2, 4 + 4 * (KS) + (g >> 1));                                                   \
+    }                                                                                                     \
+    __builtin_amdgcn_sched_barrier(0);                                                                    \
+  }
+  int s0 = 0, s1 = 1, s2 = 2;
+  for (int kt = 0; kt < nk; ++kt) {
+    SM_WIDE_STEP(0)
+    SM_WIDE_STEP(1)
+    SM_WIDE_STEP(2)
+    wait_vmcnt_lgkm0<12>();  // k-tile kt + 1 has landed (the 12 loads of kt + 2 may be in flight)
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    SM_WIDE_STEP(3)
+    const int s = s0;
+    s0 = s1;
+    s1 = s2;
+    s2 = s;
+  }
+#undef SM_WIDE_STEP
+  wait_vmcnt_lgkm0<0>();
+  __syncthreads();  // the ring is free
+
+  // Epilogue: bias and GELU, the tile row-major through LDS (16-byte chunk c
+  // of row r at c ^ (r % CH)), whole rows out (64 or 128 KB, one pass)
+  constexpr int CH = kWN * (int)sizeof(OutT) / 16, EPC = 16 / (int)sizeof(OutT);
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int lcol = wn * 64 + j * 32 + 8 * g + 4 * h2;
+      float b[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) b[e] = bf16_to_f32(bias[n0 + lcol + e]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int row = wm * 128 + i * 32 + r32, c = lcol / EPC;
+        uint8_t *dst = lds + row * (CH * 16) + ((c ^ (row & (CH - 1))) * 16) + (lcol % EPC) * (int)sizeof(OutT);
+        Store4<OutT>::put((OutT *)dst, gelu_erf(acc[i][j][4 * g + 0] + b[0]), gelu_erf(acc[i][j][4 * g + 1] + b[1]),
+                          gelu_erf(acc[i][j][4 * g + 2] + b[2]), gelu_erf(acc[i][j][4 * g + 3] + b[3]));
+      }
+    }
+  __syncthreads();
+#pragma unroll 8
+  for (int k = 0; k < kWM * CH / 256; ++k) {
+    const int q = tid + k * 256, row = q / CH, c = q % CH;
+    const u32x4_t v = *(const u32x4_t *)(lds + row * (CH * 16) + ((c ^ (row & (CH - 1))) * 16));
+    if (m0 + row < M) *(u32x4_t *)(C + (int64_t)(m0 + row) * N + n0 + c * EPC) = v;
+  }
+}
+
+template <typename OutT>
+static hipError_t launch_wide(const uint16_t *A, const int32_t *gather, int64_t a_rows, const uint16_t *B,
+                              const uint16_t *bias, OutT *C, int M, int N, int K, int32_t *err, hipStream_t stream) {
+  const hipError_t e = hipFuncSetAttribute((const void *)gemm_wide_bf16_nt_gelu<OutT>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, kWLdsBytes);
+  if (e != hipSuccess) return e;
+  const int tiles_m = (M + kWM - 1) / kWM, tiles_n = N / kWN;
+  const int per_xcd = (tiles_m * tiles_n + 7) / 8;
+  hipLaunchKernelGGL(gemm_wide_bf16_nt_gelu<OutT>, dim3(8 * per_xcd), dim3(256), kWLdsBytes, stream, A, gather, a_rows,
+                     B, bias, C, M, N, K, tiles_m, tiles_n, per_xcd, err);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
 // Large bf16 GEMM, same contract as above: 256x256 output tile per
 // workgroup, four waves in a 2 x 2 grid (128 x 128 each, accumulators in
 // the accumulation registers, one wave per SIMD) on
@@ -188,34 +605,6 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_nt_gelu(const uint16_t *__re
 constexpr int kLM = 256, kLN = 256, kLK = 64, kLStages = 2, kLThreads = 256, kGroupM = 4;
 constexpr int kLStageBytes = kLM * kLK * 2;  // per operand
 constexpr int kLLdsBytes = 2 * kLStages * kLStageBytes;
-
-__device__ __forceinline__ int lds_swz(int row) { return (row >> 1) & 7; }
-
-// s_waitcnt with vmcnt = N, lgkmcnt = 0, expcnt left open
-template <int N>
-__device__ __forceinline__ void wait_vmcnt_lgkm0() {
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
-}
-
-__device__ __forceinline__ void load_to_lds16(const uint16_t *src, uint8_t *lds) {
-  __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)src,
-                                   (void __attribute__((address_space(3))) *)lds, 16, 0, 0);
-}
-
-template <typename OutT>
-struct Store4;
-template <>
-struct Store4<float> {
-  static __device__ __forceinline__ void put(float *p, float a, float b, float c, float d) {
-    *(f32x4_t *)p = f32x4_t{a, b, c, d};
-  }
-};
-template <>
-struct Store4<uint16_t> {
-  static __device__ __forceinline__ void put(uint16_t *p, float a, float b, float c, float d) {
-    *(uint2 *)p = make_uint2(pack_bf16x2(a, b), pack_bf16x2(c, d));
-  }
-};
 
 template <typename OutT>
 __global__ __launch_bounds__(kLThreads, 1) void gemm256_bf16_nt_gelu(
@@ -467,94 +856,8 @@ static hipError_t launch_gemm256(const uint16_t *A, const int32_t *gather, int64
 }
 
 // ---------------------------------------------------------------------------
-// Skinny bf16 GEMM for M <= 64 rows (a decode-time merge of a few spans):
-// C[M][N] = GELU(A[M][K] W[N][K]^T + bias).  One workgroup per 16 output
-// columns (N / 16 workgroups, enough to keep every compute unit streaming
-// its slice of W), the four waves split K and reduce through LDS.  Operand
-// fragments are loaded straight from memory in MFMA layout, U k-steps of 32
-// at a time so that U * (1 + m-tiles) 16-byte loads per lane are in flight.
-
-constexpr int kSkinnyMaxM = 64;
-
-template <typename OutT, int U>
-__global__ __launch_bounds__(256) void gemm_skinny_bf16_gelu(const uint16_t *__restrict__ A,
-                                                             const int32_t *__restrict__ gather, int64_t a_rows,
-                                                             const uint16_t *__restrict__ W,
-                                                             const uint16_t *__restrict__ bias,
-                                                             OutT *__restrict__ C, int M, int N, int K,
-                                                             int32_t *err) {
-  __shared__ float red[4][kSkinnyMaxM][17];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int r = lane & 15, q4 = lane >> 4;
-  const int n0 = blockIdx.x * 16;
-  const int mt = (M + 15) >> 4;  // m-tiles (<= 4)
-  const uint16_t *arow[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = i * 16 + r;
-    int64_t idx = 0;
-    if (m < M) {
-      idx = gather ? gather[m] : m;
-      if (idx < 0 || idx >= a_rows) {
-        set_err(err, SM_ERR_EINVAL);
-        idx = 0;
-      }
-    }
-    arow[i] = A + idx * K + 8 * q4;
-  }
-  const uint16_t *wrow = W + (int64_t)(n0 + r) * K + 8 * q4;
-  const int kw = K >> 2, kbeg = w * kw;
-  f32x4_t acc[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  for (int k = kbeg; k < kbeg + kw; k += 32 * U) {
-    u32x4_t bw[U], fa[U][4];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      bw[u] = *(const u32x4_t *)(wrow + k + 32 * u);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (i < mt) fa[u][i] = *(const u32x4_t *)(arow[i] + k + 32 * u);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (i < mt)
-          acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(fa[u][i]), as_bf16x8(bw[u]), acc[i], 0, 0, 0);
-  }
-  // lane (r, q4) of m-tile i holds rows 16 i + 4 q4 + e, column r
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) red[w][i * 16 + 4 * q4 + e][r] = acc[i][e];
-  __syncthreads();
-  for (int o = tid; o < mt * 16 * 16; o += 256) {
-    const int m = o >> 4, n = o & 15;
-    if (m >= M) continue;
-    const float v = red[0][m][n] + red[1][m][n] + red[2][m][n] + red[3][m][n];
-    C[(int64_t)m * N + n0 + n] = Elem<OutT>::to_store(gelu_erf(v + bf16_to_f32(bias[n0 + n])));
-  }
-}
-
-template <typename OutT>
-static void launch_skinny(const uint16_t *A, const int32_t *gather, int64_t a_rows, const uint16_t *W,
-                          const uint16_t *bias, OutT *C, int M, int N, int K, int32_t *err, hipStream_t stream) {
-  const dim3 grid(N / 16), block(256);
-  if ((K / 4) % (32 * 8) == 0)
-    hipLaunchKernelGGL((gemm_skinny_bf16_gelu<OutT, 8>), grid, block, 0, stream, A, gather, a_rows, W, bias, C, M,
-                       N, K, err);
-  else if ((K / 4) % (32 * 4) == 0)
-    hipLaunchKernelGGL((gemm_skinny_bf16_gelu<OutT, 4>), grid, block, 0, stream, A, gather, a_rows, W, bias, C, M,
-                       N, K, err);
-  else
-    hipLaunchKernelGGL((gemm_skinny_bf16_gelu<OutT, 2>), grid, block, 0, stream, A, gather, a_rows, W, bias, C, M,
-                       N, K, err);
-}
-
-// ---------------------------------------------------------------------------
 // fp32 GEMM on the vector ALU (64x64 tile, 4x4 outputs per thread), same
-// contract as the bf16 one.
+// contract as the bf16 one, for operands that are not 16-byte aligned.
 
 constexpr int kFT = 64, kFK = 16;
 
@@ -615,6 +918,125 @@ __global__ __launch_bounds__(256) void gemm_f32_nt_gelu(const float *__restrict_
       C[(int64_t)row * N + col] = gelu_erf(acc[i][j] + bias[col]);
     }
   }
+}
+
+// ---------------------------------------------------------------------------
+// Which GEMM a call takes.  Times in microseconds at K = 64 nk (bf16), fitted
+// to sweeps over M = 1..30,000 at N = K = 512..8192 on the box (each within
+// about 10%): a grid of t tiles runs as waves of one workgroup per compute
+// unit; a k-tile of a wave takes a time that grows with the bytes each
+// workgroup loads for it (BM + BN rows) and, for the large tiles, with the
+// part f of the compute units that are busy (the matrix clock falls); each
+// wave adds its prologue and epilogue.  Measured at K = N = 4096:
+//   M = 64      32x32 9.6    64x64 16.7
+//   M = 609     160x64 31    128x64 47    256x128 58    256x256 86
+//   M = 1700    160x64 95    256x128 67   256x256 94
+//   M = 2400    256x128 119  256x256 95
+//   M = 4200    256x256 195, of which the 17th row of tiles alone about 78
+// The last line is why a call may be cut in two by rows: whole waves of the
+// large tile, and the rows that remain by whatever is fastest for them.
+
+struct KtShape {
+  int bm, bn;
+};
+constexpr KtShape kKtShapes[] = {{32, 32}, {32, 64}, {64, 64}, {96, 64}, {128, 64}, {160, 64}, {192, 64}};
+constexpr int kKtShapeCount = sizeof(kKtShapes) / sizeof(kKtShapes[0]);
+constexpr int kGemmWide = kKtShapeCount, kGemm256 = kKtShapeCount + 1, kGemmKinds = kKtShapeCount + 2;
+constexpr int kGemmCus = 256;
+
+static float gemm_cost(int kind, int M, int N, int K, bool f32) {
+  const int bm = kind == kGemm256 ? kLM : kind == kGemmWide ? kWM : kKtShapes[kind].bm;
+  const int bn = kind == kGemm256 ? kLN : kind == kGemmWide ? kWN : kKtShapes[kind].bn;
+  if (N % bn || (f32 && kind >= kKtShapeCount)) return 3.0e38f;
+  const int64_t tiles = (int64_t)((M + bm - 1) / bm) * (N / bn);
+  const int64_t full = tiles / kGemmCus;
+  const float f = (float)(tiles % kGemmCus) / kGemmCus, nk = (float)(K / (f32 ? 32 : 64));
+  if (kind == kGemm256) return 7.f + full * (nk * 1.53f + 14.f) + (f > 0.f ? nk * (0.88f + 0.65f * f) + 14.f : 0.f);
+  if (kind == kGemmWide) return 6.f + full * (nk * 0.88f + 8.f) + (f > 0.f ? nk * (0.55f + 0.33f * f) + 8.f : 0.f);
+  const float kt = f32 ? 0.04f + 0.16f * (bm / 32) * (bn / 32) : 0.0021f * (bm + bn) - 0.04f;
+  return 3.f + (full + (f > 0.f ? 1 : 0)) * (nk * kt + 0.8f * (bm / 32));
+}
+
+struct GemmPlan {
+  int kind, rows;        // rows [0, rows) with `kind`
+  int kind2;             // and the rest with kind2 (rows < M)
+};
+
+static GemmPlan plan_gemm(int M, int N, int K, bool f32) {
+  auto best = [&](int m, float *cost) {
+    int b = 0;
+    for (int k = 0; k < kGemmKinds; ++k) {
+      const float c = gemm_cost(k, m, N, K, f32);
+      if (k == 0 || c < *cost) {
+        *cost = c;
+        b = k;
+      }
+    }
+    return b;
+  };
+  GemmPlan p{0, M, 0};
+  float cost;
+  p.kind = best(M, &cost);
+  if (f32) return p;
+  for (int kind = kGemmWide; kind <= kGemm256; ++kind) {
+    const int bm = kind == kGemm256 ? kLM : kWM, tiles_n = N / (kind == kGemm256 ? kLN : kWN);
+    const int64_t row_tiles = (M + bm - 1) / bm;
+    const int64_t waves = row_tiles * tiles_n / kGemmCus;
+    if (tiles_n > kGemmCus || waves < 1 || waves > 4) continue;  // (beyond a few waves the last one weighs little)
+    const int64_t m1 = waves * kGemmCus / tiles_n * bm;
+    if (m1 <= 0 || m1 >= M) continue;
+    float rest;
+    const int k2 = best((int)(M - m1), &rest);
+    const float c = gemm_cost(kind, (int)m1, N, K, f32) + rest;
+    if (c < 0.95f * cost) {
+      cost = c;
+      p = GemmPlan{kind, (int)m1, k2};
+    }
+  }
+  return p;
+}
+
+template <typename OutT>
+static hipError_t launch_gemm_kind(int kind, const uint16_t *A, const int32_t *gather, int64_t a_rows,
+                                   const uint16_t *B, const uint16_t *bias, OutT *C, int M, int N, int K, int32_t *err,
+                                   hipStream_t stream) {
+  if (kind == kGemm256) return launch_gemm256<OutT>(A, gather, a_rows, B, bias, C, M, N, K, err, stream);
+  if (kind == kGemmWide) return launch_wide<OutT>(A, gather, a_rows, B, bias, C, M, N, K, err, stream);
+  return launch_ksplit<uint16_t, OutT>(kind, A, gather, a_rows, B, bias, C, M, N, K, err, stream);
+}
+
+// direct-to-LDS loads and 16-byte stores want 16-byte aligned operands (rows
+// are multiples of 512 bytes); others take the kernels with plain loads
+static bool gemm_aligned(const void *A, const void *B, const void *C) {
+  return (((uintptr_t)A | (uintptr_t)B | (uintptr_t)C) & 15) == 0;
+}
+
+// C[M][N] = GELU(A[M][K] . B[N][K]^T + bias[N]), A rows through `gather` when
+// given (N, K multiples of 256)
+template <typename OutT>
+static hipError_t launch_gemm(const uint16_t *A, const int32_t *gather, int64_t a_rows, const uint16_t *B,
+                              const uint16_t *bias, OutT *C, int M, int N, int K, int32_t *err, hipStream_t stream) {
+  if (!gemm_aligned(A, B, C)) {
+    hipLaunchKernelGGL(gemm_bf16_nt_gelu<OutT>, dim3(N / kBN, (M + kBM - 1) / kBM), dim3(256), 0, stream, A, gather,
+                       a_rows, B, bias, C, M, N, K, err);
+    return hipGetLastError();
+  }
+  const GemmPlan p = plan_gemm(M, N, K, false);
+  const hipError_t e = launch_gemm_kind<OutT>(p.kind, A, gather, a_rows, B, bias, C, p.rows, N, K, err, stream);
+  if (e != hipSuccess || p.rows == M) return e;
+  const int64_t off = (int64_t)p.rows;
+  return launch_gemm_kind<OutT>(p.kind2, gather ? A : A + off * K, gather ? gather + off : nullptr, a_rows, B, bias,
+                                C + off * N, M - p.rows, N, K, err, stream);
+}
+
+static hipError_t launch_gemm(const float *A, const int32_t *gather, int64_t a_rows, const float *B, const float *bias,
+                              float *C, int M, int N, int K, int32_t *err, hipStream_t stream) {
+  if (!gemm_aligned(A, B, C)) {
+    hipLaunchKernelGGL(gemm_f32_nt_gelu, dim3(N / kFT, (M + kFT - 1) / kFT), dim3(256), 0, stream, A, gather, a_rows, B,
+                       bias, C, M, N, K, err);
+    return hipGetLastError();
+  }
+  return launch_ksplit<float, float>(plan_gemm(M, N, K, true).kind, A, gather, a_rows, B, bias, C, M, N, K, err, stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -1643,23 +2065,12 @@ static sm_status merge_param_check(const sm_merge_params *p, sm_dtype dt) {
 static sm_status first_stage(const void *A, const int32_t *gather, int64_t a_rows, int M, const sm_merge_params *p,
                              sm_dtype dt, void *C, int32_t *err, hipStream_t stream) {
   const int d = p->d;
-  if (dt == SM_BF16) {
-    if (M <= kSkinnyMaxM)
-      launch_skinny<uint16_t>((const uint16_t *)A, gather, a_rows, (const uint16_t *)p->W_kv,
-                              (const uint16_t *)p->b_kv, (uint16_t *)C, M, d, d, err, stream);
-    else if (use_gemm256(M, d, d)) {
-      if (launch_gemm256<uint16_t>((const uint16_t *)A, gather, a_rows, (const uint16_t *)p->W_kv,
-                                   (const uint16_t *)p->b_kv, (uint16_t *)C, M, d, d, err, stream) != hipSuccess)
-        return SM_EHIP;
-    } else
-      hipLaunchKernelGGL(gemm_bf16_nt_gelu<uint16_t>, dim3(d / kBN, (M + kBM - 1) / kBM), dim3(256), 0, stream,
-                         (const uint16_t *)A, gather, a_rows, (const uint16_t *)p->W_kv, (const uint16_t *)p->b_kv,
-                         (uint16_t *)C, M, d, d, err);
-  } else {
-    hipLaunchKernelGGL(gemm_f32_nt_gelu, dim3(d / kFT, (M + kFT - 1) / kFT), dim3(256), 0, stream, (const float *)A,
-                       gather, a_rows, (const float *)p->W_kv, (const float *)p->b_kv, (float *)C, M, d, d, err);
-  }
-  return hipGetLastError() == hipSuccess ? SM_OK : SM_EHIP;
+  const hipError_t e =
+      dt == SM_BF16 ? launch_gemm((const uint16_t *)A, gather, a_rows, (const uint16_t *)p->W_kv,
+                                  (const uint16_t *)p->b_kv, (uint16_t *)C, M, d, d, err, stream)
+                    : launch_gemm((const float *)A, gather, a_rows, (const float *)p->W_kv, (const float *)p->b_kv,
+                                  (float *)C, M, d, d, err, stream);
+  return e == hipSuccess ? SM_OK : SM_EHIP;
 }
 
 // Pooling, second projection and LN_o over the first-stage rows G1 (row r
@@ -1673,23 +2084,18 @@ static sm_status pool_and_project(const void *G1, const int32_t *gidx, int64_t g
                               (const uint16_t *)p->Q, (const uint16_t *)p->g_kv, (const uint16_t *)p->beta_kv,
                               p->ln_eps, d, h, (uint16_t *)cbuf, err, stream) != hipSuccess)
       return SM_EHIP;
-    if (num_spans <= kSkinnyMaxM)
-      launch_skinny<float>((const uint16_t *)cbuf, (const int32_t *)nullptr, (int64_t)num_spans,
-                           (const uint16_t *)p->W_o, (const uint16_t *)p->b_o, ybuf, num_spans, d, d, err, stream);
-    else if (use_gemm256(num_spans, d, d)) {
-      if (launch_gemm256<uint16_t>((const uint16_t *)cbuf, (const int32_t *)nullptr, (int64_t)num_spans,
-                                   (const uint16_t *)p->W_o, (const uint16_t *)p->b_o, (uint16_t *)ybuf, num_spans, d,
-                                   d, err, stream) != hipSuccess)
+    if (use_gemm256(num_spans, d, d)) {
+      if (launch_gemm((const uint16_t *)cbuf, nullptr, (int64_t)num_spans, (const uint16_t *)p->W_o,
+                      (const uint16_t *)p->b_o, (uint16_t *)ybuf, num_spans, d, d, err, stream) != hipSuccess)
         return SM_EHIP;
       return launch_ln_bf16((const uint16_t *)ybuf, (const uint16_t *)p->g_o, (const uint16_t *)p->beta_o,
                             p->ln_eps, d, num_spans, (uint16_t *)out, stream) == hipSuccess
                  ? SM_OK
                  : SM_EHIP;
-    } else
-      hipLaunchKernelGGL(gemm_bf16_nt_gelu<float>, dim3(d / kBN, (num_spans + kBM - 1) / kBM), dim3(256), 0,
-                         stream, (const uint16_t *)cbuf, (const int32_t *)nullptr, (int64_t)num_spans,
-                         (const uint16_t *)p->W_o, (const uint16_t *)p->b_o, ybuf, num_spans, d, d, err);
-    if (hipGetLastError() != hipSuccess) return SM_EHIP;
+    }
+    if (launch_gemm((const uint16_t *)cbuf, nullptr, (int64_t)num_spans, (const uint16_t *)p->W_o,
+                    (const uint16_t *)p->b_o, ybuf, num_spans, d, d, err, stream) != hipSuccess)
+      return SM_EHIP;
     hipLaunchKernelGGL(ln_rows_kernel<uint16_t>, dim3(num_spans), dim3(kPoolThreads), 0, stream, ybuf,
                        (const uint16_t *)p->g_o, (const uint16_t *)p->beta_o, p->ln_eps, d, (uint16_t *)out);
   } else {
@@ -1697,10 +2103,9 @@ static sm_status pool_and_project(const void *G1, const int32_t *gidx, int64_t g
                            (const float *)p->Q, (const float *)p->g_kv, (const float *)p->beta_kv, p->ln_eps, d, h,
                            (float *)cbuf, err, stream) != hipSuccess)
       return SM_EHIP;
-    hipLaunchKernelGGL(gemm_f32_nt_gelu, dim3(d / kFT, (num_spans + kFT - 1) / kFT), dim3(256), 0, stream,
-                       (const float *)cbuf, (const int32_t *)nullptr, (int64_t)num_spans, (const float *)p->W_o,
-                       (const float *)p->b_o, ybuf, num_spans, d, d, err);
-    if (hipGetLastError() != hipSuccess) return SM_EHIP;
+    if (launch_gemm((const float *)cbuf, nullptr, (int64_t)num_spans, (const float *)p->W_o, (const float *)p->b_o,
+                    ybuf, num_spans, d, d, err, stream) != hipSuccess)
+      return SM_EHIP;
     hipLaunchKernelGGL(ln_rows_kernel<float>, dim3(num_spans), dim3(kPoolThreads), 0, stream, ybuf,
                        (const float *)p->g_o, (const float *)p->beta_o, p->ln_eps, d, (float *)out);
   }
@@ -1726,7 +2131,7 @@ SM_API sm_status sm_merge_spans(const void *emb, int64_t emb_rows, const int32_t
   void *g1 = wsb;
   void *cbuf = wsb + align256((size_t)total_rows * d * es);
   float *ybuf = (float *)(wsb + align256((size_t)total_rows * d * es) + align256((size_t)num_spans * d * es));
-  if (dt == SM_BF16 && total_rows > kSkinnyMaxM && use_gemm256(total_rows, d, d)) {
+  if (dt == SM_BF16 && use_gemm256(total_rows, d, d)) {
     // the first stage in token-id order (see sort_count_kernel)
     char *sw = (char *)ybuf + align256((size_t)num_spans * d * 4);
     int32_t *sorted_tok = (int32_t *)sw;
