@@ -8,8 +8,11 @@
 //   g = h / G (grouped query).
 //
 // One workgroup of eight waves per (request, kv head, block of positions).
-// It holds 256 query vectors: BQ = 256 / G positions x the G query heads of
-// kv head g, so every K/V tile it loads serves all of them.  A wave owns 32
+// It holds 256 / KS query vectors: BQ = 256 / KS / G positions x the G query
+// heads of kv head g, so every K/V tile it loads serves all of them; with
+// KS > 1 (calls too small to fill the chip, see pf_key_splits) the waves
+// form KS groups that hold the same vectors and take every KS-th tile of
+// keys, and their softmax states are merged through LDS at the end.  A wave owns 32
 // vectors, the columns of the transposed score blocks
 //   S^T (32 keys x 32 queries) = K (32 x D) . Q^T        (v_mfma_f32_32x32x16_bf16)
 // and accumulates
@@ -20,7 +23,7 @@
 // statistics need one lane swap per tile.  The K rows of a block are read in
 // a permuted order so that the 16 scores a lane holds are exactly the keys
 // its PV operand needs (8 contiguous tokens per 16-key step): no shuffle
-// between the two products.  K/V tiles of 64 keys go through LDS, the next
+// between the two products.  K/V tiles of 64 keys (32 with KS = 4) go through LDS, the next
 // tile's global loads in flight while the current one is multiplied.
 //
 // Softmax: exp2 of (score x scale log2 e - reference), with the reference
@@ -40,11 +43,9 @@ __device__ __forceinline__ uint32_t cvt_bf16x2(float lo, float hi) {
 
 namespace sm {
 
-constexpr int kPfVec = 256;                 // query vectors per workgroup
-constexpr int kPfWaves = kPfVec / 32;       // one 32-vector column block per wave
+constexpr int kPfWaves = 8;
 constexpr int kPfThreads = 64 * kPfWaves;
-constexpr int kPfKeys = 64;                 // keys per tile
-constexpr int kPfSub = kPfKeys / 32;        // 32-key score blocks per tile
+constexpr int kPfVec = 32 * kPfWaves;       // query vectors per workgroup when its waves do not split the keys
 constexpr int kPfMaxPages = 4096;
 constexpr float kPfLog2e = 1.4426950408889634f;
 
@@ -74,21 +75,33 @@ __device__ __forceinline__ int pf_token_of_row(int rho) {
   return (rho & ~15) | (q2 << 2) | (rho & 3);
 }
 
-template <int DH>
+template <int DH, int KS>
 __global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16(PrefillArgs a) {
+  constexpr int KEYS = KS == 4 ? 32 : 64;  // keys per tile
+  constexpr int SUB = KEYS / 32;           // 32-key score blocks per tile
+  constexpr int SPAN = KS * KEYS;          // keys per pass: one tile for each of the KS wave groups
+  constexpr int VG = kPfWaves / KS;        // waves per group: 32 VG query vectors per workgroup
   constexpr int KP = DH + 8;        // K tile row pitch (bf16)
-  constexpr int VP = kPfKeys + 8;   // V tile row pitch (bf16)
+  // V tile rows: 72 elements for 64 keys; 32 keys have no room for padding,
+  // so chunk c of row r sits at c ^ (r / 4 % 4) (16 rows of one chunk hit
+  // all 64 banks once)
+  constexpr int VP = KEYS == 32 ? 32 : KEYS + 8;
+  auto v_at = [](int row, int chunk) { return row * VP + 8 * (KEYS == 32 ? chunk ^ ((row >> 2) & 3) : chunk); };
   constexpr int NKS = DH / 16;      // k steps of S^T
   constexpr int NRB = DH / 32;      // 32-dim row blocks of O^T
   constexpr int KCH = DH / 8;       // 16-byte chunks of a K row
-  constexpr int VCH = kPfKeys / 8;  // 16-byte chunks of a V row (one dim) in a tile
-  constexpr int KTOT = kPfKeys * KCH, VTOT = DH * VCH;    // 16-byte chunks per tile
+  constexpr int VCH = KEYS / 8;     // 16-byte chunks of a V row (one dim) in a tile
+  constexpr int KTOT = SPAN * KCH, VTOT = KS * DH * VCH;  // 16-byte chunks per pass
   constexpr int KU = (KTOT + kPfThreads - 1) / kPfThreads;  // K chunks per thread and tile
   constexpr int VU = (VTOT + kPfThreads - 1) / kPfThreads;  // V chunks per thread and tile
   __shared__ int pages[kPfMaxPages];
   __shared__ int bad_flag;
-  __shared__ __attribute__((aligned(16))) uint16_t k_lds[2][kPfKeys * KP];
-  __shared__ __attribute__((aligned(16))) uint16_t v_lds[2][DH * VP];
+  constexpr int KBUF = SPAN * KP, VBUF = KS * DH * VP;  // elements of one buffer
+  constexpr int RING = 2 * (KBUF + VBUF) * 2;
+  constexpr int OPITCH = DH + 4;                        // floats of one vector's outputs in the merge of the groups
+  constexpr int MERGE = KS > 1 ? (kPfWaves * 32 * OPITCH + kPfWaves * 64) * 4 : 0;
+  __shared__ __attribute__((aligned(16))) uint8_t smem[RING > MERGE ? RING : MERGE];
+  uint16_t *k_lds = (uint16_t *)smem, *v_lds = k_lds + 2 * KBUF;  // [2][KBUF], [2][KS][DH * VP]
 
   // Workgroup -> (request i, kv head g, block qb).  Workgroups are dealt to
   // the eight XCDs in turn; here the blocks of one (request, head) pair all
@@ -109,6 +122,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16(PrefillArgs a) {
   const int qb = nqb - 1 - j, g = pair % a.Hkv, i = pair / a.Hkv;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int c32 = lane & 31, h2 = lane >> 5;
+  const int vg = w % VG, kg = w / VG;  // this wave's vectors and its group's share of the keys
   const int bs_log2 = a.bs_log2, bs = 1 << bs_log2;
 
   // ---- request checks (uniform) ----
@@ -161,8 +175,8 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16(PrefillArgs a) {
     return;
   }
 
-  // ---- this wave's 32 query vectors: v = 32 w + c32 -> query head g G + v / BQ, row q_lo + v % BQ ----
-  const int v = 32 * w + c32;
+  // ---- this wave's 32 query vectors: v = 32 vg + c32 -> query head g G + v / BQ, row q_lo + v % BQ ----
+  const int v = 32 * vg + c32;
   const int hh = v / a.BQ, rr = v - hh * a.BQ;
   const bool vok = hh < a.G && rr < nq;
   const int vhead = g * a.G + (vok ? hh : 0);
@@ -202,11 +216,11 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16(PrefillArgs a) {
 #pragma unroll
   for (int u = 0; u < VU; ++u) {
     const int id = min(tid + kPfThreads * u, VTOT - 1);
-    vtk[u] = 8 * (id % VCH);
-    voff[u] = ((id / VCH) * bs + (vtk[u] & (bs - 1))) * 2;
+    vtk[u] = id / (DH * VCH) * KEYS + 8 * (id % VCH);
+    voff[u] = (id / VCH % DH * bs + (vtk[u] & (bs - 1))) * 2;
   }
   auto fetch = [&](int t0, u32x4_t (&kv)[KU + VU]) {
-    const int tin = t0 & (bs - 1);  // 0 when a page is no longer than a tile
+    const int tin = t0 & (bs - 1);  // 0 when a page is no longer than a pass
 #pragma unroll
     for (int u = 0; u < KU; ++u) {
       const int tok = t0 + ktk[u];
@@ -219,7 +233,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16(PrefillArgs a) {
       const uint32_t blk = pages[tok < kend ? tok >> bs_log2 : 0];
       kv[KU + u] = *(const u32x4_t *)(vbase + blk * page_bytes + (voff[u] + tin * 2));
     }
-    if (t0 + kPfKeys > L) {  // the last tile: V entries past the length may hold anything
+    if (t0 + SPAN > L) {  // the last tile: V entries past the length may hold anything
 #pragma unroll
       for (int u = 0; u < VU; ++u) {
         const int nvalid = L - (t0 + vtk[u]);
@@ -235,12 +249,12 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16(PrefillArgs a) {
 #pragma unroll
     for (int u = 0; u < KU; ++u) {
       const int id = tid + kPfThreads * u;
-      if (KTOT % kPfThreads == 0 || id < KTOT) *(u32x4_t *)(&k_lds[buf][(id / KCH) * KP + (id % KCH) * 8]) = kv[u];
+      if (KTOT % kPfThreads == 0 || id < KTOT) *(u32x4_t *)(&k_lds[buf * KBUF + (id / KCH) * KP + (id % KCH) * 8]) = kv[u];
     }
 #pragma unroll
     for (int u = 0; u < VU; ++u) {
       const int id = tid + kPfThreads * u;
-      if (VTOT % kPfThreads == 0 || id < VTOT) *(u32x4_t *)(&v_lds[buf][(id / VCH) * VP + 8 * (id % VCH)]) = kv[KU + u];
+      if (VTOT % kPfThreads == 0 || id < VTOT) *(u32x4_t *)(&v_lds[buf * VBUF + v_at(id / VCH, id % VCH)]) = kv[KU + u];
     }
   };
 
@@ -253,23 +267,23 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16(PrefillArgs a) {
   const float sl2 = a.scale_log2e;
   const int krow = pf_token_of_row(c32);  // this lane's K row in the S^T operand
 
-  const int ntiles = (kend + kPfKeys - 1) / kPfKeys;
+  const int ntiles = (kend + SPAN - 1) / SPAN;
   u32x4_t stage[KU + VU];
   fetch(0, stage);
   stash(0, stage);
   __syncthreads();
   for (int t = 0; t < ntiles; ++t) {
-    const int buf = t & 1, t0 = t * kPfKeys;
-    if (t + 1 < ntiles) fetch(t0 + kPfKeys, stage);  // in flight during this tile
+    const int buf = t & 1, t0 = t * SPAN + kg * KEYS;  // this group's tile
+    if (t + 1 < ntiles) fetch((t + 1) * SPAN, stage);  // in flight during this pass
 
     if (t0 <= wave_hi) {
       // S^T = K . Q^T, one 32-key block at a time: its fragment reads first, then its products
-      f32x16_t sc[kPfSub];
+      f32x16_t sc[SUB];
 #pragma unroll
-      for (int sb = 0; sb < kPfSub; ++sb) {
+      for (int sb = 0; sb < SUB; ++sb) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) sc[sb][e] = 0.f;
-        const uint16_t *kl = &k_lds[buf][(32 * sb + krow) * KP + 8 * h2];
+        const uint16_t *kl = &k_lds[buf * KBUF + (kg * KEYS + 32 * sb + krow) * KP + 8 * h2];
         u32x4_t kf[NKS];
 #pragma unroll
         for (int ks = 0; ks < NKS; ++ks) kf[ks] = *(const u32x4_t *)(kl + 16 * ks);
@@ -285,14 +299,14 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16(PrefillArgs a) {
       for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
         for (int kst = 0; kst < 2; ++kst)
-          vf[rb][kst] = *(const u32x4_t *)(&v_lds[buf][(32 * rb + c32) * VP + 16 * kst + 8 * h2]);
+          vf[rb][kst] = *(const u32x4_t *)(&v_lds[buf * VBUF + v_at(kg * DH + 32 * rb + c32, 2 * kst + h2)]);
 
       // online softmax per query column; register r of block sb holds token
       // t0 + 32 sb + tau(8 (r >> 2) + 4 h2 + (r & 3)).  Masked scores become
       // -inf in place: exp2 of -inf is 0 (the multiplier is positive).
-      if (t0 + kPfKeys - 1 > wave_lo) {
+      if (t0 + KEYS - 1 > wave_lo) {
 #pragma unroll
-        for (int sb = 0; sb < kPfSub; ++sb)
+        for (int sb = 0; sb < SUB; ++sb)
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             const int tok = t0 + 32 * sb + pf_token_of_row(8 * (r >> 2) + 4 * h2 + (r & 3));
@@ -301,7 +315,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16(PrefillArgs a) {
       }
       float mx = -INFINITY;
 #pragma unroll
-      for (int sb = 0; sb < kPfSub; ++sb)
+      for (int sb = 0; sb < SUB; ++sb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[sb][r]);
       float a0, b0;
@@ -319,9 +333,9 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16(PrefillArgs a) {
       }
       m_run = m_new;
       float ps = 0.f;
-      u32x4_t pf[kPfSub][2];
+      u32x4_t pf[SUB][2];
 #pragma unroll
-      for (int sb = 0; sb < kPfSub; ++sb) {
+      for (int sb = 0; sb < SUB; ++sb) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           sc[sb][r] = __builtin_amdgcn_exp2f(fmaf(sc[sb][r], sl2, -mb));
@@ -337,13 +351,13 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16(PrefillArgs a) {
 
       // O^T += V^T . P^T
 #pragma unroll
-      for (int sb = 0; sb < kPfSub; ++sb) {
+      for (int sb = 0; sb < SUB; ++sb) {
         if (sb > 0) {
 #pragma unroll
           for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
             for (int kst = 0; kst < 2; ++kst)
-              vf[rb][kst] = *(const u32x4_t *)(&v_lds[buf][(32 * rb + c32) * VP + 32 * sb + 16 * kst + 8 * h2]);
+              vf[rb][kst] = *(const u32x4_t *)(&v_lds[buf * VBUF + v_at(kg * DH + 32 * rb + c32, 4 * sb + 2 * kst + h2)]);
         }
 #pragma unroll
         for (int rb = 0; rb < NRB; ++rb)
@@ -360,7 +374,51 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16(PrefillArgs a) {
   // ---- normalize and store: register 4 gg + e of block rb = dim 32 rb + 8 gg + 4 h2 + e ----
   float a0, b0;
   swap32(l_run, a0, b0);
-  const float l_tot = a0 + b0;
+  float l_tot = a0 + b0;
+  if constexpr (KS > 1) {
+    // The groups' softmax states, merged through LDS (the ring is free: the
+    // loop ends on a barrier).  Every wave leaves its reference and sum and,
+    // scaled to the common reference, its output columns; then wave kg of a
+    // group's KS waves adds the KS partials of its DH / KS dims.
+    float *ml = (float *)smem, *po = ml + kPfWaves * 64;  // [wave][32 m, 32 l], [wave][32][OPITCH]
+    const int live = min(KS, (kend + KEYS - 1) / KEYS);   // groups that had a tile at all
+    if (h2 == 0) {
+      ml[w * 64 + c32] = m_run;
+      ml[w * 64 + 32 + c32] = l_tot;
+    }
+    __syncthreads();
+    float m_all = -INFINITY;
+    for (int k = 0; k < live; ++k) m_all = fmaxf(m_all, ml[(k * VG + vg) * 64 + c32]);
+    const float mb = m_all == -INFINITY ? 0.f : m_all;  // an idle column
+    l_tot = 0.f;
+    for (int k = 0; k < live; ++k)
+      l_tot += ml[(k * VG + vg) * 64 + 32 + c32] * __builtin_amdgcn_exp2f(ml[(k * VG + vg) * 64 + c32] - mb);
+    const float mine = __builtin_amdgcn_exp2f(m_run - mb);
+    if (kg < live)
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+        for (int gg = 0; gg < 4; ++gg)
+          *(f32x4_t *)&po[(w * 32 + c32) * OPITCH + 32 * rb + 8 * gg + 4 * h2] =
+              f32x4_t{o[rb][4 * gg] * mine, o[rb][4 * gg + 1] * mine, o[rb][4 * gg + 2] * mine, o[rb][4 * gg + 3] * mine};
+    __syncthreads();
+    const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
+    if (!vok) return;
+    // lane (c32, h2) takes dims d0 .. d0 + DH / KS / 2 - 1 of its column
+    constexpr int DW = DH / KS / 2;
+    const int d0 = kg * (DH / KS) + h2 * DW;
+    f32x4_t y[DW / 4];
+#pragma unroll
+    for (int c = 0; c < DW / 4; ++c) y[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int k = 0; k < live; ++k)
+#pragma unroll
+      for (int c = 0; c < DW / 4; ++c) y[c] += *(const f32x4_t *)&po[((k * VG + vg) * 32 + c32) * OPITCH + d0 + 4 * c];
+    uint16_t *op = a.out + ((int64_t)vrow * a.Hq + vhead) * DH + d0;
+#pragma unroll
+    for (int c = 0; c < DW / 4; ++c)
+      *(uint2 *)(op + 4 * c) = make_uint2(cvt_bf16x2(y[c][0] * inv, y[c][1] * inv), cvt_bf16x2(y[c][2] * inv, y[c][3] * inv));
+    return;
+  }
   const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
   if (!vok) return;
   uint16_t *op = a.out + ((int64_t)vrow * a.Hq + vhead) * DH + 4 * h2;
@@ -375,6 +433,39 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16(PrefillArgs a) {
 }  // namespace sm
 
 using namespace sm;
+
+// Into how many groups the waves of a workgroup split the keys (KS).  Where
+// the query vectors make fewer workgroups than compute units, KS = 4 or 2
+// makes 4 or 2 times as many, each with a quarter or half of the vectors and
+// its waves over different keys; with the units full it only adds LDS fills
+// (16 x 2458 rows: 894, 1071 and 1663 us for KS = 1, 2, 4).  Measured, us for
+// KS = 1, 2, 4 at 32/8 heads, D = 128: 512 rows after 16384: 429, 274, 229
+// (64, 128, 256 workgroups); 1024 after 8192: 246, 171, 244 (128, ...); 2048
+// after 8192: 317, 355, 498 (256, ...); 256 rows alone: 15.8, 12.4, 11.1.
+//  * A whole prompt's workgroups differ in length (its last rows see all of
+//    it, its first almost nothing), so halving them still pays up to 3/4 of
+//    the units: 1200 rows: 42.5, 32.4, 44.8 (152, ...); not after earlier
+//    context: 1500 after 3000: 142, 145, 179 (192, ...).
+//  * Up to 128 vectors leave half of the waves idle with KS = 1, and a short
+//    context is then done sooner than a merge of groups: 64 rows at 8/8
+//    heads: 6.6, 8.5, 8.7, but after 4096: 76, 69, 59.  The cache's capacity
+//    is all that the host knows of the context.
+// The sizes are averages and bounds (the rows of each request are device
+// data); a grid that a loose max_rows would blow up keeps KS = 1.
+static int pf_key_splits(int n, int H, int G, int total_rows, int max_rows, int64_t capacity) {
+  constexpr int64_t kCus = 256;
+  const int64_t avg = ((int64_t)total_rows + n - 1) / n;
+  auto wgs = [&](int ks, int64_t rows) {
+    const int bq = kPfVec / ks / G;
+    return (rows + bq - 1) / bq * n * H;
+  };
+  if ((int64_t)max_rows * G <= 128 && capacity < 1024) return 1;
+  for (int ks = 4; ks >= 2; ks /= 2)
+    if (wgs(ks, avg) <= kCus && wgs(ks, max_rows) <= 8 * kCus) return ks;
+  if (wgs(1, avg) <= 3 * kCus / 4 && wgs(2, max_rows) <= 8 * kCus && max_rows >= 640 && capacity < 2 * (int64_t)max_rows)
+    return 2;
+  return 1;
+}
 
 SM_API sm_status sm_prefill_attention(const sm_paged_cache *c, const int32_t *seq_ids, int n,
                                       const int32_t *q_offsets, int total_rows, const void *q, int num_q_heads,
@@ -409,7 +500,8 @@ SM_API sm_status sm_prefill_attention(const sm_paged_cache *c, const int32_t *se
   a.Hkv = H;
   a.Hq = num_q_heads;
   a.G = G;
-  a.BQ = kPfVec / G;
+  const int ks = pf_key_splits(n, H, G, total_rows, max_rows, (int64_t)c->max_blocks_per_seq * bs);
+  a.BQ = kPfVec / ks / G;
   int bl = 0;
   while ((1 << bl) < bs) ++bl;
   a.bs_log2 = bl;
@@ -425,9 +517,16 @@ SM_API sm_status sm_prefill_attention(const sm_paged_cache *c, const int32_t *se
   if ((int64_t)nqb * n * H > 0x7fffffff) return SM_EINVAL;
   a.nqb = nqb;
   const dim3 grid(nqb * n * H);
-  if (D == 128)
-    hipLaunchKernelGGL(prefill_bf16<128>, grid, dim3(kPfThreads), 0, stream, a);
-  else
-    hipLaunchKernelGGL(prefill_bf16<64>, grid, dim3(kPfThreads), 0, stream, a);
+#define SM_PF_LAUNCH(DH, KS) hipLaunchKernelGGL((prefill_bf16<DH, KS>), grid, dim3(kPfThreads), 0, stream, a)
+  if (D == 128) {
+    if (ks == 1) SM_PF_LAUNCH(128, 1);
+    else if (ks == 2) SM_PF_LAUNCH(128, 2);
+    else SM_PF_LAUNCH(128, 4);
+  } else {
+    if (ks == 1) SM_PF_LAUNCH(64, 1);
+    else if (ks == 2) SM_PF_LAUNCH(64, 2);
+    else SM_PF_LAUNCH(64, 4);
+  }
+#undef SM_PF_LAUNCH
   return hipGetLastError() == hipSuccess ? SM_OK : SM_EHIP;
 }

@@ -69,6 +69,41 @@ def test_prefill_matches_oracle(orc, case):
     assert e <= TOL[torch.bfloat16]
 
 
+# Hq, H, D, bs, lens, rows per request: the waves in four groups (32-key tiles,
+# 128 keys a pass), two groups (64 and 128), and one, at the edges of tiles and
+# passes, with contexts before the rows and vectors that fill no whole block
+SPLIT_CASES = [
+    (32, 8, 128, 16, [127, 128, 129, 33], [127, 128, 100, 33]),
+    (12, 1, 128, 32, [700, 97, 31, 32], [150, 97, 1, 20]),        # group of 12: 5 positions, 4 vectors idle
+    (16, 1, 64, 512, [1100, 385], [65, 385]),
+    (28, 4, 128, 16, [1301, 1025], [40, 63]),                       # few rows after a long context
+    (8, 8, 128, 64, [512, 300, 511, 400, 129], None),               # two groups
+    (28, 4, 128, 16, [150, 151, 190, 256, 129, 127], [150, 151, 100, 150, 129, 127]),
+    (16, 4, 64, 16, [140] * 9 + [1], None),
+    (64, 8, 128, 16, [670], None),                                   # a whole prompt over 3/4 of the units
+    (64, 8, 64, 32, [258] * 7, [200] * 7),                           # one group
+]
+
+
+@pytest.mark.parametrize("case", range(len(SPLIT_CASES)))
+def test_prefill_key_split(orc, case):
+    Hq, H, D, bs, lens, ms = SPLIT_CASES[case]
+    rng = np.random.RandomState(500 + case)
+    ms = list(lens) if ms is None else ms
+    oc, c = _cache(orc, rng, H, D, bs, lens)
+    ids = np.arange(len(lens), dtype=np.int32)
+    qo = np.concatenate([[0], np.cumsum(ms)]).astype(np.int32)
+    q = wl.randn((int(qo[-1]), Hq, D), torch.bfloat16, wl.generator(600 + case), std=3.0)  # references that move
+    st, ref = oc.prefill_attention(ids, qo, wl.to_f64(q), Hq, D ** -0.5)
+    assert st == orc.OK
+    say("prefill key split", Hq, H, D, bs, lens, ms)
+    out = _gpu_prefill(c, ids, qo, q, max(ms))
+    assert c.error_bits() == 0
+    e = rel_l2_max(out, ref)
+    say("rel_l2_max", e)
+    assert e <= TOL[torch.bfloat16]
+
+
 @pytest.mark.parametrize("scale", [-0.09, 0.0, 0.4])
 def test_prefill_scale_values(orc, scale):
     """Negative, zero (the plain mean of the visible V rows) and large scales."""
