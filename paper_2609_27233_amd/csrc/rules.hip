@@ -13,15 +13,18 @@
 //    twice resolves to its first index.  A second pass copies the keys into
 //    the slots.  No thread ever waits on another.
 //  * Prompt matching ("Rule Matching": left to right, 4-, 3-, then 2-grams,
-//    take the longest match and jump past it, else step one token):
-//      1. every position looks up its longest rule (independent lookups);
-//      2. per sequence, the greedy chain is a composition of maps: a chunk
-//         of positions maps the chain's entry offset (0..3 past the chunk
-//         start) to its exit offset, four entries of two bits.  A workgroup
-//         scan of these maps gives every chunk its true entry, and each
-//         chunk then emits its spans at scanned offsets;
-//      3. the sequences' span counts are scanned into CSR offsets and the
-//         spans are compacted.
+//    take the longest match and jump past it, else step one token).  The
+//    greedy chain is a composition of maps: a stretch of positions maps the
+//    chain's entry offset (0..3 past its start) to its exit offset, and to
+//    the number of spans taken on the way.  No window crosses a sequence's
+//    end, so the chain lands on every sequence start by itself and the whole
+//    batch is one chain, cut into blocks of 256 positions whatever the
+//    sequences' lengths:
+//      1. every position looks up its longest rule (independent lookups) and
+//         every block folds its maps into one;
+//      2. every block folds the maps of the blocks before it (its true entry
+//         and the spans before it) and emits its spans at their final place,
+//         and the CSR offset of every sequence that starts in it.
 //    The result is exactly the sequential scan's.
 //  * Decode matching ("Decoding-time Integration"): per sequence a 16-byte
 //    state (number of raw tokens since the last merge, capped at 3, and
@@ -75,9 +78,13 @@ __device__ __forceinline__ int rule_find(const i32x4_t *keys, const int32_t *ids
 }
 
 // The longest of up to three candidate keys (cand[0] the longest) that is a
-// rule: the three probe chains advance together, so their memory latencies
-// overlap instead of adding up.  want[c] = false skips a candidate.  Returns
-// the index of the winning candidate (or -1) and its rule id in *id.
+// rule: the three probe chains advance together, kProbe slots of each at a
+// time, so their memory latencies overlap instead of adding up (a wave waits
+// for the longest of its 192 chains; the slots of a round mostly share a
+// 128-byte line).  want[c] = false skips a candidate.  Returns the index of
+// the winning candidate (or -1) and its rule id in *id.
+constexpr int kProbe = 4;
+
 __device__ __forceinline__ int rule_find_longest(const i32x4_t *keys, const int32_t *ids, uint32_t mask,
                                                  const i32x4_t (&cand)[3], const bool (&want)[3], int *id) {
   uint32_t slot[3];
@@ -87,21 +94,25 @@ __device__ __forceinline__ int rule_find_longest(const i32x4_t *keys, const int3
     slot[c] = (uint32_t)rule_hash(cand[c]) & mask;
     state[c] = want[c] ? -2 : -1;
   }
-  for (uint32_t p = 0; p <= mask; ++p) {
-    i32x4_t e[3];
+  for (uint32_t p = 0; p <= mask; p += kProbe) {  // (the capacity is a multiple of kProbe)
+    i32x4_t e[3][kProbe];
 #pragma unroll
     for (int c = 0; c < 3; ++c)
-      if (state[c] == -2) e[c] = keys[slot[c]];
+      if (state[c] == -2)
+#pragma unroll
+        for (int k = 0; k < kProbe; ++k) e[c][k] = keys[(slot[c] + k) & mask];
     bool busy = false;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       if (state[c] != -2) continue;
-      if (e[c].x == -1) state[c] = -1;
-      else if (key_eq(e[c], cand[c])) state[c] = (int)slot[c];
-      else {
-        slot[c] = (slot[c] + 1) & mask;
-        busy = true;
+#pragma unroll
+      for (int k = 0; k < kProbe; ++k) {
+        if (state[c] != -2) continue;
+        if (e[c][k].x == -1) state[c] = -1;
+        else if (key_eq(e[c][k], cand[c])) state[c] = (int)((slot[c] + k) & mask);
       }
+      slot[c] = (slot[c] + kProbe) & mask;
+      busy |= state[c] == -2;
     }
     if (!busy) break;
   }
@@ -170,22 +181,108 @@ __global__ void rules_lookup_kernel(const i32x4_t *keys, const int32_t *ids, uin
 
 // ---- prompt matching --------------------------------------------------------
 
-// 1. longest rule starting at every position (0 = none) and its id
-__global__ void match_len_kernel(const i32x4_t *keys, const int32_t *ids, uint32_t mask, const int32_t *tokens,
-                                 const int32_t *seq_offsets, int B, int total, int8_t *mlen, int32_t *rid) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= total) return;
+constexpr int kMatchBlock = 256;                  // positions per block, folded by one wave
+constexpr int kMatchLane = kMatchBlock / 64;      // positions per lane of that wave
+// The lookups want many compute units (each lane's probe is a line of its own,
+// one lane per cycle and unit: 32,768 positions take 23 us on 128 workgroups
+// of 256, 38 on 32 of 1024); the emit pass is a chain of short dependent
+// accesses that cost more the more units make them at once (15 us on 128
+// workgroups of one block, 10 on 32 of four).
+constexpr int kEmitBlocks = 4;
+constexpr int kEmitThreads = 64 * kEmitBlocks;
+constexpr int kMatchLds = 2048;                   // sequence offsets held in LDS
+constexpr uint32_t kMapIdentity = 0xE4u;          // e -> e, two bits per entry
+
+// What a stretch of positions does to the chain: entry offset e leaves at
+// offset (map >> 2 e) & 3 past the stretch's end, after cnt[e] spans.
+struct ChainFold {
+  uint32_t map;
+  int cnt[4];
+};
+
+__device__ __forceinline__ int pick4(const int (&v)[4], uint32_t i) {
+  return i < 2 ? (i == 0 ? v[0] : v[1]) : (i == 2 ? v[2] : v[3]);
+}
+__device__ __forceinline__ uint32_t map_at(uint32_t f, uint32_t e) { return (f >> (2 * e)) & 3u; }
+// f, then g
+__device__ __forceinline__ uint32_t map_then(uint32_t f, uint32_t g) {
+  uint32_t h = 0;
+#pragma unroll
+  for (uint32_t e = 0; e < 4; ++e) h |= map_at(g, map_at(f, e)) << (2 * e);
+  return h;
+}
+
+// the fold of a lane's kMatchLane positions, match lengths (0 = none) in
+// 4-bit fields of L
+__device__ __forceinline__ ChainFold lane_fold(uint32_t L) {
+  ChainFold f;
+  f.map = 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    int p = e, c = 0;
+#pragma unroll
+    for (int step = 0; step < kMatchLane; ++step)
+      if (p < kMatchLane) {
+        const int len = (int)((L >> (4 * p)) & 15u);
+        c += len ? 1 : 0;
+        p += max(len, 1);
+      }
+    f.map |= (uint32_t)(p - kMatchLane) << (2 * e);
+    f.cnt[e] = c;
+  }
+  return f;
+}
+
+// Inclusive scan of the lanes' maps.  Only the maps are scanned: with a
+// lane's entry known, the spans before it are an ordinary prefix sum.
+__device__ __forceinline__ uint32_t wave_map_scan(uint32_t f) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t g = __shfl_up(f, off, kWave);
+    if (lane >= off) f = map_then(g, f);
+  }
+  return f;
+}
+// the map before lane l, from the inclusive scan
+__device__ __forceinline__ uint32_t map_before(uint32_t incl) {
+  const uint32_t g = __shfl_up(incl, 1, kWave);
+  return (threadIdx.x & 63) ? g : kMapIdentity;
+}
+
+// spans of a block's fold entered at offset e
+__device__ __forceinline__ int fold_count(uint64_t v, uint32_t e) { return (int)(v >> (8 + 8 * e)) & 255; }
+
+// match lengths of the four positions of a lane, bytes -> 4-bit fields
+__device__ __forceinline__ uint32_t pack_lens(uint32_t v) {
+  return (v & 15u) | ((v >> 4) & 0xf0u) | ((v >> 8) & 0xf00u) | ((v >> 12) & 0xf000u);
+}
+
+// 1. longest rule starting at every position (0 = none) and its id; the
+// block's fold: map in bits 0-7, cnt[e] (at most 128) in bits 8 + 8 e
+__global__ __launch_bounds__(kMatchBlock) void match_len_kernel(const i32x4_t *keys, const int32_t *ids, uint32_t mask,
+                                                                const int32_t *tokens, const int32_t *seq_offsets,
+                                                                int B, int total, int8_t *mlen, int32_t *rid,
+                                                                uint64_t *folds) {
+  __shared__ int so[kMatchLds];
+  __shared__ uint32_t lens[kMatchBlock / 4];
+  const int tid = threadIdx.x, t = blockIdx.x * kMatchBlock + tid;
+  int x[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) x[j] = t + j < total ? tokens[t + j] : -1;
+  const bool in_lds = B + 1 <= kMatchLds;
+  if (in_lds)
+    for (int b = tid; b <= B; b += kMatchBlock) so[b] = seq_offsets[b];
+  __syncthreads();
+  const int *off = in_lds ? so : seq_offsets;
   // the sequence holding t: the last b with seq_offsets[b] <= t
   int lo = 0, hi = B - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
-    if (seq_offsets[mid] <= t) lo = mid;
+    if (off[mid] <= t) lo = mid;
     else hi = mid - 1;
   }
-  const int end = min(seq_offsets[lo + 1], total);
-  int x[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) x[j] = t + j < end ? tokens[t + j] : -1;
+  const int end = t >= off[0] ? min(off[lo + 1], total) : 0;  // (positions of no sequence match nothing)
   i32x4_t cand[3];
   bool want[3];
 #pragma unroll
@@ -200,121 +297,203 @@ __global__ void match_len_kernel(const i32x4_t *keys, const int32_t *ids, uint32
   int id;
   const int c = rule_find_longest(keys, ids, mask, cand, want, &id);
   const int len = c >= 0 ? 4 - c : 0;
-  mlen[t] = (int8_t)len;
-  rid[t] = id;
-}
-
-constexpr int kSelThreads = 256;
-constexpr int kSelChunk = 16;                        // positions per thread
-constexpr int kSelSeg = kSelThreads * kSelChunk;     // positions per workgroup pass
-constexpr uint32_t kMapIdentity = 0xE4u;             // e -> e, two bits per entry
-
-__device__ __forceinline__ uint32_t map_at(uint32_t f, uint32_t e) { return (f >> (2 * e)) & 3u; }
-// g after f
-__device__ __forceinline__ uint32_t map_then(uint32_t f, uint32_t g) {
-  uint32_t h = 0;
+  if (t < total) {
+    mlen[t] = (int8_t)len;
+    rid[t] = id;
+  }
+  ((uint8_t *)lens)[tid] = (uint8_t)len;
+  __syncthreads();
+  if (tid < 64) {
+    const ChainFold f = lane_fold(pack_lens(lens[tid]));
+    const uint32_t incl = wave_map_scan(f.map), before = map_before(incl);
+    uint64_t word = 0;
 #pragma unroll
-  for (uint32_t e = 0; e < 4; ++e) h |= map_at(g, map_at(f, e)) << (2 * e);
-  return h;
+    for (int e = 0; e < 4; ++e) {  // (sums of at most 128, exact in fp32)
+      const float c = wave_sum((float)pick4(f.cnt, map_at(before, e)));
+      word |= (uint64_t)(uint32_t)c << (8 + 8 * e);
+    }
+    if (tid == 63) folds[blockIdx.x] = word | incl;
+  }
 }
 
-// 2. the greedy chain of one sequence per workgroup; spans go to the
-// sequence's own region of the temporary arrays (at its first token)
-__global__ __launch_bounds__(kSelThreads) void match_select_kernel(const int8_t *mlen, const int32_t *rid,
-                                                                   const int32_t *seq_offsets, int total,
-                                                                   int32_t *tmp_start, int32_t *tmp_len,
-                                                                   int32_t *tmp_rule, int32_t *count,
-                                                                   int32_t *err) {
-  __shared__ uint32_t maps[kSelThreads];
-  __shared__ int red[16];
-  const int b = blockIdx.x, tid = threadIdx.x;
-  const int lo = seq_offsets[b], hi = seq_offsets[b + 1];
-  if (!(lo >= 0 && lo <= hi && hi <= total)) {
-    if (tid == 0) {
-      set_err(err, SM_ERR_EINVAL);
-      count[b] = 0;
+// Offsets out of order or range: their sequences get no spans, the others
+// theirs, one sequence after the other by one workgroup (an error path: such
+// a batch is not one chain).  The match lengths go through LDS; one thread
+// walks them.
+__device__ void match_bad_offsets(const int8_t *mlen, const int32_t *rid, const int32_t *seq_offsets, int B, int total,
+                                  int32_t *span_start, int32_t *span_len, int32_t *span_rule,
+                                  int32_t *seq_span_offsets, int32_t *err) {
+  constexpr int kPart = 4096;
+  __shared__ int8_t part[kPart];
+  const int tid = threadIdx.x;
+  int o = 0;  // (thread 0's)
+  for (int b = 0; b < B; ++b) {
+    const int lo = seq_offsets[b], hi = seq_offsets[b + 1];
+    if (tid == 0) seq_span_offsets[b] = o;
+    if (!(lo >= 0 && lo <= hi && hi <= total)) {
+      if (tid == 0) set_err(err, SM_ERR_EINVAL);
+      continue;
     }
+    int p = lo;
+    for (int q = lo; q < hi; q += kPart) {
+      const int n = min(kPart, hi - q);
+      __syncthreads();
+      for (int j = tid; j < n; j += kEmitThreads) part[j] = mlen[q + j];
+      __syncthreads();
+      if (tid == 0)
+        while (p < q + n) {
+          const int len = part[p - q];
+          if (len && o < total / 2) {  // (overlapping sequences must not outgrow the outputs)
+            span_start[o] = p;
+            span_len[o] = len;
+            span_rule[o] = rid[p];
+            ++o;
+          }
+          p += max(len, 1);
+        }
+    }
+  }
+  if (tid == 0) seq_span_offsets[B] = o;
+}
+
+// 2. the spans of a workgroup's blocks (one per wave) at their final place,
+// and the CSR offsets of the sequences that start in them
+__global__ __launch_bounds__(kEmitThreads) void match_emit_kernel(const int8_t *mlen, const int32_t *rid,
+                                                                  const uint64_t *folds, const int32_t *seq_offsets,
+                                                                  int B, int total, int nwg, int32_t *span_start,
+                                                                  int32_t *span_len, int32_t *span_rule,
+                                                                  int32_t *seq_span_offsets, int32_t *err) {
+  __shared__ uint32_t wmap[kEmitBlocks];
+  __shared__ int wsum[kEmitBlocks], spans_end;
+  __shared__ int so[kMatchLds];
+  __shared__ int lane_entry[kEmitThreads], lane_before[kEmitThreads];
+  __shared__ uint32_t lane_len[kEmitThreads];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int blk0 = blockIdx.x * kEmitBlocks;  // this workgroup's first block
+  const int c0 = blk0 * kMatchBlock, c1 = min(c0 + kEmitBlocks * kMatchBlock, total);
+  const bool last = (int)blockIdx.x == nwg - 1;
+  if (B == 0) {
+    if (tid == 0) seq_span_offsets[0] = 0;
     return;
   }
-  const int T = hi - lo;
-  int carry = 0, written = 0;
-  for (int seg = 0; seg < T; seg += kSelSeg) {
-    const int c0 = seg + tid * kSelChunk;  // my chunk [c0, c0 + 16) of the sequence
-    // the chunk's match lengths, four bits each: step(p) = length or 1
-    uint64_t Lp = 0;
+  // Four positions' match lengths and ids per lane, the folds of a block
+  // before the workgroup's and of its own, and the offsets: all requested
+  // before any is used (lanes past the batch's end read its last four and
+  // mask them)
+  const int t0 = c0 + kMatchLane * tid;
+  const int tc = min(t0, max(total - 1, 0) & ~(kMatchLane - 1));
+  const uint32_t lens4 = *(const uint32_t *)(mlen + tc);
+  const i32x4_t id4 = *(const i32x4_t *)(rid + tc);
+  const int per = (blk0 + kEmitThreads - 1) / kEmitThreads;  // blocks before, a contiguous share per thread
+  uint64_t fold = folds[min(tid * per, blk0)];
+  uint64_t own[kEmitBlocks];
 #pragma unroll
-    for (int j = 0; j < kSelChunk; ++j)
-      Lp |= (uint64_t)(c0 + j < T ? (uint8_t)mlen[lo + c0 + j] : 0u) << (4 * j);
-    auto len_at = [&](int p) { return (int)((Lp >> (4 * p)) & 15u); };
-    uint32_t f = 0;
+  for (int k = 0; k < kEmitBlocks; ++k) own[k] = folds[blk0 + k];
+  int o_lo = seq_offsets[min(tid, B)], o_hi = seq_offsets[min(tid + 1, B)];
+  ChainFold f{kMapIdentity, {0, 0, 0, 0}};
+  for (int k = tid * per; k < min((tid + 1) * per, blk0); ++k) {
+    if (k > tid * per) fold = folds[k];
+    const int cnt[4] = {fold_count(fold, 0), fold_count(fold, 1), fold_count(fold, 2), fold_count(fold, 3)};
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      int p = e;
-      while (p < kSelChunk) p += max(len_at(p), 1);
-      f |= (uint32_t)(p - kSelChunk) << (2 * e);
+    for (int e = 0; e < 4; ++e) f.cnt[e] += pick4(cnt, map_at(f.map, e));
+    f.map = map_then(f.map, (uint32_t)fold & 255u);
+  }
+  // offsets in order and range?
+  const bool in_lds = B + 1 <= kMatchLds;
+  bool bad = false;
+  for (int b = tid; b <= B; b += kEmitThreads) {
+    if (b > tid) {
+      o_lo = seq_offsets[b];
+      o_hi = seq_offsets[min(b + 1, B)];
     }
-    // inclusive scan of the maps: thread j gets F_j after ... after F_0
-    maps[tid] = f;
-    for (int d = 1; d < kSelThreads; d <<= 1) {
-      __syncthreads();
-      const uint32_t g = tid >= d ? maps[tid - d] : kMapIdentity;
-      __syncthreads();
-      maps[tid] = map_then(g, maps[tid]);
+    if (in_lds) so[b] = o_lo;
+    if (b < B) bad |= !(o_lo >= 0 && o_lo <= o_hi && o_hi <= total);
+  }
+  const uint32_t incl = wave_map_scan(f.map);
+  if (lane == 63) wmap[w] = incl;
+  if (__syncthreads_or(bad)) {
+    if (blockIdx.x == 0)
+      match_bad_offsets(mlen, rid, seq_offsets, B, total, span_start, span_len, span_rule, seq_span_offsets, err);
+    return;
+  }
+  // the chain enters the batch at offset 0: the entry of this thread's
+  // share, and the spans of all shares
+  uint32_t entry = 0;
+  for (int k = 0; k < w; ++k) entry = map_at(wmap[k], entry);
+  int c = pick4(f.cnt, map_at(map_before(incl), entry));
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) c += __shfl_xor(c, off, kWave);
+  if (lane == 0) wsum[w] = c;
+  __syncthreads();
+  int before = 0;  // spans before, and entry of, this wave's block
+  entry = 0;
+#pragma unroll
+  for (int k = 0; k < kEmitBlocks; ++k) {
+    before += wsum[k];
+    entry = map_at(wmap[k], entry);
+  }
+#pragma unroll
+  for (int k = 0; k < kEmitBlocks; ++k)
+    if (k < w && total > 0) {  // (no tokens: no folds were written)
+      before += fold_count(own[k], entry);
+      entry = map_at((uint32_t)own[k] & 255u, entry);
     }
-    __syncthreads();
-    const uint32_t before = tid > 0 ? maps[tid - 1] : kMapIdentity;
-    const int entry = (int)map_at(before, (uint32_t)carry);
-    const int seg_exit = (int)map_at(maps[kSelThreads - 1], (uint32_t)carry);
-    // my spans from my true entry
-    int k = 0;
-    for (int p = entry; p < kSelChunk; p += max(len_at(p), 1)) k += len_at(p) ? 1 : 0;
-    int tot;
-    const int off = block_inclusive_scan(k, red, &tot) - k;
-    int o = lo + written + off;
-    for (int p = entry; p < kSelChunk; p += max(len_at(p), 1)) {
-      if (len_at(p)) {
-        tmp_start[o] = lo + c0 + p;
-        tmp_len[o] = len_at(p);
-        tmp_rule[o] = rid[lo + c0 + p];
+  uint32_t L = pack_lens(lens4);
+#pragma unroll
+  for (int j = 0; j < kMatchLane; ++j)
+    if (t0 + j >= total) L &= ~(15u << (4 * j));
+  const ChainFold x = lane_fold(L);
+  const int e0 = (int)map_at(map_before(wave_map_scan(x.map)), entry);
+  const int mine = pick4(x.cnt, (uint32_t)e0);
+  int k0 = mine;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int u = __shfl_up(k0, off, kWave);
+    if (lane >= off) k0 += u;
+  }
+  if (tid == kEmitThreads - 1) spans_end = before + k0;  // spans up to the workgroup's end
+  k0 += before - mine;
+  const int id[kMatchLane] = {id4.x, id4.y, id4.z, id4.w};
+  int o = k0;
+#pragma unroll
+  for (int j = 0, p = e0; j < kMatchLane; ++j)
+    if (p < kMatchLane) {
+      const int len = (int)((L >> (4 * p)) & 15u);
+      if (len) {
+        span_start[o] = t0 + p;
+        span_len[o] = len;
+        span_rule[o] = pick4(id, (uint32_t)p);
         ++o;
       }
+      p += max(len, 1);
     }
-    written += tot;
-    carry = seg_exit;
-    __syncthreads();  // maps and red are reused by the next pass
+  lane_entry[tid] = e0;
+  lane_before[tid] = k0;
+  lane_len[tid] = L;
+  __syncthreads();
+  // a sequence starting at t: the spans whose start is before t
+  const int *off = in_lds ? so : seq_offsets;
+  int b0 = 0, hi = B + 1;  // first b with off[b] >= c0
+  while (b0 < hi) {
+    const int mid = (b0 + hi) >> 1;
+    if (off[mid] >= c0) hi = mid;
+    else b0 = mid + 1;
   }
-  if (tid == 0) count[b] = written;
-}
-
-// 3a. CSR offsets of the spans: exclusive scan of the counts (one workgroup)
-__global__ __launch_bounds__(kSelThreads) void match_offsets_kernel(const int32_t *count, int B,
-                                                                    int32_t *seq_span_offsets) {
-  __shared__ int red[16];
-  int base = 0;
-  for (int b0 = 0; b0 < B; b0 += kSelThreads) {
-    const int b = b0 + threadIdx.x;
-    const int c = b < B ? count[b] : 0;
-    int tot;
-    const int inc = block_inclusive_scan(c, red, &tot);
-    if (b < B) seq_span_offsets[b] = base + inc - c;
-    base += tot;
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) seq_span_offsets[B] = base;
-}
-
-// 3b. compaction: sequence b's spans from its region to its CSR range
-__global__ __launch_bounds__(kSelThreads) void match_compact_kernel(const int32_t *seq_offsets, const int32_t *count,
-                                                                    const int32_t *seq_span_offsets,
-                                                                    const int32_t *tmp_start, const int32_t *tmp_len,
-                                                                    const int32_t *tmp_rule, int32_t *span_start,
-                                                                    int32_t *span_len, int32_t *span_rule) {
-  const int b = blockIdx.x;
-  const int n = count[b], src = seq_offsets[b], dst = seq_span_offsets[b];
-  for (int j = threadIdx.x; j < n; j += kSelThreads) {
-    span_start[dst + j] = tmp_start[src + j];
-    span_len[dst + j] = tmp_len[src + j];
-    span_rule[dst + j] = tmp_rule[src + j];
+  for (int b = b0 + tid; b <= B; b += kEmitThreads) {
+    const int t = off[b];
+    if (t >= c1 && !last) break;
+    int k = spans_end;
+    if (t < c1) {
+      const int l = (t - c0) / kMatchLane, pe = (t - c0) % kMatchLane;
+      const uint32_t Lt = lane_len[l];
+      k = lane_before[l];
+      for (int p = lane_entry[l]; p < pe;) {
+        const int len = (int)((Lt >> (4 * p)) & 15u);
+        k += len ? 1 : 0;
+        p += max(len, 1);
+      }
+    }
+    seq_span_offsets[b] = k;
   }
 }
 
@@ -431,24 +610,18 @@ SM_API sm_status sm_match_prompt(const sm_rule_table *t, const int32_t *token_id
   p += align256(T);
   int32_t *rid = (int32_t *)p;
   p += align256(4 * T);
-  int32_t *tmp_start = (int32_t *)p;
-  p += align256(4 * T);
-  int32_t *tmp_len = (int32_t *)p;
-  p += align256(4 * T);
-  int32_t *tmp_rule = (int32_t *)p;
-  p += align256(4 * T);
-  int32_t *count = (int32_t *)p;
+  uint64_t *folds = (uint64_t *)p;  // 8 bytes per 256 positions
   const uint32_t mask = (uint32_t)(t->capacity - 1);
-  if (B > 0 && total_tokens > 0)
-    hipLaunchKernelGGL(match_len_kernel, dim3((total_tokens + 255) / 256), dim3(256), 0, stream,
-                       (const i32x4_t *)t->keys, t->ids, mask, token_ids, seq_offsets, B, total_tokens, mlen, rid);
-  if (B > 0)
-    hipLaunchKernelGGL(match_select_kernel, dim3(B), dim3(kSelThreads), 0, stream, mlen, rid, seq_offsets,
-                       total_tokens, tmp_start, tmp_len, tmp_rule, count, t->err);
-  hipLaunchKernelGGL(match_offsets_kernel, dim3(1), dim3(kSelThreads), 0, stream, count, B, seq_span_offsets);
-  if (B > 0)
-    hipLaunchKernelGGL(match_compact_kernel, dim3(B), dim3(kSelThreads), 0, stream, seq_offsets, count,
-                       seq_span_offsets, tmp_start, tmp_len, tmp_rule, span_start, span_len, span_rule);
+  // (whole emit workgroups: blocks past the last token fold to nothing)
+  const int nemit = (total_tokens + kEmitBlocks * kMatchBlock - 1) / (kEmitBlocks * kMatchBlock);
+  const bool any = B > 0 && nemit > 0;
+  if (any)
+    hipLaunchKernelGGL(match_len_kernel, dim3(nemit * kEmitBlocks), dim3(kMatchBlock), 0, stream,
+                       (const i32x4_t *)t->keys, t->ids, mask, token_ids, seq_offsets, B, total_tokens, mlen, rid, folds);
+  // (no sequences, or no tokens: only the offsets, all zero)
+  hipLaunchKernelGGL(match_emit_kernel, dim3(any ? nemit : 1), dim3(kEmitThreads), 0, stream, mlen, rid, folds,
+                     seq_offsets, B, B > 0 ? total_tokens : 0, any ? nemit : 1, span_start, span_len, span_rule,
+                     seq_span_offsets, t->err);
   return hipGetLastError() == hipSuccess ? SM_OK : SM_EHIP;
 }
 

@@ -1,0 +1,153 @@
+"""Prompt matching and pack indices at the edges of their pieces (256 and 1024
+or 4096 positions of the whole batch, whatever the sequences' lengths), against
+the oracle, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import dev, i32, say
+from paper_2609_27233_amd import lib as sm
+
+pytestmark = pytest.mark.gpu
+
+
+def _rules(rng, count, V):
+    out = np.full((count, 4), -1, np.int32)
+    for r in range(count):
+        n = rng.randint(2, 5)
+        out[r, :n] = rng.randint(0, V, n)
+    return out
+
+
+MATCH = [
+    # vocabulary, rules, lengths
+    (5, 30, [255, 1, 256, 257, 0, 511, 2, 0, 0, 1]),      # sequences that end and start on block edges
+    (3, 9, [256] * 5),
+    (4, 12, [1] * 700),                                     # no window fits
+    (6, 40, [3] * 2500),                                    # offsets beyond the LDS copy
+    (4, 20, [70000, 5]),                                    # more blocks than threads that fold them
+    (2, 3, [1023]),
+]
+
+
+@pytest.mark.parametrize("case", range(len(MATCH)))
+def test_match_prompt_block_edges(orc, case):
+    V, nr, lens = MATCH[case]
+    rng = np.random.RandomState(900 + case)
+    rules = _rules(rng, nr, V)
+    offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    T, B = int(offs[-1]), len(lens)
+    toks = rng.randint(0, V, T).astype(np.int32)
+    st, s0, ln, ru, sso = orc.OracleRules(rules).match_prompt(toks, offs)
+    assert st == orc.OK
+    t = sm.RuleTable(sm.RuleTable.capacity_for(nr))
+    sm.rules_build(t, i32(rules))
+    out = [torch.full((T // 2 + 1,), -7, dtype=torch.int32, device=dev()) for _ in range(3)]
+    gs = torch.full((B + 1,), -7, dtype=torch.int32, device=dev())
+    ws = torch.empty(sm.match_prompt_workspace_bytes(B, T), dtype=torch.uint8, device=dev())
+    say("match blocks", V, nr, lens[:10], "spans", len(s0))
+    sm.match_prompt(t, i32(toks), i32(offs), *out, gs, ws)
+    torch.cuda.synchronize()
+    assert t.error_bits() == 0
+    np.testing.assert_array_equal(gs.cpu().numpy(), sso)
+    for got, ref in zip(out, (s0, ln, ru)):
+        np.testing.assert_array_equal(got.cpu().numpy()[:len(s0)], ref)
+        assert (got.cpu().numpy()[len(s0):] == -7).all()
+
+
+def test_match_prompt_bad_offsets_keep_the_good_sequences(orc):
+    """A sequence past the end of the tokens gets no spans and EINVAL; those
+    before it get theirs."""
+    rng = np.random.RandomState(5)
+    rules = _rules(rng, 30, 5)
+    toks = rng.randint(0, 5, 6000).astype(np.int32)
+    good = np.array([0, 300, 5200], np.int32)
+    st, s0, ln, ru, sso = orc.OracleRules(rules).match_prompt(toks[:5200], good)
+    t = sm.RuleTable(sm.RuleTable.capacity_for(30))
+    sm.rules_build(t, i32(rules))
+    out = [torch.full((3000,), -7, dtype=torch.int32, device=dev()) for _ in range(3)]
+    gs = torch.full((4,), -7, dtype=torch.int32, device=dev())
+    ws = torch.empty(sm.match_prompt_workspace_bytes(3, 6000), dtype=torch.uint8, device=dev())
+    say("match with a sequence out of range")
+    sm.match_prompt(t, i32(toks), i32([0, 300, 5200, 6001]), *out, gs, ws)
+    torch.cuda.synchronize()
+    assert t.error_bits() == sm.ERR_EINVAL
+    assert gs.cpu().tolist() == sso.tolist() + [len(s0)]
+    for got, ref in zip(out, (s0, ln, ru)):
+        np.testing.assert_array_equal(got.cpu().numpy()[:len(s0)], ref)
+
+
+PACK = [
+    # lengths, longest span
+    ([1023, 1, 1024, 1025, 0, 2047, 2, 0], 8),
+    ([1] * 3000, 1),                                        # one-token spans remove nothing
+    ([7] * 4500, 5),                                        # offsets beyond the LDS copies
+    ([5000, 3000], 2600),                                   # spans longer than a piece
+    ([260000, 5000], 6),                                    # more than 256 pieces of 1024
+    ([0, 0], 4),
+]
+
+
+@pytest.mark.parametrize("case", range(len(PACK)))
+def test_pack_piece_edges(orc, case):
+    lens, nmax = PACK[case]
+    rng = np.random.RandomState(950 + case)
+    offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    start, ln, sso = [], [], [0]
+    for b, T in enumerate(lens):
+        t = 0
+        while t < T:
+            n = int(min(T - t, rng.randint(1, nmax + 1)))
+            if rng.rand() < 0.6:
+                start.append(offs[b] + t)
+                ln.append(n)
+            t += n
+        sso.append(len(start))
+    start, ln, sso = (np.asarray(v, np.int32) for v in (start, ln, sso))
+    T, B = int(offs[-1]), len(lens)
+    st, res = orc.pack_spans(offs, start, ln, sso)
+    assert st == orc.OK
+    pi, src = (torch.full((max(T, 1),), -7, dtype=torch.int32, device=dev()) for _ in range(2))
+    po = torch.full((B + 1,), -7, dtype=torch.int32, device=dev())
+    err = torch.zeros(1, dtype=torch.int32, device=dev())
+    say("pack pieces", lens[:8], "spans", len(start))
+    if len(start):
+        sm.pack_spans(i32(offs), i32(start), i32(ln), i32(sso), pi, po, src, err, T)
+    else:                                                   # (no spans: any pointer will do)
+        sm.pack_spans(i32(offs), i32([0])[:0], i32([0])[:0], i32(sso), pi, po, src, err, T)
+    torch.cuda.synchronize()
+    assert int(err.item()) == 0
+    np.testing.assert_array_equal(po.cpu().numpy(), res["packed_offsets"])
+    np.testing.assert_array_equal(pi.cpu().numpy()[:T], res["pi"])
+    np.testing.assert_array_equal(src.cpu().numpy()[:po[-1].item()], res["packed_src"])
+
+
+@pytest.mark.parametrize("S,rules", [(1, 3), (256, 4), (257, 1), (5000, 900), (1100000, 700000)])
+def test_dedupe_block_edges(orc, S, rules):
+    """Blocks of 256 spans; the last case has more blocks than the LDS prefix."""
+    rng = np.random.RandomState(S)
+    rule = rng.randint(0, rules, S).astype(np.int32)
+    n_of = rng.randint(2, 5, rules)
+    ln = n_of[rule].astype(np.int32)
+    start = np.concatenate([[0], np.cumsum(ln)])[:-1].astype(np.int32)
+    T = int(ln.sum())
+    toks = rng.randint(0, 1000, T).astype(np.int32)
+    # first span of each rule, in order of appearance
+    uniq, first = np.unique(rule, return_index=True)
+    order = np.sort(first)
+    slot = np.empty(rules, np.int64)
+    slot[rule[order]] = np.arange(len(order))
+    rows = np.concatenate([toks[start[s]:start[s] + ln[s]] for s in order])
+    out = {k: torch.full((m,), -7, dtype=torch.int32, device=dev())
+           for k, m in (("uniq", S), ("slot", S), ("rows", T), ("offs", S + 1), ("n", 1))}
+    err = torch.zeros(1, dtype=torch.int32, device=dev())
+    say("dedupe", S, rules, "distinct", len(order))
+    sm.span_dedupe(i32(rule), i32(start), i32(ln), rules, i32(toks), out["uniq"], out["slot"], out["rows"],
+                   out["offs"], out["n"], err)
+    torch.cuda.synchronize()
+    got = {k: v.cpu().numpy() for k, v in out.items()}
+    assert int(err.item()) == 0 and got["n"][0] == len(order)
+    np.testing.assert_array_equal(got["uniq"][:len(order)], order)
+    np.testing.assert_array_equal(got["slot"], slot[rule])
+    np.testing.assert_array_equal(got["offs"][:len(order) + 1], np.concatenate([[0], np.cumsum(ln[order])]))
+    np.testing.assert_array_equal(got["rows"][:len(rows)], rows)
