@@ -566,7 +566,7 @@ __global__ __launch_bounds__(kSegWgThreads) void append_segments_kernel(CacheArg
 // pack_spans
 
 constexpr int kPackThreads = 1024;
-constexpr int kPackChunk = 4096;  // tokens per LDS pass
+constexpr int kPackMaxPer = 4;    // tokens per thread of an index workgroup
 constexpr int kRemoved = INT32_MIN;
 
 struct PackArgs {
@@ -582,47 +582,79 @@ struct PackArgs {
   int32_t *err;
 };
 
-// Every workgroup validates the whole span list (cheap) so that no
-// workgroup writes with offsets computed from invalid input.  The span ->
-// sequence search and the sequence bounds it checks read LDS copies of
-// seq_span_offsets and seq_offsets when they fit (kPackSsoLds entries),
-// else global memory; each thread loads its spans kPackBatch at a time
-// (22.4 -> 17.3 us for the index pass of a 16 x 4096-token batch, with the
-// removed-position counts folded into the same pass).
+// Index pass of pack_spans.  With R(t) the positions removed before t in the
+// whole batch, a kept token t goes to packed row t - R(t), and its compressed
+// position is that less the row of its sequence's first token.  So the
+// batch is cut into pieces of kPackThreads x PER tokens whatever its
+// sequences' lengths (one workgroup per sequence took 38 us for one sequence
+// of 32,768 tokens, 17 for 16 of 4,096), and each workgroup needs only the
+// span list: one pass over it validates all of it (so that no workgroup
+// writes with offsets computed from invalid input), counts the positions
+// removed before its piece, before the sequence that the piece begins in and
+// in all, and marks the spans that fall into its piece in LDS.  The span ->
+// sequence search and the bounds it checks read LDS copies of the offsets
+// when they fit (kPackSsoLds entries), else global memory; each thread loads
+// its spans kPackBatch at a time, so that their loads share one round trip.
+// PER is 1 up to 256 workgroups (each repeats the pass over the spans), then 4.
 constexpr int kPackSsoLds = 4096;
 
-__device__ bool pack_inputs_valid(const PackArgs &a, int *flag, int *sso, int *so, int sp0, int &removed_before,
-                                  int &removed_all) {
-  const int t = threadIdx.x;
-  if (t == 0) {
-    *flag = 0;
-    if (a.seq_offsets[0] != 0 || a.seq_offsets[a.B] != a.total_tokens ||
-        a.seq_span_offsets[0] != 0 || a.seq_span_offsets[a.B] != a.num_spans)
-      *flag = 1;
+// last b in [0, n) with v[b] <= x (v[0] <= x)
+__device__ __forceinline__ int last_le(const int *v, int n, int x) {
+  int lo = 0, hi = n - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (v[mid] <= x) lo = mid;
+    else hi = mid - 1;
   }
+  return lo;
+}
+
+template <int PER>
+__global__ __launch_bounds__(kPackThreads) void pack_index_kernel(PackArgs a) {
+  constexpr int CHUNK = kPackThreads * PER;
+  __shared__ int src[CHUNK];         // packed source of each token, then its packed row
+  __shared__ int sso[kPackSsoLds], so[kPackSsoLds];
+  __shared__ int red[16];
+  __shared__ int flag, s_err, sums[3];
+  const int t = threadIdx.x;
+  const int c0 = blockIdx.x * CHUNK, cn = min(CHUNK, a.total_tokens - c0);  // (cn = 0: a batch of no tokens)
+  const bool last = blockIdx.x == gridDim.x - 1;
+  if (t == 0) {
+    s_err = *a.err;
+    flag = a.seq_offsets[0] != 0 || a.seq_offsets[a.B] != a.total_tokens || a.seq_span_offsets[0] != 0 ||
+           a.seq_span_offsets[a.B] != a.num_spans;
+  }
+  if (t < 3) sums[t] = 0;
+#pragma unroll
+  for (int u = 0; u < PER; ++u) src[t + u * kPackThreads] = c0 + t + u * kPackThreads;
   const bool in_lds = a.B + 1 <= kPackSsoLds;
-  if (in_lds)
-    for (int b = t; b <= a.B; b += blockDim.x) {
-      sso[b] = a.seq_span_offsets[b];
-      so[b] = a.seq_offsets[b];
+  bool bad = false;
+  for (int b = t; b <= a.B; b += kPackThreads) {
+    const int s1 = a.seq_span_offsets[b], o1 = a.seq_offsets[b];
+    if (in_lds) {
+      sso[b] = s1;
+      so[b] = o1;
     }
+    if (b < a.B) bad |= a.seq_offsets[b + 1] < o1 || a.seq_span_offsets[b + 1] < s1;
+  }
   __syncthreads();
-  for (int b = t; b < a.B; b += blockDim.x)
-    if (a.seq_offsets[b + 1] < a.seq_offsets[b] || a.seq_span_offsets[b + 1] < a.seq_span_offsets[b])
-      *flag = 1;
+  if (s_err != 0) return;
+  if (bad) flag = 1;
   __syncthreads();
-  if (*flag) return false;
+  if (flag) {
+    if (blockIdx.x == 0 && t == 0) set_err(a.err, SM_ERR_EINVAL);
+    return;
+  }
   const int *sso_src = in_lds ? sso : a.seq_span_offsets;
   const int *so_src = in_lds ? so : a.seq_offsets;
-  // kPackBatch spans per thread at a time: their loads share one round trip.
-  // The same pass counts the positions the spans remove (len - 1 each), in
-  // total and before this workgroup's sequence (first span sp0).
+  const int q0 = so_src[last_le(so_src, a.B, c0)];  // start of the sequence that holds c0
+  int rem_q0 = 0, rem_c0 = 0, rem_all = 0;          // (this thread's spans)
   constexpr int kPackBatch = 4;
-  for (int s0 = t; s0 < a.num_spans; s0 += kPackBatch * (int)blockDim.x) {
+  for (int s0 = t; s0 < a.num_spans; s0 += kPackBatch * kPackThreads) {
     int st[kPackBatch], ln[kPackBatch], pe[kPackBatch];
 #pragma unroll
     for (int k = 0; k < kPackBatch; ++k) {
-      const int s = s0 + k * (int)blockDim.x;
+      const int s = s0 + k * kPackThreads;
       const bool in = s < a.num_spans;
       st[k] = in ? a.span_start[s] : 0;
       ln[k] = in ? a.span_len[s] : 1;
@@ -630,87 +662,73 @@ __device__ bool pack_inputs_valid(const PackArgs &a, int *flag, int *sso, int *s
     }
 #pragma unroll
     for (int k = 0; k < kPackBatch; ++k) {
-      const int s = s0 + k * (int)blockDim.x;
+      const int s = s0 + k * kPackThreads;
       if (s >= a.num_spans) break;
-      int lo = 0, hi = a.B - 1;  // sequence b with sso[b] <= s < sso[b+1]
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (sso_src[mid] <= s) lo = mid;
-        else hi = mid - 1;
+      const int b = last_le(sso_src, a.B, s);  // sequence b with sso[b] <= s < sso[b + 1]
+      bool ok = ln[k] >= 1 && st[k] >= so_src[b] && (int64_t)st[k] + ln[k] <= so_src[b + 1];
+      if (ok && s > sso_src[b]) ok = st[k] >= pe[k];
+      if (!ok) {
+        bad = true;
+        continue;
       }
-      bool ok = ln[k] >= 1 && st[k] >= so_src[lo] && (int64_t)st[k] + ln[k] <= so_src[lo + 1];
-      if (ok && s > sso_src[lo]) ok = st[k] >= pe[k];
-      if (!ok) *flag = 1;
-      removed_all += ln[k] - 1;
-      if (s < sp0) removed_before += ln[k] - 1;
+      rem_all += ln[k] - 1;
+      if (st[k] < q0) rem_q0 += ln[k] - 1;
+      if (st[k] < c0) rem_c0 += min(ln[k] - 1, c0 - st[k]);
+      const int end = st[k] + ln[k] - 1;  // its last token keeps the surrogate
+      if (end >= c0 && st[k] < c0 + cn) {
+        for (int u = max(st[k], c0); u < min(end, c0 + cn); ++u) src[u - c0] = kRemoved;
+        if (end < c0 + cn) src[end - c0] = -1 - s;
+      }
     }
   }
+  if (bad) flag = 1;
+  // the sums by a wave reduction and one LDS add per wave
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    rem_q0 += __shfl_xor(rem_q0, off, kWave);
+    rem_c0 += __shfl_xor(rem_c0, off, kWave);
+    rem_all += __shfl_xor(rem_all, off, kWave);
+  }
+  if ((t & 63) == 0) {
+    atomicAdd(&sums[0], rem_q0);
+    atomicAdd(&sums[1], rem_c0);
+    atomicAdd(&sums[2], rem_all);
+  }
   __syncthreads();
-  return *flag == 0;
-}
-
-__global__ __launch_bounds__(kPackThreads) void pack_index_kernel(PackArgs a) {
-  __shared__ int src[kPackChunk];
-  __shared__ int sso[kPackSsoLds], so[kPackSsoLds];
-  __shared__ int red[16];
-  __shared__ int flag, s_err;
-  __shared__ float fred[16];
-  const int b = blockIdx.x, t = threadIdx.x;
-  if (t == 0) s_err = *a.err;
-  __syncthreads();
-  if (s_err != 0) return;
-  int removed_before = 0, removed_all = 0;  // (this thread's spans)
-  if (!pack_inputs_valid(a, &flag, sso, so, a.seq_span_offsets[b], removed_before, removed_all)) {
-    if (b == 0 && t == 0) set_err(a.err, SM_ERR_EINVAL);
+  if (flag) {
+    if (blockIdx.x == 0 && t == 0) set_err(a.err, SM_ERR_EINVAL);
     return;
   }
-  const int sp0 = a.seq_span_offsets[b], sp1 = a.seq_span_offsets[b + 1];
-  // positions removed before this sequence (and in total, for the last
-  // one), summed over the threads
-  int dummy;
-  // block sums via the scan helper (totals only)
-  block_inclusive_scan(removed_before, red, &removed_before);
-  __syncthreads();
-  block_inclusive_scan(removed_all, red, &removed_all);
-  (void)dummy;
-  (void)fred;
-  const int base = a.seq_offsets[b] - removed_before;  // packed_offsets[b]
-  if (t == 0) {
-    a.packed_offsets[b] = base;
-    if (b == a.B - 1) a.packed_offsets[a.B] = a.total_tokens - removed_all;
+  // packed rows of the piece's tokens: each thread owns PER consecutive ones
+  int v[PER], cnt = 0;
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    v[u] = PER * t + u < cn ? src[PER * t + u] : kRemoved;
+    cnt += v[u] != kRemoved;
   }
-  const int q0 = a.seq_offsets[b], q1 = a.seq_offsets[b + 1];
-  int carry = 0;
-  for (int c0 = q0; c0 < q1; c0 += kPackChunk) {
-    const int cn = min(kPackChunk, q1 - c0);
-    __syncthreads();
-    for (int e = t; e < cn; e += kPackThreads) src[e] = c0 + e;
-    __syncthreads();
-    for (int s = sp0 + t; s < sp1; s += kPackThreads) {
-      const int st = a.span_start[s], last = st + a.span_len[s] - 1;
-      if (last < c0 || st >= c0 + cn) continue;
-      for (int u = max(st, c0); u < min(last, c0 + cn); ++u) src[u - c0] = kRemoved;
-      if (last < c0 + cn) src[last - c0] = -1 - s;
-    }
-    __syncthreads();
-    // each thread owns 4 consecutive tokens of the chunk
-    const int e0 = 4 * t;
-    int keep[4], cnt = 0;
+  int tot;
+  int g = c0 - sums[1] + block_inclusive_scan(cnt, red, &tot) - cnt;  // (its barriers: every src entry is read)
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      keep[u] = (e0 + u < cn) && src[e0 + u] != kRemoved;
-      cnt += keep[u];
+  for (int u = 0; u < PER; ++u) {
+    if (PER * t + u < cn) {
+      src[PER * t + u] = g;
+      if (v[u] != kRemoved) a.packed_src[g++] = v[u];
     }
-    int tot;
-    const int incl = block_inclusive_scan(cnt, red, &tot);
-    int pos = carry + incl - cnt;
+  }
+  __syncthreads();
+  const int row_q0 = q0 - sums[0];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (e0 + u >= cn) break;
-      a.pi[c0 + e0 + u] = pos;
-      if (keep[u]) a.packed_src[base + pos++] = src[e0 + u];
+  for (int u = 0; u < PER; ++u) {
+    const int e = t + u * kPackThreads;
+    if (e < cn) {
+      const int first = so_src[last_le(so_src, a.B, c0 + e)];  // its sequence's first token
+      a.pi[c0 + e] = src[e] - (first >= c0 ? src[first - c0] : row_q0);
     }
-    carry += tot;
+  }
+  for (int b = t; b <= a.B; b += kPackThreads) {
+    const int o = so_src[b];
+    if (o >= c0 && o < c0 + cn) a.packed_offsets[b] = src[o - c0];
+    else if (last && o == a.total_tokens) a.packed_offsets[b] = o - sums[2];
   }
 }
 
@@ -907,7 +925,12 @@ SM_API sm_status sm_pack_spans(int B, const int32_t *seq_offsets, int total_toke
   a.d = d;
   a.packed = packed;
   a.err = err;
-  hipLaunchKernelGGL(pack_index_kernel, dim3(B), dim3(kPackThreads), 0, stream, a);
+  const int64_t pieces = ((int64_t)total_tokens + kPackThreads - 1) / kPackThreads;
+  if (pieces <= 256)
+    hipLaunchKernelGGL(pack_index_kernel<1>, dim3(pieces > 0 ? (unsigned)pieces : 1), dim3(kPackThreads), 0, stream, a);
+  else
+    hipLaunchKernelGGL(pack_index_kernel<kPackMaxPer>, dim3((unsigned)((pieces + kPackMaxPer - 1) / kPackMaxPer)),
+                       dim3(kPackThreads), 0, stream, a);
   if (hipGetLastError() != hipSuccess) return SM_EHIP;
   if (packed && total_tokens > 0) {
     // one wave per packed row, striding: up to 4 waves per compute unit's
