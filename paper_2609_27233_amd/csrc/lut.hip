@@ -10,10 +10,11 @@
 //  * sm_span_dedupe: spans of one merge batch that carry the same rule
 //    share one surrogate.  The first span of each rule is found with an
 //    atomic min per rule (repeats within a workgroup settled in LDS first);
-//    per-block counts of first occurrences and their lengths are scanned
-//    into the unique spans' order and CSR row offsets; a last pass gives
-//    every span the slot of its rule's first span and writes the unique
-//    spans' token ids, the merge module's input.
+//    each block of spans counts its first occurrences and their rows and
+//    ranks them; a last pass, every workgroup of which adds up the blocks'
+//    counts for itself, gives every span the slot of its rule's first span
+//    and writes the unique spans, their CSR row offsets and token ids, the
+//    merge module's input.
 #include "common.hpp"
 
 namespace sm {
@@ -42,8 +43,10 @@ __global__ __launch_bounds__(64 * kGatherWaves) void gather_rows_kernel(const T 
     *(u32x4_t *)(dst + v * VEC) = src ? *(const u32x4_t *)(src + v * VEC) : u32x4_t{0u, 0u, 0u, 0u};
 }
 
-__global__ void fill_i32_kernel(int32_t *p, int n, int v) {
-  for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x) p[r] = v;
+// owner[r] = no span yet, and the call's flag
+__global__ __launch_bounds__(256) void dedupe_clear_kernel(int32_t *owner, int n, int32_t *flag) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *flag = 0;
+  for (int r = blockIdx.x * 256 + threadIdx.x; r < n; r += gridDim.x * 256) owner[r] = 0x7fffffff;
 }
 
 // The first span of every rule; a bad rule id or span range flags the call.
@@ -90,38 +93,38 @@ __global__ __launch_bounds__(kDedupThreads) void dedupe_owner_kernel(const int32
   }
 }
 
-// per block of spans: how many are first occurrences, and their rows
+// per block of spans: how many are first occurrences, and their rows; each
+// first occurrence's rank (and rows before it) within the block
 __global__ __launch_bounds__(kDedupThreads) void dedupe_count_kernel(const int32_t *span_rule,
                                                                      const int32_t *span_len, int S,
                                                                      const int32_t *owner, const int32_t *flag,
-                                                                     int32_t *blk_u, int32_t *blk_r) {
+                                                                     int32_t *blk_u, int32_t *blk_r, int32_t *rank) {
   __shared__ int red[16];
   if (*flag) return;
   const int s = blockIdx.x * kDedupThreads + threadIdx.x;
   const bool first = s < S && owner[span_rule[s]] == s;
   const int len = first ? span_len[s] : 0;
   int ut, rt;
-  block_inclusive_scan(first ? 1 : 0, red, &ut);
+  const int ui = block_inclusive_scan(first ? 1 : 0, red, &ut);
   block_inclusive_scan(len, red, &rt);
+  if (first) rank[s] = ui - 1;
   if (threadIdx.x == 0) {
     blk_u[blockIdx.x] = ut;
     blk_r[blockIdx.x] = rt;
   }
 }
 
-// exclusive scan of the block totals (one workgroup)
+// Exclusive scan of the block totals by one workgroup, for batches of more
+// than kDedupBlocks blocks; up to there (a million spans) every workgroup of
+// the last pass forms the prefix in its own LDS, one launch less (of seven
+// launches for one 32,768-token document, 26 us, four are left, 19).
+constexpr int kDedupBlocks = 4096;
+
 __global__ __launch_bounds__(kDedupThreads) void dedupe_blocks_kernel(int nblk, const int32_t *flag, int32_t *blk_u,
                                                                       int32_t *blk_r, int32_t *uniq_span_offsets,
-                                                                      int32_t *num_uniq, int32_t *err) {
+                                                                      int32_t *num_uniq) {
   __shared__ int red[16];
-  if (*flag) {  // nothing to merge
-    if (threadIdx.x == 0) {
-      set_err(err, SM_ERR_EINVAL);
-      *num_uniq = 0;
-      uniq_span_offsets[0] = 0;
-    }
-    return;
-  }
+  if (*flag) return;
   int ub = 0, rb = 0;
   for (int b0 = 0; b0 < nblk; b0 += kDedupThreads) {
     const int b = b0 + threadIdx.x;
@@ -143,42 +146,59 @@ __global__ __launch_bounds__(kDedupThreads) void dedupe_blocks_kernel(int nblk, 
   }
 }
 
-// unique spans in order and their CSR row offsets, from the block offsets
-__global__ __launch_bounds__(kDedupThreads) void dedupe_place_kernel(const int32_t *span_rule,
-                                                                     const int32_t *span_len, int S,
-                                                                     const int32_t *owner, const int32_t *flag,
-                                                                     const int32_t *blk_u, const int32_t *blk_r,
-                                                                     int32_t *ufirst, int32_t *uniq_span,
-                                                                     int32_t *uniq_span_offsets) {
+// every span's slot; the unique spans in order, their CSR row offsets and
+// token ids.  SCANNED: blk_u and blk_r hold prefixes already.
+template <bool SCANNED>
+__global__ __launch_bounds__(kDedupThreads) void dedupe_slot_kernel(
+    const int32_t *span_rule, const int32_t *span_start, const int32_t *span_len, int S, int nblk,
+    const int32_t *owner, const int32_t *flag, const int32_t *blk_u, const int32_t *blk_r, const int32_t *rank,
+    const int32_t *token_ids, int32_t *uniq_span, int32_t *span_slot, int32_t *uniq_row_idx,
+    int32_t *uniq_span_offsets, int32_t *num_uniq, int32_t *err) {
+  __shared__ int pre[SCANNED ? 1 : kDedupBlocks];
   __shared__ int red[16];
-  if (*flag) return;
-  const int s = blockIdx.x * kDedupThreads + threadIdx.x;
-  const bool first = s < S && owner[span_rule[s]] == s;
-  const int len = first ? span_len[s] : 0;
-  int ut, rt;
-  const int ui = block_inclusive_scan(first ? 1 : 0, red, &ut) - (first ? 1 : 0);
-  const int ri = block_inclusive_scan(len, red, &rt) - len;
-  if (first) {
-    const int u = blk_u[blockIdx.x] + ui;
-    ufirst[s] = u;
-    uniq_span[u] = s;
-    uniq_span_offsets[u] = blk_r[blockIdx.x] + ri;
+  const int tid = threadIdx.x, b0 = blockIdx.x, s = b0 * kDedupThreads + tid;
+  const bool in = s < S;
+  const int len = in ? span_len[s] : 0, start = in ? span_start[s] : 0, rule = in ? span_rule[s] : 0;
+  if (*flag) {  // nothing to merge
+    if (b0 == 0 && tid == 0) {
+      set_err(err, SM_ERR_EINVAL);
+      *num_uniq = 0;
+      uniq_span_offsets[0] = 0;
+    }
+    return;
   }
-}
-
-// every span's slot; the unique spans' token ids
-__global__ void dedupe_slot_kernel(const int32_t *span_rule, const int32_t *span_start, const int32_t *span_len,
-                                   int S, const int32_t *owner, const int32_t *flag, const int32_t *ufirst,
-                                   const int32_t *uniq_span_offsets, const int32_t *token_ids, int32_t *span_slot,
-                                   int32_t *uniq_row_idx) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= S || *flag) return;
-  const int f = owner[span_rule[s]];
-  const int u = ufirst[f];
-  span_slot[s] = u;
-  if (f == s) {
-    const int a = span_start[s], o = uniq_span_offsets[u];
-    for (int j = 0; j < span_len[s]; ++j) uniq_row_idx[o + j] = token_ids[a + j];
+  const int f = in ? owner[rule] : 0;
+  const int fr = in ? rank[f] : 0;
+  // exclusive prefix of the blocks' first occurrences; rows before this block
+  int ub = 0, rb = 0, rall = 0;
+  if constexpr (SCANNED) rb = blk_r[b0];
+  else for (int c0 = 0; c0 < nblk; c0 += kDedupThreads) {
+    const int b = c0 + tid;
+    const int u = b < nblk ? blk_u[b] : 0, r = b < nblk ? blk_r[b] : 0;
+    int ut, rt, rbt;
+    const int ui = block_inclusive_scan(u, red, &ut) - u;
+    if (b < nblk) pre[b] = ub + ui;
+    block_inclusive_scan(r, red, &rt);
+    block_inclusive_scan(b < b0 ? r : 0, red, &rbt);
+    ub += ut;
+    rall += rt;
+    rb += rbt;
+  }
+  const bool first = in && f == s;
+  int dummy;
+  const int o = rb + block_inclusive_scan(first ? len : 0, red, &dummy) - (first ? len : 0);  // (its barriers order pre)
+  if (in) {
+    const int u = (SCANNED ? blk_u[f / kDedupThreads] : pre[f / kDedupThreads]) + fr;
+    span_slot[s] = u;
+    if (first) {
+      uniq_span[u] = s;
+      uniq_span_offsets[u] = o;
+      for (int j = 0; j < len; ++j) uniq_row_idx[o + j] = token_ids[start + j];
+    }
+  }
+  if (!SCANNED && b0 == 0 && tid == 0) {
+    uniq_span_offsets[ub] = rall;
+    *num_uniq = ub;
   }
 }
 
@@ -227,27 +247,29 @@ SM_API sm_status sm_span_dedupe(const int32_t *span_rule, const int32_t *span_st
   w += 256;
   int32_t *owner = (int32_t *)w;
   w += a256((size_t)num_rules * 4);
-  int32_t *ufirst = (int32_t *)w;
+  int32_t *rank = (int32_t *)w;
   w += a256((size_t)S * 4);
   int32_t *blk_u = (int32_t *)w;
   w += a256((size_t)nblk * 4);
   int32_t *blk_r = (int32_t *)w;
-  hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, stream, flag, 1, 0);
-  hipLaunchKernelGGL(fill_i32_kernel, dim3(max(1, min((num_rules + 255) / 256, 4096))), dim3(256), 0, stream, owner,
-                     num_rules, 0x7fffffff);
+  hipLaunchKernelGGL(dedupe_clear_kernel, dim3(max(1, min((num_rules + 255) / 256, 4096))), dim3(256), 0, stream, owner,
+                     num_rules, flag);
   if (S > 0) {
     hipLaunchKernelGGL(dedupe_owner_kernel, dim3(nblk), dim3(kDedupThreads), 0, stream, span_rule, span_start,
                        span_len, S, num_rules, total_tokens, owner, flag);
     hipLaunchKernelGGL(dedupe_count_kernel, dim3(nblk), dim3(kDedupThreads), 0, stream, span_rule, span_len, S, owner,
-                       flag, blk_u, blk_r);
+                       flag, blk_u, blk_r, rank);
   }
-  hipLaunchKernelGGL(dedupe_blocks_kernel, dim3(1), dim3(kDedupThreads), 0, stream, nblk, flag, blk_u, blk_r,
-                     uniq_span_offsets, num_uniq, err);
-  if (S > 0) {
-    hipLaunchKernelGGL(dedupe_place_kernel, dim3(nblk), dim3(kDedupThreads), 0, stream, span_rule, span_len, S, owner,
-                       flag, blk_u, blk_r, ufirst, uniq_span, uniq_span_offsets);
-    hipLaunchKernelGGL(dedupe_slot_kernel, dim3(nblk), dim3(kDedupThreads), 0, stream, span_rule, span_start, span_len,
-                       S, owner, flag, ufirst, uniq_span_offsets, token_ids, span_slot, uniq_row_idx);
+  if (nblk > kDedupBlocks) {
+    hipLaunchKernelGGL(dedupe_blocks_kernel, dim3(1), dim3(kDedupThreads), 0, stream, nblk, flag, blk_u, blk_r,
+                       uniq_span_offsets, num_uniq);
+    hipLaunchKernelGGL(dedupe_slot_kernel<true>, dim3(nblk), dim3(kDedupThreads), 0, stream, span_rule, span_start,
+                       span_len, S, nblk, owner, flag, blk_u, blk_r, rank, token_ids, uniq_span, span_slot,
+                       uniq_row_idx, uniq_span_offsets, num_uniq, err);
+  } else {
+    hipLaunchKernelGGL(dedupe_slot_kernel<false>, dim3(nblk > 0 ? nblk : 1), dim3(kDedupThreads), 0, stream, span_rule,
+                       span_start, span_len, S, nblk, owner, flag, blk_u, blk_r, rank, token_ids, uniq_span, span_slot,
+                       uniq_row_idx, uniq_span_offsets, num_uniq, err);
   }
   return hipGetLastError() == hipSuccess ? SM_OK : SM_EHIP;
 }
