@@ -32,7 +32,7 @@
 //    completes the longest rule suffix (4, 3, 2 in turn) or joins the raw
 //    tail.  On a match, n - 1 cached entries are to be cropped; the call can
 //    run the cache rollback right after.
-#include "common.hpp"
+#include "cache_meta.hpp"
 
 typedef int32_t i32x4_t __attribute__((ext_vector_type(4)));
 
@@ -501,16 +501,23 @@ __global__ __launch_bounds__(kEmitThreads) void match_emit_kernel(const int8_t *
 
 constexpr int kDecThreads = 1024;  // one request per thread, one workgroup
 
+static_assert(kDecThreads == kMetaThreads, "the crop runs on the threads that matched");
+
+// CROP: the rollback that the matches imply follows in the same launch (as a
+// launch of its own it took 3.9 us and the gap before it).
+template <bool CROP>
 __global__ __launch_bounds__(kDecThreads) void match_decode_kernel(const i32x4_t *keys, const int32_t *ids,
                                                                    uint32_t mask, i32x4_t *state, int max_seqs,
                                                                    const int32_t *seq_ids,
                                                                    const int32_t *new_tokens, int n,
                                                                    int32_t *k_out, int32_t *rule_out,
-                                                                   int32_t *err) {
+                                                                   int32_t *err, CacheArgs cache) {
   __shared__ int sid[kDecThreads];
   __shared__ int bad;
   const int i = threadIdx.x;
   const int s = i < n ? seq_ids[i] : -1;
+  RollbackReads rd = {};
+  if constexpr (CROP) rd = rollback_reads(cache, s);
   sid[i] = s;
   if (i == 0) bad = 0;
   __syncthreads();
@@ -520,33 +527,36 @@ __global__ __launch_bounds__(kDecThreads) void match_decode_kernel(const i32x4_t
     if (!ok) bad = 1;
   }
   __syncthreads();
-  if (i >= n) return;
-  if (bad) {  // nothing changes: no state update, no crop
-    if (i == 0) set_err(err, SM_ERR_EINVAL);
-    k_out[i] = 0;
-    rule_out[i] = -1;
-    return;
-  }
-  const i32x4_t st = state[s];
-  const int r = min(max(st.x, 0), 3);  // raw tokens since the last merge, at most 3 kept
-  const int w[4] = {st.y, st.z, st.w, new_tokens[i]};
-  i32x4_t cand[3];
-  bool want[3];
+  int crop = 0;
+  if (i < n) {
+    if (bad) {  // nothing changes: no state update, no crop
+      if (i == 0) set_err(err, SM_ERR_EINVAL);
+      k_out[i] = 0;
+      rule_out[i] = -1;
+    } else {
+      const i32x4_t st = state[s];
+      const int r = min(max(st.x, 0), 3);  // raw tokens since the last merge, at most 3 kept
+      const int w[4] = {st.y, st.z, st.w, new_tokens[i]};
+      i32x4_t cand[3];
+      bool want[3];
 #pragma unroll
-  for (int c = 0; c < 3; ++c) {  // candidate c: the suffix of m = 4 - c tokens
-    const int m = 4 - c;
-    bool ok = m <= r + 1;
+      for (int c = 0; c < 3; ++c) {  // candidate c: the suffix of m = 4 - c tokens
+        const int m = 4 - c;
+        bool ok = m <= r + 1;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) ok = ok && (j < 4 - m || w[j] >= 0);
-    want[c] = ok;
-    cand[c] = i32x4_t{w[4 - m], w[5 - m], m > 2 ? w[6 - m] : -1, m > 3 ? w[3] : -1};
+        for (int j = 0; j < 4; ++j) ok = ok && (j < 4 - m || w[j] >= 0);
+        want[c] = ok;
+        cand[c] = i32x4_t{w[4 - m], w[5 - m], m > 2 ? w[6 - m] : -1, m > 3 ? w[3] : -1};
+      }
+      int id;
+      const int c = rule_find_longest(keys, ids, mask, cand, want, &id);
+      crop = c >= 0 ? 3 - c : 0;  // n - 1 entries to crop
+      state[s] = id >= 0 ? i32x4_t{0, -1, -1, -1} : i32x4_t{min(r + 1, 3), w[1], w[2], w[3]};
+      k_out[i] = crop;
+      rule_out[i] = id;
+    }
   }
-  int id;
-  const int c = rule_find_longest(keys, ids, mask, cand, want, &id);
-  const int k = c >= 0 ? 3 - c : 0;  // n - 1 entries to crop
-  state[s] = id >= 0 ? i32x4_t{0, -1, -1, -1} : i32x4_t{min(r + 1, 3), w[1], w[2], w[3]};
-  k_out[i] = k;
-  rule_out[i] = id;
+  if constexpr (CROP) rollback_body(cache, rd, s, crop, n);
 }
 
 static bool table_ok(const sm_rule_table *t) {
@@ -635,9 +645,14 @@ SM_API sm_status sm_match_decode(const sm_rule_table *t, int32_t *state, int max
   }
   if (n == 0) return SM_OK;
   if (!state || !seq_ids || !new_tokens || !k_out || !rule_out) return SM_EINVAL;
-  hipLaunchKernelGGL(match_decode_kernel, dim3(1), dim3(kDecThreads), 0, stream, (const i32x4_t *)t->keys, t->ids,
-                     (uint32_t)(t->capacity - 1), (i32x4_t *)state, max_seqs, seq_ids, new_tokens, n, k_out,
-                     rule_out, t->err);
-  if (hipGetLastError() != hipSuccess) return SM_EHIP;
-  return cache ? sm_kv_rollback(cache, seq_ids, k_out, n, stream) : SM_OK;
+  CacheArgs ca = {};
+  if (cache && cache_ok(cache, ca))  // (checked above)
+    hipLaunchKernelGGL(match_decode_kernel<true>, dim3(1), dim3(kDecThreads), 0, stream, (const i32x4_t *)t->keys,
+                       t->ids, (uint32_t)(t->capacity - 1), (i32x4_t *)state, max_seqs, seq_ids, new_tokens, n, k_out,
+                       rule_out, t->err, ca);
+  else
+    hipLaunchKernelGGL(match_decode_kernel<false>, dim3(1), dim3(kDecThreads), 0, stream, (const i32x4_t *)t->keys,
+                       t->ids, (uint32_t)(t->capacity - 1), (i32x4_t *)state, max_seqs, seq_ids, new_tokens, n, k_out,
+                       rule_out, t->err, ca);
+  return hipGetLastError() == hipSuccess ? SM_OK : SM_EHIP;
 }
