@@ -21,10 +21,13 @@
 //  2. one workgroup per (row, 256 output features) sums the partials in a
 //     fixed order (the result does not depend on scheduling), scales by
 //     1/rms, rotates K by the position (the angle formed and reduced in
-//     double precision, then fp32 sin/cos) and writes bf16 rows;
-//  3. sm_kv_append_projected then appends those rows (block allocation and
-//     all checks of sm_kv_append).
-#include "common.hpp"
+//     double precision, then fp32 sin/cos) and writes bf16 rows.
+// sm_kv_append_projected runs all checks and the block allocation of
+// sm_kv_append in one more workgroup of the first launch, beside the product,
+// which leaves each row's position and page in the workspace, and the second
+// launch writes the rows straight into the pages (a third launch that
+// appended them took 15 us for 16 rows, 29 for 128).
+#include "cache_meta.hpp"
 
 namespace sm {
 
@@ -42,9 +45,103 @@ struct ProjArgs {
   int n, d, HD;
 };
 
-__global__ __launch_bounds__(kPjThreads) void kv_proj_partial_kernel(ProjArgs a) {
+// Where a row goes: its position (the sequence's length before the call) and
+// the page that takes it, -1 when it is not appended.
+struct RowSlot {
+  int pos, blk;
+};
+
+// The metadata of kv_append for one row per request, by one workgroup of
+// kPjThreads threads (thread t holds requests 4 t .. 4 t + 3): the same
+// checks in the same order, the same block order; all applied or nothing.
+__device__ void append_rows_meta(const CacheArgs &c, const int32_t *seq_ids, int n, RowSlot *slots) {
+  constexpr int RPT = SM_MAX_REQUESTS / kPjThreads;
+  __shared__ __attribute__((aligned(16))) int ids[SM_MAX_REQUESTS];
+  __shared__ int red[16];
+  __shared__ int fl_inval, fl_range, fl_stack;
+  const int t = threadIdx.x, r0 = RPT * t;
+  const int err0 = *c.err, top = *c.free_top;
+  const int cap = c.max_blocks << c.bs_log2, bs = 1 << c.bs_log2;
+  int s[RPT], L[RPT], need[RPT], blk[RPT], mine = 0;
+#pragma unroll
+  for (int k = 0; k < RPT; ++k) s[k] = r0 + k < n ? seq_ids[r0 + k] : -1;
+#pragma unroll
+  for (int k = 0; k < RPT; ++k) L[k] = s[k] >= 0 && s[k] < c.max_seqs ? c.lengths[s[k]] : 0;
+#pragma unroll
+  for (int k = 0; k < RPT; ++k) {
+    ids[r0 + k] = s[k];
+    if (r0 + k < n) slots[r0 + k] = RowSlot{L[k], -1};
+  }
+  if (t == 0) fl_inval = fl_range = fl_stack = 0;
+  __syncthreads();
+  if (err0 != 0) return;  // sticky: the cache is frozen
+  bool bad = false, range = false;
+#pragma unroll
+  for (int k = 0; k < RPT; ++k) {
+    if (r0 + k < n) {
+      bad |= !id_ok(ids, r0 + k, s[k], c.max_seqs);
+      range |= L[k] < 0 || L[k] + 1 > cap;
+      need[k] = (L[k] & (bs - 1)) == 0;
+    } else {
+      need[k] = 0;
+    }
+    mine += need[k];
+  }
+  if (bad) fl_inval = 1;
+  if (range) fl_range = 1;
+  int total;
+  int pop = block_inclusive_scan(mine, red, &total) - mine;  // (its barriers order the flags)
+  if (fl_inval || fl_range || top < 0 || top > c.num_blocks || total > top) {
+    if (t == 0) set_err(c.err, fl_inval ? SM_ERR_EINVAL : fl_range ? SM_ERR_ERANGE : SM_ERR_ENOMEM);
+    return;
+  }
+  // popped ids must name real blocks; a row in a partly filled page takes
+  // that page, which is checked for itself
+  bool bad_pop = false;
+#pragma unroll
+  for (int k = 0; k < RPT; ++k) {
+    blk[k] = -1;
+    if (r0 + k < n) {
+      if (need[k]) {
+        blk[k] = c.free_stack[top - 1 - pop];
+        ++pop;
+      } else {
+        blk[k] = c.block_table[(int64_t)s[k] * c.max_blocks + (L[k] >> c.bs_log2)];
+      }
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < RPT; ++k) bad_pop |= need[k] && (blk[k] < 0 || blk[k] >= c.num_blocks);
+  if (bad_pop) fl_stack = 1;
+  __syncthreads();
+  if (fl_stack) {
+    if (t == 0) set_err(c.err, SM_ERR_EINVAL);
+    return;
+  }
+#pragma unroll
+  for (int k = 0; k < RPT; ++k)
+    if (r0 + k < n) {
+      if (need[k]) c.block_table[(int64_t)s[k] * c.max_blocks + (L[k] >> c.bs_log2)] = blk[k];
+      else if (blk[k] < 0 || blk[k] >= c.num_blocks) {
+        set_err(c.err, SM_ERR_EINVAL);  // corrupt block table: the row is not written
+        blk[k] = -1;
+      }
+      c.lengths[s[k]] = L[k] + 1;
+      slots[r0 + k].blk = blk[k];
+    }
+  if (t == 0) *c.free_top = top - total;
+}
+
+template <bool APPEND>
+__global__ __launch_bounds__(kPjThreads) void kv_proj_partial_kernel(ProjArgs a, CacheArgs c, const int32_t *seq_ids,
+                                                                     RowSlot *slots) {
   __shared__ __attribute__((aligned(16))) uint16_t xs[kPjRows][kPjK + 8];
-  const int fb = blockIdx.x, kc = blockIdx.y, rg = blockIdx.z;
+  if (APPEND && blockIdx.x == 0) {  // dispatched first: it runs beside the product
+    append_rows_meta(c, seq_ids, a.n, slots);
+    return;
+  }
+  const int id = blockIdx.x - (APPEND ? 1 : 0), nfb = 2 * a.HD / kPjFeat, nkc = a.d / kPjK;
+  const int fb = id % nfb, kc = id / nfb % nkc, rg = id / (nfb * nkc);
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int r = lane & 15, q4 = lane >> 4;
   const int f0 = fb * kPjFeat + 16 * w;  // this wave's 16 features: all K (f0 < HD) or all V
@@ -93,8 +190,8 @@ struct ProjEpiArgs {
   const float *part;
   const int32_t *seq_ids;
   const int32_t *lengths;
-  uint16_t *K, *V;        // [n][HD] bf16
-  int32_t *row_offsets;   // [n + 1] (nullable)
+  uint16_t *K, *V;        // [n][HD] bf16, or the pools
+  const RowSlot *slots;   // rows go into the pools
   int n, d, HD, D, nkc, max_seqs;
   float rms_eps;
   double inv_freq[64];    // theta^(-2j/D), j < D/2, computed on the host
@@ -104,13 +201,22 @@ constexpr double kTwoPi = 6.283185307179586476925286766559;
 
 // One workgroup per (block of 256 output features, row): a block covers
 // whole heads, so both halves of every rotary pair are at hand.
-__global__ __launch_bounds__(kPjThreads) void kv_proj_epilogue_kernel(ProjEpiArgs a) {
+template <bool APPEND>
+__global__ __launch_bounds__(kPjThreads) void kv_proj_epilogue_kernel(ProjEpiArgs a, int Hkv, int bs_log2) {
   __shared__ float ys[kPjThreads];
   __shared__ float red[16];
   const int fb = blockIdx.x, i = blockIdx.y, tid = threadIdx.x;
   const int f = fb * kPjThreads + tid;  // K features first, then V
-  const int s = a.seq_ids[i];
-  const double pos = (s >= 0 && s < a.max_seqs) ? (double)a.lengths[s] : 0.0;  // bad ids fail in the append
+  double pos;
+  RowSlot rs = {0, -1};
+  if constexpr (APPEND) {
+    rs = a.slots[i];
+    if (rs.blk < 0) return;  // the append failed, or the row's page is not usable (uniform: one row per workgroup)
+    pos = (double)rs.pos;
+  } else {
+    const int s = a.seq_ids[i];
+    pos = (s >= 0 && s < a.max_seqs) ? (double)a.lengths[s] : 0.0;
+  }
   // the split-K partials, summed in a fixed order once all are loaded; their
   // loads are in flight while the row's RMSNorm scale is reduced
   float pv[kPjMaxChunks];
@@ -134,6 +240,11 @@ __global__ __launch_bounds__(kPjThreads) void kv_proj_epilogue_kernel(ProjEpiArg
   y *= inv;
   ys[tid] = y;
   __syncthreads();
+  // this feature's place: its row, or its slot in the page
+  const int fk = f < a.HD ? f : f - a.HD;
+  const int64_t kat = APPEND ? (((int64_t)rs.blk * Hkv + fk / a.D) << bs_log2) * a.D +
+                                   (int64_t)(rs.pos & ((1 << bs_log2) - 1)) * a.D + fk % a.D
+                             : (int64_t)i * a.HD + fk;
   if (f < a.HD) {
     // rotate-half RoPE: pair (j, j + D/2) turned by pos theta^(-2j/D); the
     // angle is formed and reduced to [-pi, pi] in double precision
@@ -143,13 +254,12 @@ __global__ __launch_bounds__(kPjThreads) void kv_proj_epilogue_kernel(ProjEpiArg
     const float c = cosf(r), sn = sinf(r);
     const float other = ys[jd < half ? tid + half : tid - half];
     const float out = jd < half ? y * c - other * sn : y * c + other * sn;
-    a.K[(int64_t)i * a.HD + f] = f32_to_bf16(out);
+    a.K[kat] = f32_to_bf16(out);
   } else {
-    a.V[(int64_t)i * a.HD + f - a.HD] = f32_to_bf16(y);
-  }
-  if (a.row_offsets && fb == 0 && tid == 0) {
-    a.row_offsets[i] = i;
-    if (i == a.n - 1) a.row_offsets[a.n] = a.n;
+    const int64_t vat = APPEND ? ((((int64_t)rs.blk * Hkv + fk / a.D) * a.D + fk % a.D) << bs_log2) +
+                                     (rs.pos & ((1 << bs_log2) - 1))
+                               : kat;
+    a.V[vat] = f32_to_bf16(y);
   }
 }
 
@@ -179,17 +289,25 @@ SM_API size_t sm_kv_project_workspace_bytes(int n, int d, int num_kv_heads, int 
   return part_bytes(n, d, HD) + 2 * align256((size_t)n * HD * 2) + align256((size_t)(n + 1) * 4);
 }
 
+// K, V: [n][HD] rows, or with `slots` the pools of `ca` (the append).
 static sm_status launch_project(const sm_paged_cache *c, const int32_t *seq_ids, int n, const void *x,
-                                const sm_kv_proj_params *p, void *K, void *V, int32_t *row_offsets, float *part,
-                                hipStream_t stream) {
+                                const sm_kv_proj_params *p, void *K, void *V, const CacheArgs &ca, RowSlot *slots,
+                                float *part, hipStream_t stream) {
   const int HD = c->num_kv_heads * c->head_dim;
   ProjArgs a{(const uint16_t *)x, (const uint16_t *)p->W_k, (const uint16_t *)p->W_v, part, n, p->d, HD};
-  const dim3 grid(2 * HD / kPjFeat, p->d / kPjK, (n + kPjRows - 1) / kPjRows);
-  hipLaunchKernelGGL(kv_proj_partial_kernel, grid, dim3(kPjThreads), 0, stream, a);
-  ProjEpiArgs e{(const uint16_t *)x, part, seq_ids, c->lengths, (uint16_t *)K, (uint16_t *)V, row_offsets,
+  const int groups = (n + kPjRows - 1) / kPjRows;
+  const dim3 grid(2 * HD / kPjFeat * (p->d / kPjK) * groups + (slots ? 1 : 0));
+  ProjEpiArgs e{(const uint16_t *)x, part, seq_ids, c->lengths, (uint16_t *)K, (uint16_t *)V, slots,
                 n, p->d, HD, c->head_dim, p->d / kPjK, c->max_seqs, p->rms_eps, {}};
   for (int j = 0; j < c->head_dim / 2; ++j) e.inv_freq[j] = pow((double)p->rope_theta, -2.0 * j / c->head_dim);
-  hipLaunchKernelGGL(kv_proj_epilogue_kernel, dim3(2 * HD / kPjThreads, n), dim3(kPjThreads), 0, stream, e);
+  const dim3 egrid(2 * HD / kPjThreads, n);
+  if (slots) {
+    hipLaunchKernelGGL(kv_proj_partial_kernel<true>, grid, dim3(kPjThreads), 0, stream, a, ca, seq_ids, slots);
+    hipLaunchKernelGGL(kv_proj_epilogue_kernel<true>, egrid, dim3(kPjThreads), 0, stream, e, ca.Hkv, ca.bs_log2);
+  } else {
+    hipLaunchKernelGGL(kv_proj_partial_kernel<false>, grid, dim3(kPjThreads), 0, stream, a, ca, seq_ids, slots);
+    hipLaunchKernelGGL(kv_proj_epilogue_kernel<false>, egrid, dim3(kPjThreads), 0, stream, e, 0, 0);
+  }
   return hipGetLastError() == hipSuccess ? SM_OK : SM_EHIP;
 }
 
@@ -201,28 +319,19 @@ SM_API sm_status sm_kv_project(const sm_paged_cache *c, const int32_t *seq_ids, 
   if (!seq_ids || !K || !V || !ws ||
       ws_bytes < sm_kv_project_workspace_bytes(n, p->d, c->num_kv_heads, c->head_dim))
     return SM_EINVAL;
-  return launch_project(c, seq_ids, n, x, p, K, V, nullptr, (float *)ws, stream);
+  return launch_project(c, seq_ids, n, x, p, K, V, CacheArgs{}, nullptr, (float *)ws, stream);
 }
 
 SM_API sm_status sm_kv_append_projected(const sm_paged_cache *c, const int32_t *seq_ids, int n, const void *x,
                                         const sm_kv_proj_params *p, void *ws, size_t ws_bytes,
                                         hipStream_t stream) {
   if (!proj_ok(c, n, x, p)) return SM_EINVAL;
-  // the append's own synchronous checks first: nothing is enqueued on failure
-  if (sm_kv_append(c, seq_ids, nullptr, 0, 0, nullptr, nullptr, stream) != SM_OK) return SM_EINVAL;
+  CacheArgs ca;
+  if (!cache_ok(c, ca)) return SM_EINVAL;  // (as sm_kv_append)
   if (n == 0) return SM_OK;
   if (!seq_ids || !ws || ws_bytes < sm_kv_project_workspace_bytes(n, p->d, c->num_kv_heads, c->head_dim))
     return SM_EINVAL;
-  const int HD = c->num_kv_heads * c->head_dim;
-  char *w = (char *)ws;
-  float *part = (float *)w;
-  w += part_bytes(n, p->d, HD);
-  void *K = w;
-  w += align256((size_t)n * HD * 2);
-  void *V = w;
-  w += align256((size_t)n * HD * 2);
-  int32_t *offs = (int32_t *)w;
-  const sm_status st = launch_project(c, seq_ids, n, x, p, K, V, offs, part, stream);
-  if (st != SM_OK) return st;
-  return sm_kv_append(c, seq_ids, offs, n, n, K, V, stream);
+  float *part = (float *)ws;
+  RowSlot *slots = (RowSlot *)((char *)ws + part_bytes(n, p->d, c->num_kv_heads * c->head_dim));
+  return launch_project(c, seq_ids, n, x, p, c->k_pool, c->v_pool, ca, slots, part, stream);
 }

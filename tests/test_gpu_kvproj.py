@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import TOL, dev, gpu_cache_like, i32, rel_l2_max, say
+from gpu_util import assert_same_state, TOL, dev, gpu_cache_like, i32, rel_l2_max, say
 from paper_2609_27233_amd import lib as sm
 from paper_2609_27233_amd import workload as wl
 
@@ -102,3 +102,53 @@ def test_append_projected_bad_id_changes_nothing(orc):
     torch.cuda.synchronize()
     assert c.error_bits() == sm.ERR_EINVAL
     assert torch.equal(c.lengths, before[0]) and torch.equal(c.block_table, before[1])
+
+
+@pytest.mark.parametrize("n,H,D,d,bs", [(1, 8, 128, 1024, 16), (5, 2, 64, 256, 64), (65, 4, 128, 512, 16),
+                                        (300, 4, 64, 256, 32)])
+def test_append_projected_many_rows(orc, n, H, D, d, bs):
+    """Rows straight into the pages: one to more requests than the metadata
+    workgroup has threads, lengths on and off page edges, against the oracle's
+    append of the rows that sm_kv_project gives."""
+    rng = np.random.RandomState(n)
+    lens = [int(v) for v in rng.choice([0, 1, bs - 1, bs, bs + 1, 3 * bs, 70], n)]
+    oc, c = _setup(orc, H, D, lens, bs=bs, seed=n)
+    ids = rng.permutation(n).astype(np.int32)
+    x, Wk, Wv = _inputs(n, d, H * D, n)
+    xd, Wkd, Wvd = x.to(dev()), Wk.to(dev()), Wv.to(dev())
+    K = torch.empty((n, H, D), dtype=torch.bfloat16, device=dev())
+    V = torch.empty_like(K)
+    say("append projected", n, H, D, d, bs)
+    sm.kv_project(c, i32(ids), xd, Wkd, Wvd, K, V)
+    sm.kv_append_projected(c, i32(ids), xd, Wkd, Wvd)
+    assert oc.append(ids, np.arange(n + 1, dtype=np.int32), wl.to_raw(K.cpu()), wl.to_raw(V.cpu())) == orc.OK
+    assert_same_state(c, oc)
+
+
+@pytest.mark.parametrize("what", ["repeat", "full stack", "no room", "bad stack", "frozen"])
+def test_append_projected_all_or_nothing(orc, what):
+    """Each failing check of the append leaves the cache as it was."""
+    H, D, d, bs = 4, 64, 256, 16
+    oc, c = _setup(orc, H, D, [16, 20, 32], seed=8)
+    ids, bit = [0, 1, 2], sm.ERR_EINVAL
+    if what == "repeat":
+        ids = [0, 1, 0]
+    elif what == "full stack":
+        c.free_top.fill_(1)                               # two rows begin a page
+        bit = sm.ERR_ENOMEM
+    elif what == "no room":
+        c.lengths[1] = c.max_blocks * bs
+        bit = sm.ERR_ERANGE
+    elif what == "bad stack":
+        c.free_stack[int(c.free_top.item()) - 2] = c.num_blocks
+    else:
+        c.err.fill_(sm.ERR_ENOMEM)
+        bit = sm.ERR_ENOMEM
+    x, Wk, Wv = _inputs(3, d, H * D, 9)
+    before = [t.clone() for t in (c.lengths, c.block_table, c.free_stack, c.free_top, c.k_pool, c.v_pool)]
+    say("append projected fails:", what)
+    sm.kv_append_projected(c, i32(ids), x.to(dev()), Wk.to(dev()), Wv.to(dev()))
+    torch.cuda.synchronize()
+    assert c.error_bits() == bit
+    for t, b in zip((c.lengths, c.block_table, c.free_stack, c.free_top, c.k_pool, c.v_pool), before):
+        assert torch.equal(t, b)
