@@ -1,4 +1,5 @@
-"""Compile the HIP sources into ``libspanmerge.so`` (gfx950 only).
+"""Compile the HIP sources into ``libspanmerge.so`` (gfx950 only), and the
+CPython binding that calls it.
 
 Run as ``python -m paper_2609_27233_amd.build`` or through
 ``__graft_entry__.build()``.  Every source is compiled with hipcc for
@@ -10,6 +11,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -18,6 +20,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libspanmerge.so")
 SOURCES = ["decode_attn.hip", "kv_paged.hip", "kvproj.hip", "lut.hip", "merge_spans.hip", "prefill_attn.hip", "rules.hip"]
+BINDING = os.path.join(HERE, "_binding" + sysconfig.get_config_var("EXT_SUFFIX"))
 ARCH = "gfx950"
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -42,6 +45,18 @@ def _compile(src: str, out_dir: str) -> str:
     return obj
 
 
+def _build_binding() -> None:
+    """The extension module beside the library, which it finds by its own place."""
+    tmp = BINDING + ".tmp%d" % os.getpid()
+    cmd = [HIPCC, f"--offload-arch={ARCH}", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+           "-Wall", f"-I{INCLUDE}", f"-I{sysconfig.get_paths()['include']}", os.path.join(CSRC, "binding.cpp"),
+           "-o", tmp, f"-L{HERE}", "-lspanmerge", "-Wl,-rpath,$ORIGIN"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("binding failed:\n" + res.stderr)
+    os.replace(tmp, BINDING)
+
+
 def build(verbose: bool = False) -> str:
     out_dir = os.path.join(HERE, "_build")
     os.makedirs(out_dir, exist_ok=True)
@@ -53,6 +68,7 @@ def build(verbose: bool = False) -> str:
     if res.returncode != 0:
         raise RuntimeError("link failed:\n" + res.stderr)
     os.replace(tmp, LIB)
+    _build_binding()
     if verbose:
         print("built", LIB)
     return LIB

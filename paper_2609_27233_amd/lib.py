@@ -1,4 +1,6 @@
-"""Thin ctypes binding of ``libspanmerge.so`` (argument marshalling only).
+"""Thin binding of ``libspanmerge.so`` (argument marshalling only): the
+structures and the raw C entries through ctypes, the calls themselves through
+the extension module ``_binding``.
 
 Every function mirrors one C entry point of ``include/spanmerge.h`` and takes
 torch tensors that already live on the GPU; the work itself runs in the HIP
@@ -8,6 +10,7 @@ has not been built.
 from __future__ import annotations
 
 import ctypes as C
+import importlib
 import os
 from typing import Optional
 
@@ -61,11 +64,12 @@ class SpanMergeError(RuntimeError):
 
 
 _lib = None
+_fast = None      # the extension module, once load() has run
 
 
 def load(path: str = LIB_PATH):
     """Load the HIP library (raises if it is missing: no fallback)."""
-    global _lib
+    global _lib, _fast
     if _lib is not None:
         return _lib
     if not os.path.exists(path):
@@ -135,8 +139,22 @@ def load(path: str = LIB_PATH):
     L.sm_kv_project.restype = _I
     L.sm_kv_append_projected.argtypes = [C.POINTER(PagedCacheDesc), _P, _I, _P, C.POINTER(KVProjParams), _P, _Z, _P]
     L.sm_kv_append_projected.restype = _I
+    try:
+        fast = importlib.import_module("._binding", __package__)
+    except ImportError as e:
+        raise SpanMergeError(f"the extension module is missing ({e}); build it with "
+                             "`python -m paper_2609_27233_amd.build`") from e
+    fast.set_error(SpanMergeError)
+    _fast = fast
     _lib = L
     return L
+
+
+def _calls():
+    """The extension module's entries (loads the library on first use)."""
+    if _fast is None:
+        load()
+    return _fast
 
 
 def _ptr(t: Optional[torch.Tensor]):
@@ -149,9 +167,15 @@ def _ptr(t: Optional[torch.Tensor]):
     return t.data_ptr()
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _check(st: int, what: str):
@@ -180,25 +204,21 @@ def merge_spans(emb, row_idx, span_offsets, params: dict, h: int, out, ws, err,
     """z_s = M_phi(emb[row_idx[span s]]) for every span; writes ``out``."""
     S = span_offsets.numel() - 1
     R = row_idx.numel() if total_rows is None else total_rows
-    p = MergeParams(emb.shape[1], h, ln_eps, *(_ptr(params[k]) for k in
-                    ("Q", "W_kv", "b_kv", "g_kv", "beta_kv", "W_o", "b_o", "g_o", "beta_o")))
-    st = load().sm_merge_spans(_ptr(emb), emb.shape[0], _ptr(row_idx), R,
-                               _ptr(span_offsets), S, C.byref(p), dtype_code(emb.dtype),
-                               _ptr(out), _ptr(ws), ws.numel() * ws.element_size(),
-                               _ptr(err), _stream(stream))
+    p = _merge_params(emb.shape[1], h, params, ln_eps)
+    st = _calls().sm_merge_spans(emb, emb.shape[0], row_idx, R, span_offsets, S, p, dtype_code(emb.dtype), out, ws,
+                                 ws.nbytes, err, _stream(stream))
     _check(st, "sm_merge_spans")
 
 
 def _merge_params(d: int, h: int, params: dict, ln_eps: float):
-    return MergeParams(d, h, ln_eps, *(_ptr(params[k]) for k in
-                       ("Q", "W_kv", "b_kv", "g_kv", "beta_kv", "W_o", "b_o", "g_o", "beta_o")))
+    return _calls().merge_params(d, h, ln_eps, *(params[k] for k in
+                                 ("Q", "W_kv", "b_kv", "g_kv", "beta_kv", "W_o", "b_o", "g_o", "beta_o")))
 
 
 def merge_token_table(emb, params: dict, h: int, table, err, ln_eps: float = 1e-5, stream=None):
     """table[v] = GELU(Linear_kv(emb[v])) for every row of ``emb``."""
     p = _merge_params(emb.shape[1], h, params, ln_eps)
-    st = load().sm_merge_token_table(_ptr(emb), emb.shape[0], C.byref(p), dtype_code(emb.dtype),
-                                     _ptr(table), _ptr(err), _stream(stream))
+    st = _calls().sm_merge_token_table(emb, emb.shape[0], p, dtype_code(emb.dtype), table, err, _stream(stream))
     _check(st, "sm_merge_token_table")
 
 
@@ -209,10 +229,8 @@ def merge_spans_tabled(table, row_idx, span_offsets, params: dict, h: int, out, 
     S = span_offsets.numel() - 1
     R = row_idx.numel() if total_rows is None else total_rows
     p = _merge_params(table.shape[1], h, params, ln_eps)
-    st = load().sm_merge_spans_tabled(_ptr(table), table.shape[0], _ptr(row_idx), R,
-                                      _ptr(span_offsets), S, C.byref(p), dtype_code(table.dtype),
-                                      _ptr(out), _ptr(ws), ws.numel() * ws.element_size(),
-                                      _ptr(err), _stream(stream))
+    st = _calls().sm_merge_spans_tabled(table, table.shape[0], row_idx, R, span_offsets, S, p,
+                                        dtype_code(table.dtype), out, ws, ws.nbytes, err, _stream(stream))
     _check(st, "sm_merge_spans_tabled")
 
 
@@ -226,12 +244,9 @@ def pack_spans(seq_offsets, span_start, span_len, seq_span_offsets, pi,
     S = span_start.numel()
     d = emb.shape[1] if emb is not None else 0
     dt = dtype_code(emb.dtype) if emb is not None else SM_BF16
-    st = load().sm_pack_spans(B, _ptr(seq_offsets), total_tokens, S, _ptr(span_start),
-                              _ptr(span_len), _ptr(seq_span_offsets), _ptr(pi),
-                              _ptr(packed_offsets), _ptr(packed_src), _ptr(token_ids),
-                              _ptr(emb), emb.shape[0] if emb is not None else 0,
-                              _ptr(surrogates), d, dt, _ptr(packed), _ptr(err),
-                              _stream(stream))
+    st = _calls().sm_pack_spans(B, seq_offsets, total_tokens, S, span_start, span_len, seq_span_offsets, pi,
+                                packed_offsets, packed_src, token_ids, emb, emb.shape[0] if emb is not None else 0,
+                                surrogates, d, dt, packed, err, _stream(stream))
     _check(st, "sm_pack_spans")
 
 
@@ -272,16 +287,14 @@ class PagedCache:
 
 
 def kv_rollback(cache: PagedCache, seq_ids, k, stream=None):
-    st = load().sm_kv_rollback(C.byref(cache.desc), _ptr(seq_ids), _ptr(k), seq_ids.numel(),
-                               _stream(stream))
+    st = _calls().sm_kv_rollback(cache.desc, seq_ids, k, seq_ids.numel(), _stream(stream))
     _check(st, "sm_kv_rollback")
 
 
 def kv_append(cache: PagedCache, seq_ids, row_offsets, K, V, total_rows: Optional[int] = None,
               stream=None):
     R = K.shape[0] if total_rows is None else total_rows
-    st = load().sm_kv_append(C.byref(cache.desc), _ptr(seq_ids), _ptr(row_offsets),
-                             seq_ids.numel(), R, _ptr(K), _ptr(V), _stream(stream))
+    st = _calls().sm_kv_append(cache.desc, seq_ids, row_offsets, seq_ids.numel(), R, K, V, _stream(stream))
     _check(st, "sm_kv_append")
 
 
@@ -293,9 +306,7 @@ def decode_attention(cache: PagedCache, seq_ids, q, out, ws, max_len: int,
                      scale: Optional[float] = None, stream=None):
     n, Hq, D = q.shape
     sc = D ** -0.5 if scale is None else scale
-    st = load().sm_decode_attention(C.byref(cache.desc), _ptr(seq_ids), n, _ptr(q), Hq, sc,
-                                    max_len, _ptr(out), _ptr(ws),
-                                    ws.numel() * ws.element_size(), _stream(stream))
+    st = _calls().sm_decode_attention(cache.desc, seq_ids, n, q, Hq, sc, max_len, out, ws, ws.nbytes, _stream(stream))
     _check(st, "sm_decode_attention")
 
 
@@ -305,9 +316,8 @@ def decode_step(cache: PagedCache, seq_ids, K, V, q, out, ws, max_len: int,
     as kv_append(cache, seq_ids, arange(n + 1), K, V) then decode_attention."""
     n, Hq, D = q.shape
     sc = D ** -0.5 if scale is None else scale
-    st = load().sm_decode_step(C.byref(cache.desc), _ptr(seq_ids), n, _ptr(K), _ptr(V), _ptr(q), Hq, sc,
-                               max_len, _ptr(out), _ptr(ws), ws.numel() * ws.element_size(),
-                               _stream(stream))
+    st = _calls().sm_decode_step(cache.desc, seq_ids, n, K, V, q, Hq, sc, max_len, out, ws, ws.nbytes,
+                                 _stream(stream))
     _check(st, "sm_decode_step")
 
 
@@ -319,9 +329,8 @@ def decode_merge_step(cache: PagedCache, seq_ids, crop, K, V, q, out, ws, max_le
     all)."""
     n, Hq, D = q.shape
     sc = D ** -0.5 if scale is None else scale
-    st = load().sm_decode_merge_step(C.byref(cache.desc), _ptr(seq_ids), _ptr(crop), n, _ptr(K), _ptr(V), _ptr(q),
-                                     Hq, sc, max_len, _ptr(out), _ptr(ws), ws.numel() * ws.element_size(),
-                                     _stream(stream))
+    st = _calls().sm_decode_merge_step(cache.desc, seq_ids, crop, n, K, V, q, Hq, sc, max_len, out, ws, ws.nbytes,
+                                       _stream(stream))
     _check(st, "sm_decode_merge_step")
 
 
@@ -332,8 +341,7 @@ def decode_step_noalloc(cache: PagedCache, seq_ids, K, V, q, out, max_len: int,
     overlap)."""
     n, Hq, D = q.shape
     sc = D ** -0.5 if scale is None else scale
-    st = load().sm_decode_step_noalloc(C.byref(cache.desc), _ptr(seq_ids), n, _ptr(K), _ptr(V), _ptr(q), Hq, sc,
-                                       max_len, _ptr(out), _stream(stream))
+    st = _calls().sm_decode_step_noalloc(cache.desc, seq_ids, n, K, V, q, Hq, sc, max_len, out, _stream(stream))
     _check(st, "sm_decode_step_noalloc")
 
 
@@ -343,8 +351,8 @@ def prefill_attention(cache: PagedCache, seq_ids, q_offsets, q, out, max_rows: i
     q, out [rows, Hq, D] bf16; q_offsets [n + 1] int32 row ranges."""
     rows, Hq, D = q.shape
     sc = D ** -0.5 if scale is None else scale
-    st = load().sm_prefill_attention(C.byref(cache.desc), _ptr(seq_ids), seq_ids.numel(), _ptr(q_offsets), rows,
-                                     _ptr(q), Hq, sc, max_rows, _ptr(out), _stream(stream))
+    st = _calls().sm_prefill_attention(cache.desc, seq_ids, seq_ids.numel(), q_offsets, rows, q, Hq, sc, max_rows,
+                                       out, _stream(stream))
     _check(st, "sm_prefill_attention")
 
 
@@ -381,13 +389,12 @@ def rules_build(table: RuleTable, rules, ws=None, stream=None):
     need = load().sm_rules_build_workspace_bytes(table.capacity)
     if ws is None:
         ws = torch.empty(need, dtype=torch.uint8, device=rules.device)
-    st = load().sm_rules_build(_ptr(rules), rules.shape[0], C.byref(table.desc), _ptr(ws),
-                               ws.numel() * ws.element_size(), _stream(stream))
+    st = _calls().sm_rules_build(rules, rules.shape[0], table.desc, ws, ws.nbytes, _stream(stream))
     _check(st, "sm_rules_build")
 
 
 def rules_lookup(table: RuleTable, grams, ids, stream=None):
-    st = load().sm_rules_lookup(C.byref(table.desc), _ptr(grams), grams.shape[0], _ptr(ids), _stream(stream))
+    st = _calls().sm_rules_lookup(table.desc, grams, grams.shape[0], ids, _stream(stream))
     _check(st, "sm_rules_lookup")
 
 
@@ -398,18 +405,16 @@ def match_prompt_workspace_bytes(B: int, total_tokens: int) -> int:
 def match_prompt(table: RuleTable, token_ids, seq_offsets, span_start, span_len, span_rule,
                  seq_span_offsets, ws, stream=None):
     B = seq_offsets.numel() - 1
-    st = load().sm_match_prompt(C.byref(table.desc), _ptr(token_ids), _ptr(seq_offsets), B, token_ids.numel(),
-                                _ptr(span_start), _ptr(span_len), _ptr(span_rule), _ptr(seq_span_offsets),
-                                _ptr(ws), ws.numel() * ws.element_size(), _stream(stream))
+    st = _calls().sm_match_prompt(table.desc, token_ids, seq_offsets, B, token_ids.numel(), span_start, span_len,
+                                  span_rule, seq_span_offsets, ws, ws.nbytes, _stream(stream))
     _check(st, "sm_match_prompt")
 
 
 def match_decode(table: RuleTable, state, seq_ids, new_tokens, k_out, rule_out,
                  cache: Optional[PagedCache] = None, stream=None):
     """state [max_seqs, 4] int32 (zeroed when a sequence starts generating)."""
-    st = load().sm_match_decode(C.byref(table.desc), _ptr(state), state.shape[0], _ptr(seq_ids),
-                                _ptr(new_tokens), seq_ids.numel(), _ptr(k_out), _ptr(rule_out),
-                                None if cache is None else C.byref(cache.desc), _stream(stream))
+    st = _calls().sm_match_decode(table.desc, state, state.shape[0], seq_ids, new_tokens, seq_ids.numel(), k_out,
+                                  rule_out, None if cache is None else cache.desc, _stream(stream))
     _check(st, "sm_match_decode")
 
 
@@ -419,9 +424,8 @@ def match_decode(table: RuleTable, state, seq_ids, new_tokens, k_out, rule_out,
 def gather_surrogates(lut, rule_ids, out, err, emb=None, token_ids=None, stream=None):
     """out[i] = lut[rule_ids[i]] if rule_ids[i] >= 0 else emb[token_ids[i]]."""
     n, d = out.shape
-    st = load().sm_gather_surrogates(_ptr(emb), 0 if emb is None else emb.shape[0], _ptr(lut), lut.shape[0],
-                                     _ptr(token_ids), _ptr(rule_ids), n, d, dtype_code(out.dtype), _ptr(out),
-                                     _ptr(err), _stream(stream))
+    st = _calls().sm_gather_surrogates(emb, 0 if emb is None else emb.shape[0], lut, lut.shape[0], token_ids,
+                                       rule_ids, n, d, dtype_code(out.dtype), out, err, _stream(stream))
     _check(st, "sm_gather_surrogates")
 
 
@@ -431,10 +435,9 @@ def span_dedupe(span_rule, span_start, span_len, num_rules, token_ids, uniq_span
     need = load().sm_span_dedupe_workspace_bytes(S, num_rules)
     if ws is None:
         ws = torch.empty(need, dtype=torch.uint8, device=span_rule.device)
-    st = load().sm_span_dedupe(_ptr(span_rule), _ptr(span_start), _ptr(span_len), S, num_rules, _ptr(token_ids),
-                               token_ids.numel(), _ptr(uniq_span), _ptr(span_slot), _ptr(uniq_row_idx),
-                               _ptr(uniq_span_offsets), _ptr(num_uniq), _ptr(ws), ws.numel() * ws.element_size(),
-                               _ptr(err), _stream(stream))
+    st = _calls().sm_span_dedupe(span_rule, span_start, span_len, S, num_rules, token_ids, token_ids.numel(),
+                                 uniq_span, span_slot, uniq_row_idx, uniq_span_offsets, num_uniq, ws, ws.nbytes, err,
+                                 _stream(stream))
     _check(st, "sm_span_dedupe")
 
 
@@ -442,7 +445,7 @@ def span_dedupe(span_rule, span_start, span_len, num_rules, token_ids, uniq_span
 # K/V state of an input row at its compressed position
 
 def _proj_params(W_k, W_v, rope_theta, rms_eps):
-    return KVProjParams(W_k.shape[1], _ptr(W_k), _ptr(W_v), rope_theta, rms_eps)
+    return _calls().kv_proj_params(W_k.shape[1], W_k, W_v, rope_theta, rms_eps)
 
 
 def kv_project_workspace_bytes(n: int, d: int, num_kv_heads: int, head_dim: int) -> int:
@@ -457,8 +460,7 @@ def kv_project(cache: PagedCache, seq_ids, x, W_k, W_v, K, V, ws=None, rope_thet
         ws = torch.empty(kv_project_workspace_bytes(n, x.shape[1], cache.H, cache.D), dtype=torch.uint8,
                          device=x.device)
     p = _proj_params(W_k, W_v, rope_theta, rms_eps)
-    st = load().sm_kv_project(C.byref(cache.desc), _ptr(seq_ids), n, _ptr(x), C.byref(p), _ptr(K), _ptr(V),
-                              _ptr(ws), ws.numel() * ws.element_size(), _stream(stream))
+    st = _calls().sm_kv_project(cache.desc, seq_ids, n, x, p, K, V, ws, ws.nbytes, _stream(stream))
     _check(st, "sm_kv_project")
 
 
@@ -469,6 +471,5 @@ def kv_append_projected(cache: PagedCache, seq_ids, x, W_k, W_v, ws=None, rope_t
         ws = torch.empty(kv_project_workspace_bytes(n, x.shape[1], cache.H, cache.D), dtype=torch.uint8,
                          device=x.device)
     p = _proj_params(W_k, W_v, rope_theta, rms_eps)
-    st = load().sm_kv_append_projected(C.byref(cache.desc), _ptr(seq_ids), n, _ptr(x), C.byref(p), _ptr(ws),
-                                       ws.numel() * ws.element_size(), _stream(stream))
+    st = _calls().sm_kv_append_projected(cache.desc, seq_ids, n, x, p, ws, ws.nbytes, _stream(stream))
     _check(st, "sm_kv_append_projected")
