@@ -50,7 +50,7 @@ __device__ __forceinline__ RollbackReads rollback_reads(const CacheArgs &c, int 
 // error bit set, nothing.
 __device__ __forceinline__ void rollback_body(const CacheArgs &c, const RollbackReads &rd, int s, int k, int n) {
   __shared__ int red[16];
-  __shared__ int fl_inval, fl_range;
+  __shared__ int fl_inval, fl_range, fl_many;
   __shared__ int ids[kMetaThreads];
   const int t = threadIdx.x;
   if (rd.err != 0) return;  // sticky: the cache is frozen until the caller clears err
@@ -58,6 +58,7 @@ __device__ __forceinline__ void rollback_body(const CacheArgs &c, const Rollback
   if (t == 0) {
     fl_inval = 0;
     fl_range = 0;
+    fl_many = 0;
   }
   if (active) ids[t] = s;
   __syncthreads();
@@ -73,6 +74,8 @@ __device__ __forceinline__ void rollback_body(const CacheArgs &c, const Rollback
     L = rd.len;
     if (L < 0 || L > cap || k > L) fl_range = 1;
     else freed = blocks_for(L, c.bs_log2) - blocks_for(L - k, c.bs_log2);
+    // up to two blocks a request (a decode step's crop) the search costs more than it saves
+    if (freed > 2) fl_many = 1;
   }
   __syncthreads();
   if (fl_range) {
@@ -86,18 +89,35 @@ __device__ __forceinline__ void rollback_body(const CacheArgs &c, const Rollback
     if (t == 0) set_err(c.err, SM_ERR_ERANGE);
     return;
   }
-  if (active) {
-    // requests are served in reverse order: request t's first push lands
-    // above the blocks of every later request
+  // Requests are served in reverse order: request t's first push lands above
+  // the blocks of every later request, its highest logical block first.
+  if (fl_many) {
+    // The freed blocks of all requests as one list, a thread per block: a
+    // thread alone with its request's blocks waits out a table read per block
+    // (16 requests of 154 blocks: 32.6 us; as one list 6.6 us).
+    __shared__ int ends[kMetaThreads], lens[kMetaThreads];
+    ends[t] = incl;  // threads past n repeat the total
+    lens[t] = L;
+    __syncthreads();
+    for (int e = t; e < total; e += kMetaThreads) {
+      int r = 0;  // the first request whose blocks end past e
+#pragma unroll
+      for (int step = kMetaThreads / 2; step > 0; step >>= 1) r += ends[r + step - 1] <= e ? step : 0;
+      int32_t *cell = c.block_table + (int64_t)ids[r] * c.max_blocks + blocks_for(lens[r], c.bs_log2) -
+                      1 - (e - (r > 0 ? ends[r - 1] : 0));
+      c.free_stack[top + total - ends[r] + (e - (r > 0 ? ends[r - 1] : 0))] = *cell;
+      *cell = -1;
+    }
+  } else if (active) {
     int pos = top + (total - incl);
     int32_t *row = c.block_table + (int64_t)s * c.max_blocks;
-    const int nb_old = blocks_for(L, c.bs_log2), nb_new = blocks_for(L - k, c.bs_log2);
-    for (int j = nb_old - 1; j >= nb_new; --j) {
+    const int nb_old = blocks_for(L, c.bs_log2);
+    for (int j = nb_old - 1; j >= nb_old - freed; --j) {
       c.free_stack[pos++] = row[j];
       row[j] = -1;
     }
-    c.lengths[s] = L - k;
   }
+  if (active) c.lengths[s] = L - k;
   if (t == 0) *c.free_top = top + total;
 }
 

@@ -119,6 +119,30 @@ def test_rollback_reappend_restores_gpu_cache(orc):
     assert int(c.free_top.item()) == top and torch.equal(stack, c.free_stack[:top])
 
 
+@pytest.mark.parametrize("n,blocks", [(1, 3), (1, 2), (5, 40), (7, 147), (16, 70), (130, 8), (600, 3)])
+def test_rollback_of_many_blocks(orc, n, blocks):
+    """Crops that free up to `blocks` blocks a request: the freed blocks are dealt over the workgroup's threads
+    when a request frees more than two (n x blocks from below one round of 1024 threads to past it)."""
+    rng = np.random.RandomState(n + blocks)
+    bs, NB = 16, n * blocks + 3
+    oc = orc.OracleCache(bf16=True, num_kv_heads=1, head_dim=64, block_size=bs, num_blocks=NB, max_seqs=n + 2,
+                         max_blocks_per_seq=blocks, free_order=rng.permutation(NB).astype(np.int32))
+    c = gpu_cache_like(oc, torch.bfloat16)
+    ids = rng.permutation(n + 2)[:n].astype(np.int32)
+    m = np.maximum(1, blocks * bs - rng.randint(0, bs, n) * (rng.rand(n) < 0.7))
+    assert _append_both(orc, oc, c, ids, m, rng, torch.bfloat16) == orc.OK
+    for part in (0.3, 1.0):                                          # some of it, then all that is left
+        k = np.array([int(part * oc.lengths[s]) if part == 1.0 or rng.rand() < 0.8 else 0 for s in ids], np.int32)
+        k[0] = oc.lengths[ids[0]]
+        order = rng.permutation(n)
+        say("crop", n, blocks, int(k.sum()))
+        assert oc.rollback(ids[order], k[order]) == orc.OK
+        sm.kv_rollback(c, i32(ids[order]), i32(k[order]))
+        torch.cuda.synchronize()
+        assert c.error_bits() == 0
+        assert_same_state(c, oc)
+
+
 def test_bulk_prompt_append_llama3_8b_shape(orc):
     """Appending the compacted prompts of the 16 x 4096 workload (about 39k
     rows, 161 MB of K/V) in one call."""
