@@ -277,7 +277,14 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16(PrefillArgs a) {
     if (t + 1 < ntiles) fetch((t + 1) * SPAN, stage);  // in flight during this pass
 
     if (t0 <= wave_hi) {
-      // S^T = K . Q^T, one 32-key block at a time: its fragment reads first, then its products
+      // S^T = K . Q^T, one 32-key block at a time: its fragment reads first,
+      // then its products.  Raised priority until the V reads are issued: the
+      // wave that feeds the matrix unit goes before the SIMD's other wave's
+      // softmax, so the two fall out of step (512 rows after 16384, KS = 4:
+      // 235 -> 217 us with the append; around the second product instead it
+      // measured 243; the 16 x 2458 batch gains 1 to 2% and loses 1% with
+      // the second).
+      __builtin_amdgcn_s_setprio(1);
       f32x16_t sc[SUB];
 #pragma unroll
       for (int sb = 0; sb < SUB; ++sb) {
@@ -300,6 +307,8 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16(PrefillArgs a) {
 #pragma unroll
         for (int kst = 0; kst < 2; ++kst)
           vf[rb][kst] = *(const u32x4_t *)(&v_lds[buf * VBUF + v_at(kg * DH + 32 * rb + c32, 2 * kst + h2)]);
+
+      __builtin_amdgcn_s_setprio(0);
 
       // online softmax per query column; register r of block sb holds token
       // t0 + 32 sb + tau(8 (r >> 2) + 4 h2 + (r & 3)).  Masked scores become
