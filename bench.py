@@ -154,7 +154,7 @@ class Job:
         rng = np.random.RandomState(w.seed + 5)
         # the resident batches reach a merge step together: the fresh spans
         # of a lane's batches go to the merge module together, 64 spans (4
-        # batches of 16) per call (the skinny GEMM's row limit), each batch
+        # batches of 16) per call, each batch
         # then rolls back its own cache
         self.merge_group = max(1, 64 // B)
         G = self.merge_group

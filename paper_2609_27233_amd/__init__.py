@@ -1,7 +1,7 @@
 """Span-merging (UMIM) inference hot path on AMD Instinct MI355X (gfx950).
 
 Submodules:
-  lib       ctypes binding of libspanmerge.so (the C ABI in include/spanmerge.h)
+  lib       binding of libspanmerge.so (the C ABI in include/spanmerge.h)
   workload  seeded synthetic inputs for the five benchmark workloads
   build     compiles the HIP sources
 
