@@ -46,11 +46,11 @@ def _compile(src: str, out_dir: str) -> str:
 
 
 def _build_binding() -> None:
-    """The extension module beside the library, which it finds by its own place."""
+    """The extension module beside the library (lib.load() tells it which library to open)."""
     tmp = BINDING + ".tmp%d" % os.getpid()
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
            "-Wall", f"-I{INCLUDE}", f"-I{sysconfig.get_paths()['include']}", os.path.join(CSRC, "binding.cpp"),
-           "-o", tmp, f"-L{HERE}", "-lspanmerge", "-Wl,-rpath,$ORIGIN"]
+           "-o", tmp]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("binding failed:\n" + res.stderr)

@@ -9,6 +9,7 @@
 // stream handle, plain numbers for the rest; it returns the status.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
+#include <dlfcn.h>
 
 #include <cstring>
 #include <tuple>
@@ -18,6 +19,15 @@
 #include "spanmerge.h"
 
 namespace {
+
+// The entries, resolved by open() from the library that the program loaded.
+#define SM_ENTRIES(X)                                                                                         \
+  X(sm_merge_spans) X(sm_merge_token_table) X(sm_merge_spans_tabled) X(sm_pack_spans) X(sm_kv_rollback)       \
+  X(sm_kv_append) X(sm_decode_attention) X(sm_decode_step) X(sm_decode_merge_step)                            \
+  X(sm_decode_step_noalloc) X(sm_prefill_attention) X(sm_rules_build) X(sm_rules_lookup) X(sm_match_prompt)   \
+  X(sm_match_decode) X(sm_gather_surrogates) X(sm_span_dedupe) X(sm_kv_project) X(sm_kv_append_projected)
+#define SM_SLOT(name) decltype(&::name) p_##name;
+SM_ENTRIES(SM_SLOT)
 
 PyObject *g_is_cuda, *g_is_contiguous, *g_data_ptr;  // interned names
 PyObject *g_error;                                   // the exception for unusable tensors
@@ -109,9 +119,35 @@ PyObject *dispatch(sm_status (*fn)(A...), PyObject *const *args, Py_ssize_t n) {
   return call(fn, args, n, std::index_sequence_for<A...>{});
 }
 
-template <auto Fn>
+template <auto *Fn>
 PyObject *entry(PyObject *, PyObject *const *args, Py_ssize_t n) {
-  return dispatch(Fn, args, n);
+  if (!*Fn) {
+    PyErr_SetString(g_error, "the library is not open");
+    return nullptr;
+  }
+  return dispatch(*Fn, args, n);
+}
+
+// open(path): the entries of the library at `path` (kept loaded)
+PyObject *open_library(PyObject *, PyObject *path) {
+  PyObject *name;
+  if (!PyUnicode_FSConverter(path, &name)) return nullptr;
+  void *lib = dlopen(PyBytes_AS_STRING(name), RTLD_NOW | RTLD_LOCAL);
+  Py_DECREF(name);
+  if (!lib) {
+    PyErr_SetString(g_error, dlerror());
+    return nullptr;
+  }
+#define SM_FIND(name)                                                   \
+  void *const f_##name = dlsym(lib, #name);                             \
+  if (!f_##name) {                                                      \
+    PyErr_SetString(g_error, "the library lacks the entry " #name);     \
+    return nullptr;                                                     \
+  }
+  SM_ENTRIES(SM_FIND)
+#define SM_STORE(name) p_##name = (decltype(&::name))f_##name;
+  SM_ENTRIES(SM_STORE)
+  Py_RETURN_NONE;
 }
 
 // merge_params(d, h, ln_eps, Q, W_kv, b_kv, g_kv, beta_kv, W_o, b_o, g_o, beta_o): the structure's bytes
@@ -149,17 +185,13 @@ PyObject *set_error(PyObject *, PyObject *type) {
   Py_RETURN_NONE;
 }
 
-#define SM_ENTRY(name) {#name, (PyCFunction)(void (*)(void))entry<name>, METH_FASTCALL, nullptr}
+#define SM_ENTRY(name) {#name, (PyCFunction)(void (*)(void))entry<&p_##name>, METH_FASTCALL, nullptr},
 PyMethodDef methods[] = {
-    SM_ENTRY(sm_merge_spans), SM_ENTRY(sm_merge_token_table), SM_ENTRY(sm_merge_spans_tabled),
-    SM_ENTRY(sm_pack_spans), SM_ENTRY(sm_kv_rollback), SM_ENTRY(sm_kv_append), SM_ENTRY(sm_decode_attention),
-    SM_ENTRY(sm_decode_step), SM_ENTRY(sm_decode_merge_step), SM_ENTRY(sm_decode_step_noalloc),
-    SM_ENTRY(sm_prefill_attention), SM_ENTRY(sm_rules_build), SM_ENTRY(sm_rules_lookup), SM_ENTRY(sm_match_prompt),
-    SM_ENTRY(sm_match_decode), SM_ENTRY(sm_gather_surrogates), SM_ENTRY(sm_span_dedupe), SM_ENTRY(sm_kv_project),
-    SM_ENTRY(sm_kv_append_projected),
+    SM_ENTRIES(SM_ENTRY)
     {"merge_params", (PyCFunction)(void (*)(void))merge_params, METH_FASTCALL, nullptr},
     {"kv_proj_params", (PyCFunction)(void (*)(void))kv_proj_params, METH_FASTCALL, nullptr},
     {"set_error", set_error, METH_O, nullptr},
+    {"open", open_library, METH_O, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

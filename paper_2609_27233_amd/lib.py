@@ -145,6 +145,7 @@ def load(path: str = LIB_PATH):
         raise SpanMergeError(f"the extension module is missing ({e}); build it with "
                              "`python -m paper_2609_27233_amd.build`") from e
     fast.set_error(SpanMergeError)
+    fast.open(path)
     _fast = fast
     _lib = L
     return L

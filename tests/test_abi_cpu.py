@@ -3,6 +3,9 @@ argument checks return their status without touching a GPU."""
 import ctypes as C
 import os
 import re
+import shutil
+import subprocess
+import sys
 
 import pytest
 
@@ -202,3 +205,17 @@ def test_kv_project_argument_checks(L):
     assert ap(n=0) == sm.SM_OK
     assert ap(ws_bytes=need - 1) == sm.SM_EINVAL
     assert ap(desc=_desc(head_dim=96)) == sm.SM_EINVAL
+
+
+def test_calls_go_to_the_loaded_library(tmp_path):
+    """load(path) of a copy of the library: the calls use that copy, and no other one is mapped."""
+    copy = tmp_path / "libcopy.so"
+    shutil.copy(sm.LIB_PATH, copy)
+    code = ("import sys\n"
+            "from paper_2609_27233_amd import lib\n"
+            "lib.load(sys.argv[1])\n"
+            "assert lib._calls().sm_kv_rollback(None, None, None, 0, 0) == 1\n"
+            "maps = open('/proc/self/maps').read()\n"
+            "assert sys.argv[1] in maps and 'libspanmerge.so' not in maps\n")
+    subprocess.run([sys.executable, "-c", code, str(copy)], check=True, timeout=120,
+                   cwd=ROOT)
