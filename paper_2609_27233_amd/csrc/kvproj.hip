@@ -80,7 +80,7 @@ __device__ void append_rows_meta(const CacheArgs &c, const int32_t *seq_ids, int
   for (int k = 0; k < RPT; ++k) {
     if (r0 + k < n) {
       bad |= !id_ok(ids, r0 + k, s[k], c.max_seqs);
-      range |= L[k] < 0 || L[k] + 1 > cap;
+      range |= L[k] < 0 || L[k] >= cap;  // (no L + 1: a corrupt length may be the largest int)
       need[k] = (L[k] & (bs - 1)) == 0;
     } else {
       need[k] = 0;

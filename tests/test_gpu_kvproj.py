@@ -125,7 +125,7 @@ def test_append_projected_many_rows(orc, n, H, D, d, bs):
     assert_same_state(c, oc)
 
 
-@pytest.mark.parametrize("what", ["repeat", "full stack", "no room", "bad stack", "frozen"])
+@pytest.mark.parametrize("what", ["repeat", "full stack", "no room", "largest int", "bad stack", "frozen"])
 def test_append_projected_all_or_nothing(orc, what):
     """Each failing check of the append leaves the cache as it was."""
     H, D, d, bs = 4, 64, 256, 16
@@ -138,6 +138,9 @@ def test_append_projected_all_or_nothing(orc, what):
         bit = sm.ERR_ENOMEM
     elif what == "no room":
         c.lengths[1] = c.max_blocks * bs
+        bit = sm.ERR_ERANGE
+    elif what == "largest int":                           # length + 1 does not fit 32 bits
+        c.lengths[1] = 2 ** 31 - 1
         bit = sm.ERR_ERANGE
     elif what == "bad stack":
         c.free_stack[int(c.free_top.item()) - 2] = c.num_blocks
