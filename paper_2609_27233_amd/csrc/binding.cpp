@@ -4,9 +4,13 @@
 // conversion of their arguments in Python took longer than the launches (one
 // step's rule check, input row and projected append: 36 us of host time for
 // four calls, 30 us of kernels).  Every entry here takes the C call's
-// arguments in order: a tensor (or None) for a device pointer, an object with
-// a buffer (a ctypes structure, bytes) for a host structure, an int for a
-// stream handle, plain numbers for the rest; it returns the status.
+// arguments in order: a tensor (or None) for a device pointer, the ctypes
+// structure for a cache or a rule table, the bytes that merge_params or
+// kv_proj_params gave for parameters, an int (or None) for a stream handle,
+// plain numbers for the rest; it returns the status.  Values are taken and
+// refused as ctypes does for the same prototypes: integers wrap to the C
+// type's width, a ctypes number of the argument's own type counts as its
+// value, and what does not fit raises ctypes.ArgumentError.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <dlfcn.h>
@@ -29,14 +33,18 @@ namespace {
 #define SM_SLOT(name) decltype(&::name) p_##name;
 SM_ENTRIES(SM_SLOT)
 
-PyObject *g_is_cuda, *g_is_contiguous, *g_data_ptr;  // interned names
-PyObject *g_error;                                   // the exception for unusable tensors
+PyObject *g_is_cuda, *g_is_contiguous, *g_data_ptr, *g_value;  // interned names
+
+// What setup() is given: the exceptions for unusable tensors and for other
+// unusable arguments, the structures, and the C types of plain arguments.
+enum { kError, kArgumentError, kPagedCache, kRuleTable, kInt, kInt64, kFloat, kSize, kPointer, kTypes };
+PyObject *g_type[kTypes];
 
 bool is_true(PyObject *r, const char *otherwise) {
   if (!r) return false;
   const int v = PyObject_IsTrue(r);
   Py_DECREF(r);
-  if (v == 0) PyErr_SetString(g_error, otherwise);
+  if (v == 0) PyErr_SetString(g_type[kError], otherwise);
   return v > 0;
 }
 
@@ -56,47 +64,80 @@ template <class T>
 constexpr bool is_host_struct = std::is_same_v<T, sm_paged_cache> || std::is_same_v<T, sm_rule_table> ||
                                 std::is_same_v<T, sm_merge_params> || std::is_same_v<T, sm_kv_proj_params>;
 
+// the C type that a plain argument (or a stream handle) has in the prototypes
+template <class A>
+constexpr int plain_type = std::is_same_v<A, hipStream_t>      ? kPointer
+                           : std::is_floating_point_v<A>       ? kFloat
+                           : std::is_same_v<A, size_t>         ? kSize
+                           : sizeof(A) == 8                    ? kInt64
+                                                               : kInt;
+
+// a new reference to o, or to its value where o is a ctypes number of type t
+PyObject *plain_value(PyObject *o, int t) {
+  if (!PyLong_Check(o) && !PyFloat_Check(o) && PyObject_TypeCheck(o, (PyTypeObject *)g_type[t]))
+    return PyObject_GetAttr(o, g_value);
+  Py_INCREF(o);
+  return o;
+}
+
+template <class T>
+bool get_struct(PyObject *o, T **v) {
+  *v = nullptr;
+  if (o == Py_None) return true;
+  constexpr int t = std::is_same_v<std::remove_cv_t<T>, sm_paged_cache>  ? kPagedCache
+                    : std::is_same_v<std::remove_cv_t<T>, sm_rule_table> ? kRuleTable
+                                                                         : kTypes;  // the parameters: bytes
+  const bool right = t == kTypes ? PyBytes_Check(o) : PyObject_TypeCheck(o, (PyTypeObject *)g_type[t % kTypes]);
+  Py_buffer b;
+  if (!right) {
+    PyErr_SetString(PyExc_TypeError, "wrong structure");
+    return false;
+  }
+  if (PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) return false;
+  const bool whole = b.len >= (Py_ssize_t)sizeof(T);
+  *v = (T *)b.buf;  // (the caller's object keeps it for the length of the call)
+  PyBuffer_Release(&b);
+  if (!whole) PyErr_SetString(PyExc_TypeError, "structure too short");
+  return whole;
+}
+
 template <class A>
 bool get(PyObject *o, A *v) {
-  if constexpr (std::is_same_v<A, hipStream_t>) {
-    *v = (hipStream_t)PyLong_AsVoidPtr(o);
-    return !PyErr_Occurred();
-  } else if constexpr (std::is_pointer_v<A>) {
-    using T = std::remove_cv_t<std::remove_pointer_t<A>>;
-    if constexpr (is_host_struct<T>) {
-      *v = nullptr;
-      if (o == Py_None) return true;
-      Py_buffer b;
-      if (PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) return false;
-      const bool whole = b.len >= (Py_ssize_t)sizeof(T);
-      *v = (A)b.buf;  // (the caller's object keeps it for the length of the call)
-      PyBuffer_Release(&b);
-      if (!whole) PyErr_SetString(PyExc_ValueError, "structure too short");
-      return whole;
+  if constexpr (std::is_pointer_v<A> && !std::is_same_v<A, hipStream_t>) {
+    if constexpr (is_host_struct<std::remove_cv_t<std::remove_pointer_t<A>>>) {
+      return get_struct(o, v);
     } else {
       void *p;
       if (!tensor_address(o, &p)) return false;
       *v = (A)p;
       return true;
     }
-  } else if constexpr (std::is_floating_point_v<A>) {
-    *v = (A)PyFloat_AsDouble(o);
-    return !PyErr_Occurred();
-  } else if constexpr (std::is_same_v<A, size_t>) {
-    *v = PyLong_AsSize_t(o);
-    return !PyErr_Occurred();
   } else {
-    const long long x = PyLong_AsLongLong(o);
-    if (PyErr_Occurred()) return false;
-    if constexpr (sizeof(A) == 4) {
-      if (x != (long long)(int)x) {
-        PyErr_SetString(PyExc_OverflowError, "argument does not fit 32 bits");
-        return false;
-      }
+    PyObject *x = plain_value(o, plain_type<A>);
+    if (!x) return false;
+    if constexpr (std::is_same_v<A, hipStream_t>) {
+      *v = nullptr;
+      if (PyLong_Check(x)) *v = (hipStream_t)(uintptr_t)PyLong_AsUnsignedLongLongMask(x);
+      else if (x != Py_None) PyErr_SetString(PyExc_TypeError, "expected a stream handle");
+    } else if constexpr (std::is_floating_point_v<A>) {
+      *v = (A)PyFloat_AsDouble(x);
+    } else {
+      *v = (A)PyLong_AsUnsignedLongLongMask(x);
     }
-    *v = (A)x;
-    return true;
+    Py_DECREF(x);
+    return !PyErr_Occurred();
   }
+}
+
+// A TypeError of argument `at` (from 1) as ctypes reports it.
+void argument_error(int at) {
+  if (!PyErr_ExceptionMatches(PyExc_TypeError)) return;
+  PyObject *type, *value, *trace;
+  PyErr_Fetch(&type, &value, &trace);
+  PyErr_Format(g_type[kArgumentError], "argument %d: %S: %S", at, type, value ? value : Py_None);
+  Py_XDECREF(type);
+  Py_XDECREF(value);
+  Py_XDECREF(trace);
 }
 
 template <class... A, size_t... I>
@@ -106,7 +147,11 @@ PyObject *call(sm_status (*fn)(A...), PyObject *const *args, Py_ssize_t n, std::
     return nullptr;
   }
   std::tuple<A...> v;
-  if (!(get(args[I], &std::get<I>(v)) && ...)) return nullptr;
+  int at = 0;
+  if (!((++at, get(args[I], &std::get<I>(v))) && ...)) {
+    argument_error(at);
+    return nullptr;
+  }
   sm_status st;
   Py_BEGIN_ALLOW_THREADS;
   st = fn(std::get<I>(v)...);
@@ -122,7 +167,7 @@ PyObject *dispatch(sm_status (*fn)(A...), PyObject *const *args, Py_ssize_t n) {
 template <auto *Fn>
 PyObject *entry(PyObject *, PyObject *const *args, Py_ssize_t n) {
   if (!*Fn) {
-    PyErr_SetString(g_error, "the library is not open");
+    PyErr_SetString(g_type[kError], "the library is not open");
     return nullptr;
   }
   return dispatch(*Fn, args, n);
@@ -135,13 +180,13 @@ PyObject *open_library(PyObject *, PyObject *path) {
   void *lib = dlopen(PyBytes_AS_STRING(name), RTLD_NOW | RTLD_LOCAL);
   Py_DECREF(name);
   if (!lib) {
-    PyErr_SetString(g_error, dlerror());
+    PyErr_SetString(g_type[kError], dlerror());
     return nullptr;
   }
 #define SM_FIND(name)                                                   \
   void *const f_##name = dlsym(lib, #name);                             \
   if (!f_##name) {                                                      \
-    PyErr_SetString(g_error, "the library lacks the entry " #name);     \
+    PyErr_SetString(g_type[kError], "the library lacks the entry " #name);     \
     return nullptr;                                                     \
   }
   SM_ENTRIES(SM_FIND)
@@ -179,9 +224,21 @@ PyObject *kv_proj_params(PyObject *, PyObject *const *args, Py_ssize_t n) {
   return PyBytes_FromStringAndSize((const char *)&p, sizeof p);
 }
 
-PyObject *set_error(PyObject *, PyObject *type) {
-  Py_INCREF(type);
-  Py_XSETREF(g_error, type);
+// setup(types): the objects of the enumeration above, in its order
+PyObject *setup(PyObject *, PyObject *types) {
+  if (!PyTuple_Check(types) || PyTuple_GET_SIZE(types) != kTypes) {
+    PyErr_SetString(PyExc_TypeError, "setup takes a tuple of the types");
+    return nullptr;
+  }
+  for (int i = 0; i < kTypes; ++i) {
+    PyObject *t = PyTuple_GET_ITEM(types, i);
+    if (!PyType_Check(t)) {
+      PyErr_SetString(PyExc_TypeError, "setup takes a tuple of the types");
+      return nullptr;
+    }
+    Py_INCREF(t);
+    Py_XSETREF(g_type[i], t);
+  }
   Py_RETURN_NONE;
 }
 
@@ -190,7 +247,7 @@ PyMethodDef methods[] = {
     SM_ENTRIES(SM_ENTRY)
     {"merge_params", (PyCFunction)(void (*)(void))merge_params, METH_FASTCALL, nullptr},
     {"kv_proj_params", (PyCFunction)(void (*)(void))kv_proj_params, METH_FASTCALL, nullptr},
-    {"set_error", set_error, METH_O, nullptr},
+    {"setup", setup, METH_O, nullptr},
     {"open", open_library, METH_O, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 
@@ -202,8 +259,11 @@ PyMODINIT_FUNC PyInit__binding(void) {
   g_is_cuda = PyUnicode_InternFromString("is_cuda");
   g_is_contiguous = PyUnicode_InternFromString("is_contiguous");
   g_data_ptr = PyUnicode_InternFromString("data_ptr");
-  if (!g_is_cuda || !g_is_contiguous || !g_data_ptr) return nullptr;
-  Py_INCREF(PyExc_RuntimeError);
-  g_error = PyExc_RuntimeError;
+  g_value = PyUnicode_InternFromString("value");
+  if (!g_is_cuda || !g_is_contiguous || !g_data_ptr || !g_value) return nullptr;
+  for (PyObject *&t : g_type) {  // (until setup: no structure or ctypes number is of these types)
+    Py_INCREF(PyExc_RuntimeError);
+    t = PyExc_RuntimeError;
+  }
   return PyModule_Create(&module);
 }

@@ -144,7 +144,7 @@ def load(path: str = LIB_PATH):
     except ImportError as e:
         raise SpanMergeError(f"the extension module is missing ({e}); build it with "
                              "`python -m paper_2609_27233_amd.build`") from e
-    fast.set_error(SpanMergeError)
+    fast.setup((SpanMergeError, C.ArgumentError, PagedCacheDesc, RuleTableDesc, _I, _L, _F, _Z, _P))
     fast.open(path)
     _fast = fast
     _lib = L

@@ -219,3 +219,77 @@ def test_calls_go_to_the_loaded_library(tmp_path):
             "assert sys.argv[1] in maps and 'libspanmerge.so' not in maps\n")
     subprocess.run([sys.executable, "-c", code, str(copy)], check=True, timeout=120,
                    cwd=ROOT)
+
+
+class _Index:
+    def __index__(self):
+        return 16
+
+
+class _Float:
+    def __float__(self):
+        return 0.5
+
+
+class _Tensor:
+    """Stands for a GPU tensor at address 1."""
+    is_cuda = True
+
+    def is_contiguous(self):
+        return True
+
+    def data_ptr(self):
+        return 1
+
+
+INTS = [16, True, -1, 17, 2 ** 31, 2 ** 32 + 16, 2 ** 32 - 1, 2 ** 70, _Index(), C.c_int(16), C.c_long(16), C.c_uint(16),
+        C.c_float(16), 16.0, "16", b"16", None]
+FLOATS = [0.5, 1, -0.0, 1e300, float("inf"), float("nan"), _Float(), _Index(), C.c_float(0.5), C.c_double(0.5), "1", None]
+STREAMS = [0, None, C.c_void_p(0), C.c_void_p(None), -1, 2 ** 64, _Index(), 0.0, C.c_int(0)]
+
+
+@pytest.mark.parametrize("kind,value", [(k, v) for k, vs in (("int", INTS), ("int64", INTS), ("size", INTS),
+                                                             ("float", FLOATS), ("stream", STREAMS)) for v in vs],
+                         ids=lambda v: v if isinstance(v, str) else type(v).__name__ + "-" + str(v)[:12])
+def test_binding_takes_and_refuses_what_ctypes_does(L, kind, value):
+    """The same value for the same argument through the extension module and
+    through the ctypes prototype: the same status, or both refuse it with the
+    same exception.  (No request, no row: accepted calls enqueue nothing.)"""
+    fast, d, t = sm._calls(), _desc(), _Tensor()
+    calls = {
+        "int": lambda a, b: (a.sm_decode_attention(d, t, 0, t, 8, 1.0, value, t, t, 1 << 30, 0),
+                             b.sm_decode_attention(C.byref(d), 1, 0, 1, 8, 1.0, value, 1, 1, 1 << 30, 0)),
+        # (the row count of the table: no span, so it is checked only where it is negative)
+        "int64": lambda a, b: (a.sm_gather_surrogates(t, value, t, 1, t, t, 0, 64, 1, t, t, 0),
+                               b.sm_gather_surrogates(1, value, 1, 1, 1, 1, 0, 64, 1, 1, 1, 0)),
+        "size": lambda a, b: (a.sm_rules_build(t, 769, sm.RuleTableDesc(1024, 1, 1, 1), t, value, 0),
+                              b.sm_rules_build(1, 769, C.byref(sm.RuleTableDesc(1024, 1, 1, 1)), 1, value, 0)),
+        "float": lambda a, b: (a.sm_prefill_attention(d, t, 0, t, 0, t, 8, value, 0, t, 0),
+                               b.sm_prefill_attention(C.byref(d), 1, 0, 1, 0, 1, 8, value, 0, 1, 0)),
+        "stream": lambda a, b: (a.sm_kv_rollback(d, t, t, 0, value), b.sm_kv_rollback(C.byref(d), 1, 1, 0, value)),
+    }
+    got = []
+    for i in range(2):
+        class Skip:                                          # one side at a time: the other call gives nothing
+            def __getattr__(self, name):
+                return lambda *a: None
+        try:
+            got.append(calls[kind](*((fast, Skip()) if i == 0 else (Skip(), L)))[i])
+        except Exception as e:                                # noqa: BLE001
+            got.append(type(e))
+    assert got[0] == got[1], (value, got)
+
+
+def test_binding_takes_the_structures_of_its_entries():
+    fast, d, t = sm._calls(), _desc(), _Tensor()
+    assert fast.sm_kv_rollback(d, t, t, 0, 0) == sm.SM_OK
+    for wrong in (sm.RuleTableDesc(1024, 1, 1, 1), bytes(200), C.pointer(d), 7):
+        with pytest.raises(C.ArgumentError):
+            fast.sm_kv_rollback(wrong, t, t, 0, 0)
+    table = sm.RuleTableDesc(1024, 1, 1, 1)
+    assert fast.sm_rules_lookup(table, t, 0, t, 0) == sm.SM_OK
+    for wrong in (d, bytes(200)):                            # (a cache is long enough to be read as a table)
+        with pytest.raises(C.ArgumentError):
+            fast.sm_rules_lookup(wrong, t, 0, t, 0)
+    with pytest.raises(sm.SpanMergeError):
+        fast.sm_kv_rollback(d, type("Cpu", (_Tensor,), dict(is_cuda=False))(), t, 0, 0)
