@@ -23,8 +23,9 @@
 //      1. every position looks up its longest rule (independent lookups) and
 //         every block folds its maps into one;
 //      2. every block folds the maps of the blocks before it (its true entry
-//         and the spans before it) and emits its spans at their final place,
-//         and the CSR offset of every sequence that starts in it.
+//         and the spans before it; one scan gives them to all in a large
+//         batch) and emits its spans at their final place, and the CSR offset
+//         of every sequence that starts in it.
 //    The result is exactly the sequential scan's.
 //  * Decode matching ("Decoding-time Integration"): per sequence a 16-byte
 //    state (number of raw tokens since the last merge, capped at 3, and
@@ -190,45 +191,40 @@ constexpr int kMatchLane = kMatchBlock / 64;      // positions per lane of that 
 // workgroups of one block, 10 on 32 of four).
 constexpr int kEmitBlocks = 4;
 constexpr int kEmitThreads = 64 * kEmitBlocks;
+constexpr int kShareRead = 4;                     // folds a thread of the emit pass reads at a time
+// Emit workgroups up to which each forms its own entry from the folds before
+// it (524,288 positions).  That is one launch less but work that grows with
+// the square of the batch: 128 x 32,768 tokens, 50,000 rules: 194 us a call,
+// 153 with the scan (17 of them); 256 x 32,768: 547 and 293.
+constexpr int kScanEmit = 512;
 constexpr int kMatchLds = 2048;                   // sequence offsets held in LDS
-constexpr uint32_t kMapIdentity = 0xE4u;          // e -> e, two bits per entry
+constexpr uint32_t kMapIdentity = 0x03020100u;    // e -> e, a byte per entry
 
-// What a stretch of positions does to the chain: entry offset e leaves at
-// offset (map >> 2 e) & 3 past the stretch's end, after cnt[e] spans.
+// What a stretch of at most 256 positions does to the chain, a byte per entry
+// offset e: it leaves at offset map_e past the stretch's end, after cnt_e
+// spans (at most 128: a span takes two positions).
 struct ChainFold {
-  uint32_t map;
-  int cnt[4];
+  uint32_t map, cnt;
 };
 
-__device__ __forceinline__ int pick4(const int (&v)[4], uint32_t i) {
-  return i < 2 ? (i == 0 ? v[0] : v[1]) : (i == 2 ? v[2] : v[3]);
-}
-__device__ __forceinline__ uint32_t map_at(uint32_t f, uint32_t e) { return (f >> (2 * e)) & 3u; }
-// f, then g
-__device__ __forceinline__ uint32_t map_then(uint32_t f, uint32_t g) {
-  uint32_t h = 0;
-#pragma unroll
-  for (uint32_t e = 0; e < 4; ++e) h |= map_at(g, map_at(f, e)) << (2 * e);
-  return h;
-}
+__device__ __forceinline__ uint32_t byte_at(uint32_t v, uint32_t e) { return (v >> (8 * e)) & 255u; }
+// byte e of the result is v's byte f_e: one v_perm_b32, whose selectors 0 to
+// 3 pick from its second operand.  With v a map this is f, then v; with v
+// counts it is what a stretch entered through f counts.  (With two bits per
+// entry, shifts, and a sum per entry the lookup pass of 16 x 4096 tokens over
+// 50,000 rules took 22 us instead of 11, the emit pass 10 instead of 4.4.)
+__device__ __forceinline__ uint32_t through(uint32_t f, uint32_t v) { return __builtin_amdgcn_perm(v, v, f); }
 
 // the fold of a lane's kMatchLane positions, match lengths (0 = none) in
-// 4-bit fields of L
+// 4-bit fields of L: from the last position back
 __device__ __forceinline__ ChainFold lane_fold(uint32_t L) {
-  ChainFold f;
-  f.map = 0;
+  ChainFold f{0u, 0u};
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    int p = e, c = 0;
-#pragma unroll
-    for (int step = 0; step < kMatchLane; ++step)
-      if (p < kMatchLane) {
-        const int len = (int)((L >> (4 * p)) & 15u);
-        c += len ? 1 : 0;
-        p += max(len, 1);
-      }
-    f.map |= (uint32_t)(p - kMatchLane) << (2 * e);
-    f.cnt[e] = c;
+  for (int p = kMatchLane - 1; p >= 0; --p) {
+    const uint32_t len = (L >> (4 * p)) & 15u, next = p + max(len, 1u);
+    const bool out = next >= (uint32_t)kMatchLane;  // past the lane's positions: offset at most 3
+    f.map |= (out ? next - kMatchLane : byte_at(f.map, next)) << (8 * p);
+    f.cnt |= ((len ? 1u : 0u) + (out ? 0u : byte_at(f.cnt, next))) << (8 * p);
   }
   return f;
 }
@@ -240,7 +236,7 @@ __device__ __forceinline__ uint32_t wave_map_scan(uint32_t f) {
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
     const uint32_t g = __shfl_up(f, off, kWave);
-    if (lane >= off) f = map_then(g, f);
+    if (lane >= off) f = through(g, f);
   }
   return f;
 }
@@ -250,39 +246,38 @@ __device__ __forceinline__ uint32_t map_before(uint32_t incl) {
   return (threadIdx.x & 63) ? g : kMapIdentity;
 }
 
-// spans of a block's fold entered at offset e
-__device__ __forceinline__ int fold_count(uint64_t v, uint32_t e) { return (int)(v >> (8 + 8 * e)) & 255; }
-
 // match lengths of the four positions of a lane, bytes -> 4-bit fields
 __device__ __forceinline__ uint32_t pack_lens(uint32_t v) {
   return (v & 15u) | ((v >> 4) & 0xf0u) | ((v >> 8) & 0xf00u) | ((v >> 12) & 0xf000u);
 }
 
 // 1. longest rule starting at every position (0 = none) and its id; the
-// block's fold: map in bits 0-7, cnt[e] (at most 128) in bits 8 + 8 e
+// block's fold.  IN_LDS: the sequence offsets fit kMatchLds (decided by the
+// host: a pointer to one or the other would make every read a flat one).
+template <bool IN_LDS>
 __global__ __launch_bounds__(kMatchBlock) void match_len_kernel(const i32x4_t *keys, const int32_t *ids, uint32_t mask,
                                                                 const int32_t *tokens, const int32_t *seq_offsets,
                                                                 int B, int total, int8_t *mlen, int32_t *rid,
-                                                                uint64_t *folds) {
-  __shared__ int so[kMatchLds];
+                                                                ChainFold *folds) {
+  __shared__ int so[IN_LDS ? kMatchLds : 1];
   __shared__ uint32_t lens[kMatchBlock / 4];
   const int tid = threadIdx.x, t = blockIdx.x * kMatchBlock + tid;
   int x[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) x[j] = t + j < total ? tokens[t + j] : -1;
-  const bool in_lds = B + 1 <= kMatchLds;
-  if (in_lds)
+  if constexpr (IN_LDS) {
     for (int b = tid; b <= B; b += kMatchBlock) so[b] = seq_offsets[b];
-  __syncthreads();
-  const int *off = in_lds ? so : seq_offsets;
+    __syncthreads();
+  }
+  auto off = [&](int b) { return IN_LDS ? so[b] : seq_offsets[b]; };
   // the sequence holding t: the last b with seq_offsets[b] <= t
   int lo = 0, hi = B - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
-    if (off[mid] <= t) lo = mid;
+    if (off(mid) <= t) lo = mid;
     else hi = mid - 1;
   }
-  const int end = t >= off[0] ? min(off[lo + 1], total) : 0;  // (positions of no sequence match nothing)
+  const int end = t >= off(0) ? min(off(lo + 1), total) : 0;  // (positions of no sequence match nothing)
   i32x4_t cand[3];
   bool want[3];
 #pragma unroll
@@ -305,14 +300,11 @@ __global__ __launch_bounds__(kMatchBlock) void match_len_kernel(const i32x4_t *k
   __syncthreads();
   if (tid < 64) {
     const ChainFold f = lane_fold(pack_lens(lens[tid]));
-    const uint32_t incl = wave_map_scan(f.map), before = map_before(incl);
-    uint64_t word = 0;
+    const uint32_t incl = wave_map_scan(f.map);
+    uint32_t c = through(map_before(incl), f.cnt);  // this lane's spans, by the block's entry
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {  // (sums of at most 128, exact in fp32)
-      const float c = wave_sum((float)pick4(f.cnt, map_at(before, e)));
-      word |= (uint64_t)(uint32_t)c << (8 + 8 * e);
-    }
-    if (tid == 63) folds[blockIdx.x] = word | incl;
+    for (int o = 1; o < 64; o <<= 1) c += __shfl_xor(c, o, kWave);  // (no byte passes 128)
+    if (tid == 63) folds[blockIdx.x] = ChainFold{incl, c};
   }
 }
 
@@ -356,16 +348,65 @@ __device__ void match_bad_offsets(const int8_t *mlen, const int32_t *rid, const 
   if (tid == 0) seq_span_offsets[B] = o;
 }
 
+// Where the chain enters an emit workgroup's positions (offset past their
+// first) and the spans taken before.
+struct ChainEntry {
+  uint32_t entry;
+  int spans;
+};
+
+// 1b. those of all emit workgroups by one workgroup, a contiguous share per
+// thread: the shares' maps and their scan give every share's entry, walking
+// the share from there its spans, and walking it again every place in it
+constexpr int kScanThreads = 1024;
+
+__global__ __launch_bounds__(kScanThreads) void match_scan_kernel(const ChainFold *folds, int nwg, ChainEntry *at) {
+  __shared__ uint32_t wmap[kScanThreads / 64];
+  __shared__ int red[16];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int per = (nwg + kScanThreads - 1) / kScanThreads, g0 = min(tid * per, nwg), g1 = min(g0 + per, nwg);
+  uint32_t map = kMapIdentity;
+#pragma unroll 4
+  for (int k = kEmitBlocks * g0; k < kEmitBlocks * g1; ++k) map = through(map, folds[k].map);
+  const uint32_t incl = wave_map_scan(map);
+  if (lane == 63) wmap[w] = incl;
+  __syncthreads();
+  uint32_t entry = 0;
+  for (int k = 0; k < w; ++k) entry = byte_at(wmap[k], entry);
+  entry = byte_at(map_before(incl), entry);
+  int spans = 0;
+  uint32_t e = entry;
+#pragma unroll 4
+  for (int k = kEmitBlocks * g0; k < kEmitBlocks * g1; ++k) {
+    spans += (int)byte_at(folds[k].cnt, e);
+    e = byte_at(folds[k].map, e);
+  }
+  int total;
+  int before = block_inclusive_scan(spans, red, &total) - spans;
+  for (int g = g0; g < g1; ++g) {
+    at[g] = ChainEntry{entry, before};
+#pragma unroll
+    for (int k = 0; k < kEmitBlocks; ++k) {
+      const ChainFold f = folds[kEmitBlocks * g + k];
+      before += (int)byte_at(f.cnt, entry);
+      entry = byte_at(f.map, entry);
+    }
+  }
+}
+
 // 2. the spans of a workgroup's blocks (one per wave) at their final place,
-// and the CSR offsets of the sequences that start in them
+// and the CSR offsets of the sequences that start in them.  SCANNED: `at` is
+// there.
+template <bool IN_LDS, bool SCANNED>
 __global__ __launch_bounds__(kEmitThreads) void match_emit_kernel(const int8_t *mlen, const int32_t *rid,
-                                                                  const uint64_t *folds, const int32_t *seq_offsets,
+                                                                  const ChainFold *folds, const ChainEntry *at,
+                                                                  const int32_t *seq_offsets,
                                                                   int B, int total, int nwg, int32_t *span_start,
                                                                   int32_t *span_len, int32_t *span_rule,
                                                                   int32_t *seq_span_offsets, int32_t *err) {
   __shared__ uint32_t wmap[kEmitBlocks];
   __shared__ int wsum[kEmitBlocks], spans_end;
-  __shared__ int so[kMatchLds];
+  __shared__ int so[IN_LDS ? kMatchLds : 1];
   __shared__ int lane_entry[kEmitThreads], lane_before[kEmitThreads];
   __shared__ uint32_t lane_len[kEmitThreads];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -376,40 +417,49 @@ __global__ __launch_bounds__(kEmitThreads) void match_emit_kernel(const int8_t *
     if (tid == 0) seq_span_offsets[0] = 0;
     return;
   }
-  // Four positions' match lengths and ids per lane, the folds of a block
-  // before the workgroup's and of its own, and the offsets: all requested
-  // before any is used (lanes past the batch's end read its last four and
-  // mask them)
+  // Four positions' match lengths and ids per lane, the folds of its own
+  // blocks, and the offsets: all requested before any is used (lanes past the
+  // batch's end read its last four and mask them)
   const int t0 = c0 + kMatchLane * tid;
   const int tc = min(t0, max(total - 1, 0) & ~(kMatchLane - 1));
   const uint32_t lens4 = *(const uint32_t *)(mlen + tc);
   const i32x4_t id4 = *(const i32x4_t *)(rid + tc);
-  const int per = (blk0 + kEmitThreads - 1) / kEmitThreads;  // blocks before, a contiguous share per thread
-  uint64_t fold = folds[min(tid * per, blk0)];
-  uint64_t own[kEmitBlocks];
+  const int per = SCANNED ? 0 : (blk0 + kEmitThreads - 1) / kEmitThreads;  // blocks before, a contiguous share per thread
+  ChainEntry mine_at = {0u, 0};
+  if constexpr (SCANNED) mine_at = at[blockIdx.x];
+  ChainFold own[kEmitBlocks];
 #pragma unroll
   for (int k = 0; k < kEmitBlocks; ++k) own[k] = folds[blk0 + k];
   int o_lo = seq_offsets[min(tid, B)], o_hi = seq_offsets[min(tid + 1, B)];
-  ChainFold f{kMapIdentity, {0, 0, 0, 0}};
-  for (int k = tid * per; k < min((tid + 1) * per, blk0); ++k) {
-    if (k > tid * per) fold = folds[k];
-    const int cnt[4] = {fold_count(fold, 0), fold_count(fold, 1), fold_count(fold, 2), fold_count(fold, 3)};
+  uint32_t map = kMapIdentity;  // of this thread's share
+  int cnt0 = 0, cnt1 = 0, cnt2 = 0, cnt3 = 0;
+  const int share_end = min((tid + 1) * per, blk0);
+  for (int k = tid * per; k < share_end; k += kShareRead) {
+    ChainFold fold[kShareRead];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) f.cnt[e] += pick4(cnt, map_at(f.map, e));
-    f.map = map_then(f.map, (uint32_t)fold & 255u);
+    for (int j = 0; j < kShareRead; ++j) fold[j] = folds[min(k + j, blk0)];
+#pragma unroll
+    for (int j = 0; j < kShareRead; ++j)
+      if (k + j < share_end) {
+        const uint32_t c = through(map, fold[j].cnt);
+        cnt0 += byte_at(c, 0);
+        cnt1 += byte_at(c, 1);
+        cnt2 += byte_at(c, 2);
+        cnt3 += byte_at(c, 3);
+        map = through(map, fold[j].map);
+      }
   }
   // offsets in order and range?
-  const bool in_lds = B + 1 <= kMatchLds;
   bool bad = false;
   for (int b = tid; b <= B; b += kEmitThreads) {
     if (b > tid) {
       o_lo = seq_offsets[b];
       o_hi = seq_offsets[min(b + 1, B)];
     }
-    if (in_lds) so[b] = o_lo;
+    if constexpr (IN_LDS) so[b] = o_lo;
     if (b < B) bad |= !(o_lo >= 0 && o_lo <= o_hi && o_hi <= total);
   }
-  const uint32_t incl = wave_map_scan(f.map);
+  const uint32_t incl = wave_map_scan(map);
   if (lane == 63) wmap[w] = incl;
   if (__syncthreads_or(bad)) {
     if (blockIdx.x == 0)
@@ -419,32 +469,34 @@ __global__ __launch_bounds__(kEmitThreads) void match_emit_kernel(const int8_t *
   // the chain enters the batch at offset 0: the entry of this thread's
   // share, and the spans of all shares
   uint32_t entry = 0;
-  for (int k = 0; k < w; ++k) entry = map_at(wmap[k], entry);
-  int c = pick4(f.cnt, map_at(map_before(incl), entry));
+  for (int k = 0; k < w; ++k) entry = byte_at(wmap[k], entry);
+  const uint32_t se = byte_at(map_before(incl), entry);
+  int c = se < 2 ? (se == 0 ? cnt0 : cnt1) : (se == 2 ? cnt2 : cnt3);
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) c += __shfl_xor(c, off, kWave);
   if (lane == 0) wsum[w] = c;
   __syncthreads();
-  int before = 0;  // spans before, and entry of, this wave's block
-  entry = 0;
+  int before = mine_at.spans;  // spans before, and entry of, this wave's block
+  entry = mine_at.entry;
+  if constexpr (!SCANNED)
 #pragma unroll
-  for (int k = 0; k < kEmitBlocks; ++k) {
-    before += wsum[k];
-    entry = map_at(wmap[k], entry);
-  }
+    for (int k = 0; k < kEmitBlocks; ++k) {
+      before += wsum[k];
+      entry = byte_at(wmap[k], entry);
+    }
 #pragma unroll
   for (int k = 0; k < kEmitBlocks; ++k)
     if (k < w && total > 0) {  // (no tokens: no folds were written)
-      before += fold_count(own[k], entry);
-      entry = map_at((uint32_t)own[k] & 255u, entry);
+      before += byte_at(own[k].cnt, entry);
+      entry = byte_at(own[k].map, entry);
     }
   uint32_t L = pack_lens(lens4);
 #pragma unroll
   for (int j = 0; j < kMatchLane; ++j)
     if (t0 + j >= total) L &= ~(15u << (4 * j));
   const ChainFold x = lane_fold(L);
-  const int e0 = (int)map_at(map_before(wave_map_scan(x.map)), entry);
-  const int mine = pick4(x.cnt, (uint32_t)e0);
+  const uint32_t e0 = byte_at(map_before(wave_map_scan(x.map)), entry);
+  const int mine = (int)byte_at(x.cnt, e0);
   int k0 = mine;
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
@@ -453,34 +505,34 @@ __global__ __launch_bounds__(kEmitThreads) void match_emit_kernel(const int8_t *
   }
   if (tid == kEmitThreads - 1) spans_end = before + k0;  // spans up to the workgroup's end
   k0 += before - mine;
-  const int id[kMatchLane] = {id4.x, id4.y, id4.z, id4.w};
   int o = k0;
+  uint32_t next = e0;  // the chain's next position among this lane's
 #pragma unroll
-  for (int j = 0, p = e0; j < kMatchLane; ++j)
-    if (p < kMatchLane) {
-      const int len = (int)((L >> (4 * p)) & 15u);
+  for (int p = 0; p < kMatchLane; ++p)
+    if (next == (uint32_t)p) {
+      const uint32_t len = (L >> (4 * p)) & 15u;
       if (len) {
         span_start[o] = t0 + p;
-        span_len[o] = len;
-        span_rule[o] = pick4(id, (uint32_t)p);
+        span_len[o] = (int)len;
+        span_rule[o] = id4[p];
         ++o;
       }
-      p += max(len, 1);
+      next += max(len, 1u);
     }
-  lane_entry[tid] = e0;
+  lane_entry[tid] = (int)e0;
   lane_before[tid] = k0;
   lane_len[tid] = L;
   __syncthreads();
   // a sequence starting at t: the spans whose start is before t
-  const int *off = in_lds ? so : seq_offsets;
-  int b0 = 0, hi = B + 1;  // first b with off[b] >= c0
+  auto off = [&](int b) { return IN_LDS ? so[b] : seq_offsets[b]; };
+  int b0 = 0, hi = B + 1;  // first b with off(b) >= c0
   while (b0 < hi) {
     const int mid = (b0 + hi) >> 1;
-    if (off[mid] >= c0) hi = mid;
+    if (off(mid) >= c0) hi = mid;
     else b0 = mid + 1;
   }
   for (int b = b0 + tid; b <= B; b += kEmitThreads) {
-    const int t = off[b];
+    const int t = off(b);
     if (t >= c1 && !last) break;
     int k = spans_end;
     if (t < c1) {
@@ -620,18 +672,25 @@ SM_API sm_status sm_match_prompt(const sm_rule_table *t, const int32_t *token_id
   p += align256(T);
   int32_t *rid = (int32_t *)p;
   p += align256(4 * T);
-  uint64_t *folds = (uint64_t *)p;  // 8 bytes per 256 positions
+  ChainFold *folds = (ChainFold *)p;  // 8 bytes per 256 positions
   const uint32_t mask = (uint32_t)(t->capacity - 1);
   // (whole emit workgroups: blocks past the last token fold to nothing)
   const int nemit = (total_tokens + kEmitBlocks * kMatchBlock - 1) / (kEmitBlocks * kMatchBlock);
-  const bool any = B > 0 && nemit > 0;
+  const bool any = B > 0 && nemit > 0, in_lds = B + 1 <= kMatchLds;
   if (any)
-    hipLaunchKernelGGL(match_len_kernel, dim3(nemit * kEmitBlocks), dim3(kMatchBlock), 0, stream,
-                       (const i32x4_t *)t->keys, t->ids, mask, token_ids, seq_offsets, B, total_tokens, mlen, rid, folds);
+    hipLaunchKernelGGL(in_lds ? match_len_kernel<true> : match_len_kernel<false>, dim3(nemit * kEmitBlocks),
+                       dim3(kMatchBlock), 0, stream, (const i32x4_t *)t->keys, t->ids, mask, token_ids, seq_offsets, B,
+                       total_tokens, mlen, rid, folds);
+  const bool scanned = any && nemit > kScanEmit;
+  ChainEntry *at = (ChainEntry *)(folds + (size_t)nemit * kEmitBlocks);  // 8 bytes per 1024 positions
+  if (scanned)
+    hipLaunchKernelGGL(match_scan_kernel, dim3(1), dim3(kScanThreads), 0, stream, folds, nemit, at);
   // (no sequences, or no tokens: only the offsets, all zero)
-  hipLaunchKernelGGL(match_emit_kernel, dim3(any ? nemit : 1), dim3(kEmitThreads), 0, stream, mlen, rid, folds,
-                     seq_offsets, B, B > 0 ? total_tokens : 0, any ? nemit : 1, span_start, span_len, span_rule,
-                     seq_span_offsets, t->err);
+  const auto emit = scanned ? (in_lds ? match_emit_kernel<true, true> : match_emit_kernel<false, true>)
+                            : (in_lds ? match_emit_kernel<true, false> : match_emit_kernel<false, false>);
+  hipLaunchKernelGGL(emit, dim3(any ? nemit : 1), dim3(kEmitThreads), 0, stream, mlen, rid, folds, at, seq_offsets, B,
+                     B > 0 ? total_tokens : 0, any ? nemit : 1, span_start, span_len, span_rule, seq_span_offsets,
+                     t->err);
   return hipGetLastError() == hipSuccess ? SM_OK : SM_EHIP;
 }
 

@@ -27,6 +27,10 @@ MATCH = [
     (6, 40, [3] * 2500),                                    # offsets beyond the LDS copy
     (4, 20, [70000, 5]),                                    # more blocks than threads that fold them
     (2, 3, [1023]),
+    (5, 25, [524288]),                                      # as many positions as emit workgroups fold by themselves,
+    (5, 25, [524288, 1]),                                   # one more,
+    (3, 9, [300001, 0, 1, 700003, 1026, 99999]),            # more of them than threads of the scan,
+    (4, 20, [251] * 2400),                                  # and the scan with offsets beyond the LDS copy
 ]
 
 
