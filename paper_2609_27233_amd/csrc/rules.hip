@@ -184,11 +184,12 @@ __global__ void rules_lookup_kernel(const i32x4_t *keys, const int32_t *ids, uin
 
 constexpr int kMatchBlock = 256;                  // positions per block, folded by one wave
 constexpr int kMatchLane = kMatchBlock / 64;      // positions per lane of that wave
-// The lookups want many compute units (each lane's probe is a line of its own,
-// one lane per cycle and unit: 32,768 positions take 23 us on 128 workgroups
-// of 256, 38 on 32 of 1024); the emit pass is a chain of short dependent
-// accesses that cost more the more units make them at once (15 us on 128
-// workgroups of one block, 10 on 32 of four).
+// The lookups want many compute units: each lane's probe is a line of its own,
+// one lane per cycle and unit, so workgroups of 256.  The emit pass takes four
+// of their blocks per workgroup: each workgroup reads all sequence offsets and
+// its share of the folds before it.  Call in us with one, two, four and eight
+// blocks: 1 x 4096 tokens 11.8, 12.3, 12.4, 13.1; 16 x 32,768 30.7, 30.5,
+// 28.2, 28.0; 60,000 x 16 257, 160, 99, 75.
 constexpr int kEmitBlocks = 4;
 constexpr int kEmitThreads = 64 * kEmitBlocks;
 constexpr int kShareRead = 4;                     // folds a thread of the emit pass reads at a time
@@ -308,44 +309,112 @@ __global__ __launch_bounds__(kMatchBlock) void match_len_kernel(const i32x4_t *k
   }
 }
 
-// Offsets out of order or range: their sequences get no spans, the others
-// theirs, one sequence after the other by one workgroup (an error path: such
-// a batch is not one chain).  The match lengths go through LDS; one thread
-// walks them.
-__device__ void match_bad_offsets(const int8_t *mlen, const int32_t *rid, const int32_t *seq_offsets, int B, int total,
-                                  int32_t *span_start, int32_t *span_len, int32_t *span_rule,
-                                  int32_t *seq_span_offsets, int32_t *err) {
-  constexpr int kPart = 4096;
-  __shared__ int8_t part[kPart];
-  const int tid = threadIdx.x;
-  int o = 0;  // (thread 0's)
-  for (int b = 0; b < B; ++b) {
-    const int lo = seq_offsets[b], hi = seq_offsets[b + 1];
-    if (tid == 0) seq_span_offsets[b] = o;
-    if (!(lo >= 0 && lo <= hi && hi <= total)) {
-      if (tid == 0) set_err(err, SM_ERR_EINVAL);
-      continue;
-    }
-    int p = lo;
-    for (int q = lo; q < hi; q += kPart) {
-      const int n = min(kPart, hi - q);
-      __syncthreads();
-      for (int j = tid; j < n; j += kEmitThreads) part[j] = mlen[q + j];
-      __syncthreads();
-      if (tid == 0)
-        while (p < q + n) {
-          const int len = part[p - q];
-          if (len && o < total / 2) {  // (overlapping sequences must not outgrow the outputs)
-            span_start[o] = p;
-            span_len[o] = len;
-            span_rule[o] = rid[p];
-            ++o;
-          }
-          p += max(len, 1);
-        }
-    }
+// Inclusive scan over the workgroup of sums that stop at cap (at most 2^30 - 1,
+// so that no addition overflows).
+__device__ __forceinline__ int capped_scan(int v, int cap, int *red) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  v = min(v, cap);
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int u = __shfl_up(v, off, kWave);
+    if (lane >= off) v = min(v + u, cap);
   }
-  if (tid == 0) seq_span_offsets[B] = o;
+  __syncthreads();
+  if (lane == 63) red[w] = v;
+  __syncthreads();
+  int before = 0;
+  for (int k = 0; k < w; ++k) before = min(before + red[k], cap);
+  return min(before + v, cap);
+}
+
+// Offsets out of order or range (an error path: such a batch is not one
+// chain): their sequences get no spans, the others theirs.  Every workgroup
+// counts the spans of all sequences, a thread per sequence, whole blocks
+// through their folds; so each knows the places of those it writes, every
+// gridDim.x-th.  Overlapping sequences may hold more spans than the outputs
+// (total / 2): those past the end are dropped.
+__device__ void match_bad_offsets(const int8_t *mlen, const int32_t *rid, const ChainFold *folds,
+                                  const int32_t *seq_offsets, int B, int total, int32_t *span_start, int32_t *span_len,
+                                  int32_t *span_rule, int32_t *seq_span_offsets, int32_t *err) {
+  __shared__ uint32_t wmap[kEmitBlocks];
+  __shared__ int red[16], sums[kEmitThreads];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int cap = total / 2, grid = (int)gridDim.x;
+  int base = 0;
+  for (int b0 = 0; b0 < B; b0 += kEmitThreads) {
+    const int b = b0 + tid;
+    int lo = 0, hi = 0;
+    if (b < B) {
+      lo = seq_offsets[b];
+      hi = seq_offsets[b + 1];
+      if (!(lo >= 0 && lo <= hi && hi <= total)) {
+        if (blockIdx.x == 0) set_err(err, SM_ERR_EINVAL);
+        lo = hi = 0;
+      }
+    }
+    int n = 0;
+    for (int p = lo; p < hi;) {
+      const uint32_t e = p & (kMatchBlock - 1);
+      if (e < 4 && (p | (kMatchBlock - 1)) < hi) {  // the block to its end, entered at e
+        const ChainFold f = folds[p / kMatchBlock];
+        n += (int)byte_at(f.cnt, e);
+        p = (p | (kMatchBlock - 1)) + 1 + (int)byte_at(f.map, e);
+      } else {
+        const int len = mlen[p];
+        n += len ? 1 : 0;
+        p += max(len, 1);
+      }
+    }
+    const int end = min(base + capped_scan(n, cap, red), cap);
+    sums[tid] = end;
+    if (blockIdx.x == 0 && b < B) seq_span_offsets[b + 1] = end;
+    __syncthreads();
+    for (int s = b0 + (((int)blockIdx.x - b0) % grid + grid) % grid; s < min(b0 + kEmitThreads, B); s += grid) {
+      const int slo = seq_offsets[s], shi = seq_offsets[s + 1];
+      if (!(slo >= 0 && slo <= shi && shi <= total)) continue;
+      int o = s > b0 ? sums[s - b0 - 1] : base;
+      uint32_t entry = 0;
+      for (int q = slo; q < shi; q += kMatchLane * kEmitThreads) {
+        const int t0 = q + kMatchLane * tid;
+        uint32_t L = 0;
+#pragma unroll
+        for (int j = 0; j < kMatchLane; ++j)
+          if (t0 + j < shi) L |= (uint32_t)mlen[t0 + j] << (4 * j);
+        const ChainFold f = lane_fold(L);
+        const uint32_t incl = wave_map_scan(f.map);
+        if (lane == 63) wmap[w] = incl;
+        __syncthreads();
+        uint32_t e = entry;
+#pragma unroll
+        for (int k = 0; k < kEmitBlocks; ++k) {
+          if (k < w) e = byte_at(wmap[k], e);
+          entry = byte_at(wmap[k], entry);
+        }
+        e = byte_at(map_before(incl), e);
+        const int mine = (int)byte_at(f.cnt, e);
+        int all;
+        int at = o + block_inclusive_scan(mine, red, &all) - mine;  // (its barriers: wmap is read)
+#pragma unroll
+        for (int p = 0; p < kMatchLane; ++p)
+          if (e == (uint32_t)p) {
+            const uint32_t len = (L >> (4 * p)) & 15u;
+            if (len) {
+              if (at < cap) {
+                span_start[at] = t0 + p;
+                span_len[at] = (int)len;
+                span_rule[at] = rid[t0 + p];
+              }
+              ++at;
+            }
+            e += max(len, 1u);
+          }
+        o += all;
+      }
+    }
+    base = sums[kEmitThreads - 1];
+    __syncthreads();
+  }
+  if (blockIdx.x == 0 && tid == 0) seq_span_offsets[0] = 0;
 }
 
 // Where the chain enters an emit workgroup's positions (offset past their
@@ -462,8 +531,7 @@ __global__ __launch_bounds__(kEmitThreads) void match_emit_kernel(const int8_t *
   const uint32_t incl = wave_map_scan(map);
   if (lane == 63) wmap[w] = incl;
   if (__syncthreads_or(bad)) {
-    if (blockIdx.x == 0)
-      match_bad_offsets(mlen, rid, seq_offsets, B, total, span_start, span_len, span_rule, seq_span_offsets, err);
+    match_bad_offsets(mlen, rid, folds, seq_offsets, B, total, span_start, span_len, span_rule, seq_span_offsets, err);
     return;
   }
   // the chain enters the batch at offset 0: the entry of this thread's

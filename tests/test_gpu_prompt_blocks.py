@@ -81,6 +81,53 @@ def test_match_prompt_bad_offsets_keep_the_good_sequences(orc):
         np.testing.assert_array_equal(got.cpu().numpy()[:len(s0)], ref)
 
 
+@pytest.mark.parametrize("B,T,tail", [(1, 700, [9]), (40, 3000, [1]), (700, 300, [1, 5]), (2100, 40, [3]),
+                                      (3, 300000, [1])])
+def test_match_prompt_bad_offsets_many_sequences(orc, B, T, tail):
+    """Sequences past the end of the tokens after B good ones of up to T
+    positions: more sequences than workgroups and fewer, than threads, than
+    offsets in the LDS copy, and a batch whose entries are scanned."""
+    rng = np.random.RandomState(B)
+    rules = _rules(rng, 30, 5)
+    lens = rng.randint(0, T + 1, B)
+    good = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    N = int(good[-1])
+    toks = rng.randint(0, 5, N).astype(np.int32)
+    st, s0, ln, ru, sso = orc.OracleRules(rules).match_prompt(toks, good)
+    t = sm.RuleTable(sm.RuleTable.capacity_for(30))
+    sm.rules_build(t, i32(rules))
+    offs = np.concatenate([good, N + np.cumsum(tail)])
+    out = [torch.full((N // 2 + 1,), -7, dtype=torch.int32, device=dev()) for _ in range(3)]
+    gs = torch.full((len(offs),), -7, dtype=torch.int32, device=dev())
+    ws = torch.empty(sm.match_prompt_workspace_bytes(len(offs) - 1, N), dtype=torch.uint8, device=dev())
+    say("match with sequences out of range", B, T, "spans", len(s0))
+    sm.match_prompt(t, i32(toks), i32(offs), *out, gs, ws)
+    torch.cuda.synchronize()
+    assert t.error_bits() == sm.ERR_EINVAL
+    assert gs.cpu().tolist() == sso.tolist() + [len(s0)] * len(tail)
+    for got, ref in zip(out, (s0, ln, ru)):
+        np.testing.assert_array_equal(got.cpu().numpy()[:len(s0)], ref)
+        assert (got.cpu().numpy()[len(s0):] == -7).all()
+
+
+def test_match_prompt_overlapping_sequences_stay_in_the_outputs():
+    """Offsets that go back: two good sequences over the same positions hold
+    more spans than the outputs take; those past the end are dropped."""
+    t = sm.RuleTable(16)
+    sm.rules_build(t, i32([[0, 0, -1, -1]]))
+    out = [torch.full((3001,), -7, dtype=torch.int32, device=dev()) for _ in range(3)]
+    gs = torch.full((4,), -7, dtype=torch.int32, device=dev())
+    ws = torch.empty(sm.match_prompt_workspace_bytes(3, 6000), dtype=torch.uint8, device=dev())
+    say("match with overlapping sequences")
+    sm.match_prompt(t, i32(np.zeros(6000)), i32([0, 4000, 1000, 6000]), *out, gs, ws)
+    torch.cuda.synchronize()
+    assert t.error_bits() == sm.ERR_EINVAL
+    assert gs.cpu().tolist() == [0, 2000, 2000, 3000]
+    start = out[0].cpu().numpy()
+    np.testing.assert_array_equal(start[:3000], np.concatenate([np.arange(0, 4000, 2), np.arange(1000, 3000, 2)]))
+    assert all(int(v[3000]) == -7 for v in out) and (out[1][:3000] == 2).all() and (out[2][:3000] == 0).all()
+
+
 PACK = [
     # lengths, longest span
     ([1023, 1, 1024, 1025, 0, 2047, 2, 0], 8),
