@@ -509,45 +509,52 @@ struct PackArgs {
 // removed before its piece, before the sequence that the piece begins in and
 // in all, and marks the spans that fall into its piece in LDS.  The span ->
 // sequence search and the bounds it checks read LDS copies of the offsets
-// when they fit (kPackSsoLds entries), else global memory; each thread loads
-// its spans kPackBatch at a time, so that their loads share one round trip.
-// PER is 1 up to 256 workgroups (each repeats the pass over the spans), then 4.
+// when they fit (kPackSsoLds entries; IN_LDS), else global memory; each thread
+// loads its spans kPackBatch at a time, so that their loads share one round
+// trip, and searches again only when a span is past the sequence of the one
+// before (a search per span: 586 us, not 422, for 128 x 32,768 tokens).
+// PER is 1 up to kPackWgs workgroups, then 4.  Each repeats the pass over the
+// spans, so there are no more of them: a larger batch (MANY) gives each
+// several consecutive pieces, and from its second piece on a workgroup reads
+// the spans that start there only.  Index pass in us with a workgroup per
+// piece, and so: 64 x 32,768 tokens, 262,144 spans: 418, 191; 128 x 32,768:
+// 1652, 422 (a workgroup per sequence took 258 and 557).
+constexpr int kPackWgs = 256;
 constexpr int kPackSsoLds = 4096;
 
-// last b in [0, n) with v[b] <= x (v[0] <= x)
-__device__ __forceinline__ int last_le(const int *v, int n, int x) {
+// last b in [0, n) with at(b) <= x (at(0) <= x)
+template <class F>
+__device__ __forceinline__ int last_le(F at, int n, int x) {
   int lo = 0, hi = n - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
-    if (v[mid] <= x) lo = mid;
+    if (at(mid) <= x) lo = mid;
     else hi = mid - 1;
   }
   return lo;
 }
 
-template <int PER>
-__global__ __launch_bounds__(kPackThreads) void pack_index_kernel(PackArgs a) {
+template <int PER, bool MANY, bool IN_LDS>
+__global__ __launch_bounds__(kPackThreads) void pack_index_kernel(PackArgs a, int pieces) {
   constexpr int CHUNK = kPackThreads * PER;
   __shared__ int src[CHUNK];         // packed source of each token, then its packed row
-  __shared__ int sso[kPackSsoLds], so[kPackSsoLds];
+  __shared__ int sso[IN_LDS ? kPackSsoLds : 1], so[IN_LDS ? kPackSsoLds : 1];
   __shared__ int red[16];
-  __shared__ int flag, s_err, sums[3];
+  __shared__ int flag, s_err, sums[4];
   const int t = threadIdx.x;
-  const int c0 = blockIdx.x * CHUNK, cn = min(CHUNK, a.total_tokens - c0);  // (cn = 0: a batch of no tokens)
-  const bool last = blockIdx.x == gridDim.x - 1;
+  int c0 = blockIdx.x * CHUNK * (MANY ? pieces : 1), cn = min(CHUNK, a.total_tokens - c0);  // (cn = 0: no tokens at all)
   if (t == 0) {
     s_err = *a.err;
     flag = a.seq_offsets[0] != 0 || a.seq_offsets[a.B] != a.total_tokens || a.seq_span_offsets[0] != 0 ||
            a.seq_span_offsets[a.B] != a.num_spans;
   }
-  if (t < 3) sums[t] = 0;
+  if (t < 4) sums[t] = 0;
 #pragma unroll
   for (int u = 0; u < PER; ++u) src[t + u * kPackThreads] = c0 + t + u * kPackThreads;
-  const bool in_lds = a.B + 1 <= kPackSsoLds;
   bool bad = false;
   for (int b = t; b <= a.B; b += kPackThreads) {
     const int s1 = a.seq_span_offsets[b], o1 = a.seq_offsets[b];
-    if (in_lds) {
+    if constexpr (IN_LDS) {
       sso[b] = s1;
       so[b] = o1;
     }
@@ -561,11 +568,12 @@ __global__ __launch_bounds__(kPackThreads) void pack_index_kernel(PackArgs a) {
     if (blockIdx.x == 0 && t == 0) set_err(a.err, SM_ERR_EINVAL);
     return;
   }
-  const int *sso_src = in_lds ? sso : a.seq_span_offsets;
-  const int *so_src = in_lds ? so : a.seq_offsets;
-  const int q0 = so_src[last_le(so_src, a.B, c0)];  // start of the sequence that holds c0
-  int rem_q0 = 0, rem_c0 = 0, rem_all = 0;          // (this thread's spans)
+  auto sso_at = [&](int b) { return IN_LDS ? sso[b] : a.seq_span_offsets[b]; };
+  auto so_at = [&](int b) { return IN_LDS ? so[b] : a.seq_offsets[b]; };
+  const int q0 = so_at(last_le(so_at, a.B, c0));  // start of the sequence that holds c0
+  int rem_q0 = 0, rem_c0 = 0, rem_all = 0, before_end = 0;  // (this thread's spans)
   constexpr int kPackBatch = 4;
+  int b = last_le(sso_at, a.B, t);  // sequence b with sso[b] <= s < sso[b + 1]
   for (int s0 = t; s0 < a.num_spans; s0 += kPackBatch * kPackThreads) {
     int st[kPackBatch], ln[kPackBatch], pe[kPackBatch];
 #pragma unroll
@@ -580,9 +588,9 @@ __global__ __launch_bounds__(kPackThreads) void pack_index_kernel(PackArgs a) {
     for (int k = 0; k < kPackBatch; ++k) {
       const int s = s0 + k * kPackThreads;
       if (s >= a.num_spans) break;
-      const int b = last_le(sso_src, a.B, s);  // sequence b with sso[b] <= s < sso[b + 1]
-      bool ok = ln[k] >= 1 && st[k] >= so_src[b] && (int64_t)st[k] + ln[k] <= so_src[b + 1];
-      if (ok && s > sso_src[b]) ok = st[k] >= pe[k];
+      if (s >= sso_at(b + 1)) b = last_le(sso_at, a.B, s);
+      bool ok = ln[k] >= 1 && st[k] >= so_at(b) && (int64_t)st[k] + ln[k] <= so_at(b + 1);
+      if (ok && s > sso_at(b)) ok = st[k] >= pe[k];
       if (!ok) {
         bad = true;
         continue;
@@ -591,6 +599,7 @@ __global__ __launch_bounds__(kPackThreads) void pack_index_kernel(PackArgs a) {
       if (st[k] < q0) rem_q0 += ln[k] - 1;
       if (st[k] < c0) rem_c0 += min(ln[k] - 1, c0 - st[k]);
       const int end = st[k] + ln[k] - 1;  // its last token keeps the surrogate
+      if (MANY) before_end += st[k] < c0 + cn;
       if (end >= c0 && st[k] < c0 + cn) {
         for (int u = max(st[k], c0); u < min(end, c0 + cn); ++u) src[u - c0] = kRemoved;
         if (end < c0 + cn) src[end - c0] = -1 - s;
@@ -604,47 +613,83 @@ __global__ __launch_bounds__(kPackThreads) void pack_index_kernel(PackArgs a) {
     rem_q0 += __shfl_xor(rem_q0, off, kWave);
     rem_c0 += __shfl_xor(rem_c0, off, kWave);
     rem_all += __shfl_xor(rem_all, off, kWave);
+    if (MANY) before_end += __shfl_xor(before_end, off, kWave);
   }
   if ((t & 63) == 0) {
     atomicAdd(&sums[0], rem_q0);
     atomicAdd(&sums[1], rem_c0);
     atomicAdd(&sums[2], rem_all);
+    if (MANY) atomicAdd(&sums[3], before_end);
   }
   __syncthreads();
   if (flag) {
     if (blockIdx.x == 0 && t == 0) set_err(a.err, SM_ERR_EINVAL);
     return;
   }
-  // packed rows of the piece's tokens: each thread owns PER consecutive ones
-  int v[PER], cnt = 0;
+  int removed = sums[1], row_q0 = q0 - sums[0];  // positions removed before c0; the row of the token at q0
+  int next_span = sums[3];                      // the first span that starts past the piece
+  for (int piece = 1;; ++piece) {
+    // packed rows of the piece's tokens: each thread owns PER consecutive ones
+    int v[PER], cnt = 0;
 #pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    v[u] = PER * t + u < cn ? src[PER * t + u] : kRemoved;
-    cnt += v[u] != kRemoved;
-  }
-  int tot;
-  int g = c0 - sums[1] + block_inclusive_scan(cnt, red, &tot) - cnt;  // (its barriers: every src entry is read)
-#pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    if (PER * t + u < cn) {
-      src[PER * t + u] = g;
-      if (v[u] != kRemoved) a.packed_src[g++] = v[u];
+    for (int u = 0; u < PER; ++u) {
+      v[u] = PER * t + u < cn ? src[PER * t + u] : kRemoved;
+      cnt += v[u] != kRemoved;
     }
-  }
-  __syncthreads();
-  const int row_q0 = q0 - sums[0];
+    int tot;
+    int g = c0 - removed + block_inclusive_scan(cnt, red, &tot) - cnt;  // (its barriers: every src entry is read)
 #pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const int e = t + u * kPackThreads;
-    if (e < cn) {
-      const int first = so_src[last_le(so_src, a.B, c0 + e)];  // its sequence's first token
-      a.pi[c0 + e] = src[e] - (first >= c0 ? src[first - c0] : row_q0);
+    for (int u = 0; u < PER; ++u) {
+      if (PER * t + u < cn) {
+        src[PER * t + u] = g;
+        if (v[u] != kRemoved) a.packed_src[g++] = v[u];
+      }
     }
-  }
-  for (int b = t; b <= a.B; b += kPackThreads) {
-    const int o = so_src[b];
-    if (o >= c0 && o < c0 + cn) a.packed_offsets[b] = src[o - c0];
-    else if (last && o == a.total_tokens) a.packed_offsets[b] = o - sums[2];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int e = t + u * kPackThreads;
+      if (e < cn) {
+        const int first = so_at(last_le(so_at, a.B, c0 + e));  // its sequence's first token
+        a.pi[c0 + e] = src[e] - (first >= c0 ? src[first - c0] : row_q0);
+      }
+    }
+    const bool last = c0 + cn >= a.total_tokens;
+    for (int b = t; b <= a.B; b += kPackThreads) {
+      const int o = so_at(b);
+      if (o >= c0 && o < c0 + cn) a.packed_offsets[b] = src[o - c0];
+      else if (last && o == a.total_tokens) a.packed_offsets[b] = o - sums[2];
+    }
+    if (!MANY || last || piece == pieces) return;
+    // The next piece: positions removed before it, the row of the first token
+    // of the sequence that it begins in, and the spans in it (the list is
+    // valid, so its starts ascend), from the one that may reach into it.
+    removed += cn - tot;
+    const int next0 = c0 + CHUNK, first = so_at(last_le(so_at, a.B, next0));
+    if (first >= c0 && first < next0) row_q0 = src[first - c0];
+    __syncthreads();  // src is read
+    c0 = next0;
+    cn = min(CHUNK, a.total_tokens - c0);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) src[t + u * kPackThreads] = c0 + t + u * kPackThreads;
+    __syncthreads();
+    for (int s0 = max(next_span - 1, 0), got = kPackBatch * kPackThreads; got == kPackBatch * kPackThreads;
+         s0 += kPackBatch * kPackThreads) {
+      int mine = 0;
+#pragma unroll
+      for (int k = 0; k < kPackBatch; ++k) {
+        const int s = s0 + t + k * kPackThreads;
+        if (s >= a.num_spans) continue;
+        const int st = a.span_start[s], end = st + a.span_len[s] - 1;
+        mine += st < c0 + cn;
+        if (end >= c0 && st < c0 + cn) {
+          for (int u = max(st, c0); u < min(end, c0 + cn); ++u) src[u - c0] = kRemoved;
+          if (end < c0 + cn) src[end - c0] = -1 - s;
+        }
+      }
+      block_inclusive_scan(mine, red, &got);  // (its barriers: the marks are there)
+      next_span = s0 + got;
+    }
   }
 }
 
@@ -805,12 +850,17 @@ SM_API sm_status sm_pack_spans(int B, const int32_t *seq_offsets, int total_toke
   a.d = d;
   a.packed = packed;
   a.err = err;
-  const int64_t pieces = ((int64_t)total_tokens + kPackThreads - 1) / kPackThreads;
-  if (pieces <= 256)
-    hipLaunchKernelGGL(pack_index_kernel<1>, dim3(pieces > 0 ? (unsigned)pieces : 1), dim3(kPackThreads), 0, stream, a);
-  else
-    hipLaunchKernelGGL(pack_index_kernel<kPackMaxPer>, dim3((unsigned)((pieces + kPackMaxPer - 1) / kPackMaxPer)),
-                       dim3(kPackThreads), 0, stream, a);
+  const int64_t n1 = ((int64_t)total_tokens + kPackThreads - 1) / kPackThreads;  // pieces of PER = 1
+  const int64_t n4 = (n1 + kPackMaxPer - 1) / kPackMaxPer;
+  const int many = (int)((n4 + kPackWgs - 1) / kPackWgs);
+  const bool in_lds = B + 1 <= kPackSsoLds;
+  const int64_t grid = n1 <= kPackWgs ? (n1 > 0 ? n1 : 1) : (n4 + many - 1) / many;
+  const auto index = n1 <= kPackWgs ? (in_lds ? pack_index_kernel<1, false, true> : pack_index_kernel<1, false, false>)
+                     : many <= 1    ? (in_lds ? pack_index_kernel<kPackMaxPer, false, true>
+                                              : pack_index_kernel<kPackMaxPer, false, false>)
+                                    : (in_lds ? pack_index_kernel<kPackMaxPer, true, true>
+                                              : pack_index_kernel<kPackMaxPer, true, false>);
+  hipLaunchKernelGGL(index, dim3((unsigned)grid), dim3(kPackThreads), 0, stream, a, many);
   if (hipGetLastError() != hipSuccess) return SM_EHIP;
   if (packed && total_tokens > 0) {
     // one wave per packed row, striding: up to 4 waves per compute unit's

@@ -136,6 +136,11 @@ PACK = [
     ([5000, 3000], 2600),                                   # spans longer than a piece
     ([260000, 5000], 6),                                    # more than 256 pieces of 1024
     ([0, 0], 4),
+    ([600000, 3, 0, 447000, 1573], 30),                     # as many pieces of 4096 as workgroups,
+    ([600000, 3, 0, 447000, 1574], 30),                     # one more: two pieces each,
+    ([3000, 900001, 1, 0, 1500000, 4095, 4097, 1] + [777] * 500, 60),   # three, sequences that begin in any of them,
+    ([1200000, 1000000], 30000),                            # spans over several pieces,
+    ([20] * 60000, 4),                                     # and offsets beyond the LDS copies
 ]
 
 
