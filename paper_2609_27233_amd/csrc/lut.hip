@@ -115,10 +115,13 @@ __global__ __launch_bounds__(kDedupThreads) void dedupe_count_kernel(const int32
 }
 
 // Exclusive scan of the block totals by one workgroup, for batches of more
-// than kDedupBlocks blocks; up to there (a million spans) every workgroup of
+// than kDedupBlocks blocks; up to there (131,072 spans) every workgroup of
 // the last pass forms the prefix in its own LDS, one launch less (of seven
-// launches for one 32,768-token document, 26 us, four are left, 19).
-constexpr int kDedupBlocks = 4096;
+// launches for one 32,768-token document, 26 us, four are left, 19), but work
+// that grows with the square of the spans.  Calls in us, with the scan and
+// without: 131,072 spans 29.8 and 29.1; 262,144 41.3 and 42.1; 1,048,576 101
+// and 152 (seven launches: 35, 47 and 110).
+constexpr int kDedupBlocks = 512;
 
 __global__ __launch_bounds__(kDedupThreads) void dedupe_blocks_kernel(int nblk, const int32_t *flag, int32_t *blk_u,
                                                                       int32_t *blk_r, int32_t *uniq_span_offsets,

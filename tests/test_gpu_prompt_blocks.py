@@ -178,9 +178,10 @@ def test_pack_piece_edges(orc, case):
     np.testing.assert_array_equal(src.cpu().numpy()[:po[-1].item()], res["packed_src"])
 
 
-@pytest.mark.parametrize("S,rules", [(1, 3), (256, 4), (257, 1), (5000, 900), (1100000, 700000)])
+@pytest.mark.parametrize("S,rules", [(1, 3), (256, 4), (257, 1), (5000, 900), (131072, 60000), (131073, 60000),
+                                     (1100000, 700000)])
 def test_dedupe_block_edges(orc, S, rules):
-    """Blocks of 256 spans; the last case has more blocks than the LDS prefix."""
+    """Blocks of 256 spans; the last two cases have more blocks than the LDS prefix."""
     rng = np.random.RandomState(S)
     rule = rng.randint(0, rules, S).astype(np.int32)
     n_of = rng.randint(2, 5, rules)
