@@ -15,6 +15,7 @@
 //   4. LN_o   z_s = LN_o(Y_s)
 // The fp32 dtype runs the same four steps on v_mfma_f32_32x32x2_f32.
 #include "common.hpp"
+#include "gemm_plan.hpp"
 
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
@@ -385,12 +386,11 @@ static hipError_t launch_ksplit_shape(const T *A, const int32_t *gather, int64_t
 template <typename T, typename OutT>
 static hipError_t launch_ksplit(int shape, const T *A, const int32_t *gather, int64_t a_rows, const T *B,
                                 const T *bias, OutT *C, int M, int N, int K, int32_t *err, hipStream_t stream) {
-#define SM_KT_CASE(I, BM, BN, S) \
-  case I:                        \
-    return launch_ksplit_shape<T, OutT, BM, BN, S>(A, gather, a_rows, B, bias, C, M, N, K, err, stream);
+#define SM_KT_CASE(I, S) \
+  case I:                 \
+    return launch_ksplit_shape<T, OutT, kGemmShapes[I].bm, kGemmShapes[I].bn, S>(A, gather, a_rows, B, bias, C, M, N, K, err, stream);
   switch (shape) {
-    SM_KT_CASE(0, 32, 32, 8) SM_KT_CASE(1, 32, 64, 8) SM_KT_CASE(2, 64, 64, 8) SM_KT_CASE(3, 96, 64, 7)
-    SM_KT_CASE(4, 128, 64, 6) SM_KT_CASE(5, 160, 64, 5) SM_KT_CASE(6, 192, 64, 4)
+    SM_KT_CASE(0, 8) SM_KT_CASE(1, 8) SM_KT_CASE(2, 8) SM_KT_CASE(3, 7) SM_KT_CASE(4, 6) SM_KT_CASE(5, 5) SM_KT_CASE(6, 4)
   }
 #undef SM_KT_CASE
   return hipErrorInvalidValue;
@@ -856,6 +856,93 @@ static hipError_t launch_gemm256(const uint16_t *A, const int32_t *gather, int64
 }
 
 // ---------------------------------------------------------------------------
+// Skinny bf16 GEMM for M <= 64 rows (a decode-time merge of a few spans):
+// C[M][N] = GELU(A[M][K] W[N][K]^T + bias).  One workgroup per 16 output
+// columns (N / 16 workgroups, enough to keep every compute unit streaming
+// its slice of W), the four waves split K and reduce through LDS.  Operand
+// fragments are loaded straight from memory in MFMA layout, U k-steps of 32
+// at a time so that U * (1 + m-tiles) 16-byte loads per lane are in flight.
+// Its loads are plain ones: few rows whose operands are not 16-byte aligned
+// take it (16 rows, K = N = 4096: 31 us against 86 with 128x128 tiles; 64
+// rows: 75 against 89).
+
+template <typename OutT, int U>
+__global__ __launch_bounds__(256) void gemm_skinny_bf16_gelu(const uint16_t *__restrict__ A,
+                                                             const int32_t *__restrict__ gather, int64_t a_rows,
+                                                             const uint16_t *__restrict__ W,
+                                                             const uint16_t *__restrict__ bias,
+                                                             OutT *__restrict__ C, int M, int N, int K,
+                                                             int32_t *err) {
+  __shared__ float red[4][kSkinnyMaxM][17];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int r = lane & 15, q4 = lane >> 4;
+  const int n0 = blockIdx.x * 16;
+  const int mt = (M + 15) >> 4;  // m-tiles (<= 4)
+  const uint16_t *arow[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int m = i * 16 + r;
+    int64_t idx = 0;
+    if (m < M) {
+      idx = gather ? gather[m] : m;
+      if (idx < 0 || idx >= a_rows) {
+        set_err(err, SM_ERR_EINVAL);
+        idx = 0;
+      }
+    }
+    arow[i] = A + idx * K + 8 * q4;
+  }
+  const uint16_t *wrow = W + (int64_t)(n0 + r) * K + 8 * q4;
+  const int kw = K >> 2, kbeg = w * kw;
+  f32x4_t acc[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int k = kbeg; k < kbeg + kw; k += 32 * U) {
+    u32x4_t bw[U], fa[U][4];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      bw[u] = *(const u32x4_t *)(wrow + k + 32 * u);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (i < mt) fa[u][i] = *(const u32x4_t *)(arow[i] + k + 32 * u);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (i < mt)
+          acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(fa[u][i]), as_bf16x8(bw[u]), acc[i], 0, 0, 0);
+  }
+  // lane (r, q4) of m-tile i holds rows 16 i + 4 q4 + e, column r
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red[w][i * 16 + 4 * q4 + e][r] = acc[i][e];
+  __syncthreads();
+  for (int o = tid; o < mt * 16 * 16; o += 256) {
+    const int m = o >> 4, n = o & 15;
+    if (m >= M) continue;
+    const float v = red[0][m][n] + red[1][m][n] + red[2][m][n] + red[3][m][n];
+    C[(int64_t)m * N + n0 + n] = Elem<OutT>::to_store(gelu_erf(v + bf16_to_f32(bias[n0 + n])));
+  }
+}
+
+template <typename OutT>
+static void launch_skinny(const uint16_t *A, const int32_t *gather, int64_t a_rows, const uint16_t *W,
+                          const uint16_t *bias, OutT *C, int M, int N, int K, int32_t *err, hipStream_t stream) {
+  const dim3 grid(N / 16), block(256);
+  if ((K / 4) % (32 * 8) == 0)
+    hipLaunchKernelGGL((gemm_skinny_bf16_gelu<OutT, 8>), grid, block, 0, stream, A, gather, a_rows, W, bias, C, M,
+                       N, K, err);
+  else if ((K / 4) % (32 * 4) == 0)
+    hipLaunchKernelGGL((gemm_skinny_bf16_gelu<OutT, 4>), grid, block, 0, stream, A, gather, a_rows, W, bias, C, M,
+                       N, K, err);
+  else
+    hipLaunchKernelGGL((gemm_skinny_bf16_gelu<OutT, 2>), grid, block, 0, stream, A, gather, a_rows, W, bias, C, M,
+                       N, K, err);
+}
+
+// ---------------------------------------------------------------------------
 // fp32 GEMM on the vector ALU (64x64 tile, 4x4 outputs per thread), same
 // contract as the bf16 one, for operands that are not 16-byte aligned.
 
@@ -921,85 +1008,25 @@ __global__ __launch_bounds__(256) void gemm_f32_nt_gelu(const float *__restrict_
 }
 
 // ---------------------------------------------------------------------------
-// Which GEMM a call takes.  Times in microseconds at K = 64 nk (bf16), fitted
-// to sweeps over M = 1..30,000 at N = K = 512..8192 on the box (each within
-// about 10%): a grid of t tiles runs as waves of one workgroup per compute
-// unit; a k-tile of a wave takes a time that grows with the bytes each
-// workgroup loads for it (BM + BN rows) and, for the large tiles, with the
-// part f of the compute units that are busy (the matrix clock falls); each
-// wave adds its prologue and epilogue.  Measured at K = N = 4096:
-//   M = 64      32x32 9.6    64x64 16.7
-//   M = 609     160x64 31    128x64 47    256x128 58    256x256 86
-//   M = 1700    160x64 95    256x128 67   256x256 94
-//   M = 2400    256x128 119  256x256 95
-//   M = 4200    256x256 195, of which the 17th row of tiles alone about 78
-// The last line is why a call may be cut in two by rows: whole waves of the
-// large tile, and the rows that remain by whatever is fastest for them.
+// The GEMM of a call, by the plan of gemm_plan.hpp.
 
-struct KtShape {
-  int bm, bn;
-};
-constexpr KtShape kKtShapes[] = {{32, 32}, {32, 64}, {64, 64}, {96, 64}, {128, 64}, {160, 64}, {192, 64}};
-constexpr int kKtShapeCount = sizeof(kKtShapes) / sizeof(kKtShapes[0]);
-constexpr int kGemmWide = kKtShapeCount, kGemm256 = kKtShapeCount + 1, kGemmKinds = kKtShapeCount + 2;
-constexpr int kGemmCus = 256;
-
-static float gemm_cost(int kind, int M, int N, int K, bool f32) {
-  const int bm = kind == kGemm256 ? kLM : kind == kGemmWide ? kWM : kKtShapes[kind].bm;
-  const int bn = kind == kGemm256 ? kLN : kind == kGemmWide ? kWN : kKtShapes[kind].bn;
-  if (N % bn || (f32 && kind >= kKtShapeCount)) return 3.0e38f;
-  const int64_t tiles = (int64_t)((M + bm - 1) / bm) * (N / bn);
-  const int64_t full = tiles / kGemmCus;
-  const float f = (float)(tiles % kGemmCus) / kGemmCus, nk = (float)(K / (f32 ? 32 : 64));
-  if (kind == kGemm256) return 7.f + full * (nk * 1.53f + 14.f) + (f > 0.f ? nk * (0.88f + 0.65f * f) + 14.f : 0.f);
-  if (kind == kGemmWide) return 6.f + full * (nk * 0.88f + 8.f) + (f > 0.f ? nk * (0.55f + 0.33f * f) + 8.f : 0.f);
-  const float kt = f32 ? 0.04f + 0.16f * (bm / 32) * (bn / 32) : 0.0021f * (bm + bn) - 0.04f;
-  return 3.f + (full + (f > 0.f ? 1 : 0)) * (nk * kt + 0.8f * (bm / 32));
-}
-
-struct GemmPlan {
-  int kind, rows;        // rows [0, rows) with `kind`
-  int kind2;             // and the rest with kind2 (rows < M)
-};
-
-static GemmPlan plan_gemm(int M, int N, int K, bool f32) {
-  auto best = [&](int m, float *cost) {
-    int b = 0;
-    for (int k = 0; k < kGemmKinds; ++k) {
-      const float c = gemm_cost(k, m, N, K, f32);
-      if (k == 0 || c < *cost) {
-        *cost = c;
-        b = k;
-      }
-    }
-    return b;
-  };
-  GemmPlan p{0, M, 0};
-  float cost;
-  p.kind = best(M, &cost);
-  if (f32) return p;
-  for (int kind = kGemmWide; kind <= kGemm256; ++kind) {
-    const int bm = kind == kGemm256 ? kLM : kWM, tiles_n = N / (kind == kGemm256 ? kLN : kWN);
-    const int64_t row_tiles = (M + bm - 1) / bm;
-    const int64_t waves = row_tiles * tiles_n / kGemmCus;
-    if (tiles_n > kGemmCus || waves < 1 || waves > 4) continue;  // (beyond a few waves the last one weighs little)
-    const int64_t m1 = waves * kGemmCus / tiles_n * bm;
-    if (m1 <= 0 || m1 >= M) continue;
-    float rest;
-    const int k2 = best((int)(M - m1), &rest);
-    const float c = gemm_cost(kind, (int)m1, N, K, f32) + rest;
-    if (c < 0.95f * cost) {
-      cost = c;
-      p = GemmPlan{kind, (int)m1, k2};
-    }
-  }
-  return p;
-}
+static_assert(kGemmShapes[kGemmWide].bm == kWM && kGemmShapes[kGemmWide].bn == kWN &&
+                  kGemmShapes[kGemm256].bm == kLM && kGemmShapes[kGemm256].bn == kLN,
+              "the plan's tiles");
 
 template <typename OutT>
 static hipError_t launch_gemm_kind(int kind, const uint16_t *A, const int32_t *gather, int64_t a_rows,
                                    const uint16_t *B, const uint16_t *bias, OutT *C, int M, int N, int K, int32_t *err,
                                    hipStream_t stream) {
+  if (kind == kGemmPlain) {
+    hipLaunchKernelGGL(gemm_bf16_nt_gelu<OutT>, dim3(N / kBN, (M + kBM - 1) / kBM), dim3(256), 0, stream, A, gather,
+                       a_rows, B, bias, C, M, N, K, err);
+    return hipGetLastError();
+  }
+  if (kind == kGemmSkinny) {
+    launch_skinny<OutT>(A, gather, a_rows, B, bias, C, M, N, K, err, stream);
+    return hipGetLastError();
+  }
   if (kind == kGemm256) return launch_gemm256<OutT>(A, gather, a_rows, B, bias, C, M, N, K, err, stream);
   if (kind == kGemmWide) return launch_wide<OutT>(A, gather, a_rows, B, bias, C, M, N, K, err, stream);
   return launch_ksplit<uint16_t, OutT>(kind, A, gather, a_rows, B, bias, C, M, N, K, err, stream);
@@ -1016,12 +1043,7 @@ static bool gemm_aligned(const void *A, const void *B, const void *C) {
 template <typename OutT>
 static hipError_t launch_gemm(const uint16_t *A, const int32_t *gather, int64_t a_rows, const uint16_t *B,
                               const uint16_t *bias, OutT *C, int M, int N, int K, int32_t *err, hipStream_t stream) {
-  if (!gemm_aligned(A, B, C)) {
-    hipLaunchKernelGGL(gemm_bf16_nt_gelu<OutT>, dim3(N / kBN, (M + kBM - 1) / kBM), dim3(256), 0, stream, A, gather,
-                       a_rows, B, bias, C, M, N, K, err);
-    return hipGetLastError();
-  }
-  const GemmPlan p = plan_gemm(M, N, K, false);
+  const GemmPlan p = plan_gemm(M, N, K, false, gemm_aligned(A, B, C));
   const hipError_t e = launch_gemm_kind<OutT>(p.kind, A, gather, a_rows, B, bias, C, p.rows, N, K, err, stream);
   if (e != hipSuccess || p.rows == M) return e;
   const int64_t off = (int64_t)p.rows;
@@ -1031,12 +1053,13 @@ static hipError_t launch_gemm(const uint16_t *A, const int32_t *gather, int64_t 
 
 static hipError_t launch_gemm(const float *A, const int32_t *gather, int64_t a_rows, const float *B, const float *bias,
                               float *C, int M, int N, int K, int32_t *err, hipStream_t stream) {
-  if (!gemm_aligned(A, B, C)) {
+  const GemmPlan p = plan_gemm(M, N, K, true, gemm_aligned(A, B, C));
+  if (p.kind == kGemmPlain) {
     hipLaunchKernelGGL(gemm_f32_nt_gelu, dim3(N / kFT, (M + kFT - 1) / kFT), dim3(256), 0, stream, A, gather, a_rows, B,
                        bias, C, M, N, K, err);
     return hipGetLastError();
   }
-  return launch_ksplit<float, float>(plan_gemm(M, N, K, true).kind, A, gather, a_rows, B, bias, C, M, N, K, err, stream);
+  return launch_ksplit<float, float>(p.kind, A, gather, a_rows, B, bias, C, M, N, K, err, stream);
 }
 
 // ---------------------------------------------------------------------------

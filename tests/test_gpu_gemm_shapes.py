@@ -49,7 +49,10 @@ def test_gemm_f32(d, rows):
     _check(torch.float32, d, rows, 0)
 
 
-@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
-def test_gemm_operands_off_16_bytes(dtype):
-    """One element past a 16-byte boundary: the kernels with plain loads."""
-    _check(dtype, 256, 300, 1)
+@pytest.mark.parametrize("dtype,d,rows", [(torch.bfloat16, 256, 300), (torch.float32, 256, 300)] + [
+    (torch.bfloat16, d, m) for d, m in ((256, 1), (512, 17), (1024, 64), (3584, 48), (1024, 65))])
+def test_gemm_operands_off_16_bytes(dtype, d, rows):
+    """One element past a 16-byte boundary: the kernels with plain loads, for
+    up to 64 rows in bf16 the one of 16 columns a workgroup (K by four waves,
+    8, 4 or 2 steps at a time)."""
+    _check(dtype, d, rows, 1)
