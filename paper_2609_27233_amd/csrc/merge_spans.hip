@@ -26,8 +26,11 @@ namespace sm {
 // gathered through `gather`.  128x128 tile per workgroup, K step 64, four
 // waves each owning a 64x64 quadrant (4x4 MFMA tiles of 16x16).  The next
 // K step is fetched into registers while the current one is multiplied from
-// LDS (double-buffered LDS, one barrier per step).  Only operands that are
-// not 16-byte aligned still take it: its loads are plain ones.
+// LDS (double-buffered LDS, one barrier per step).  Its LDS lets two workgroups
+// share a compute unit, so one's prologue and epilogue hide behind the other's
+// loop: with few k-tiles (d up to about 1024) and many rows it is the best
+// kernel (d = 256, 23,719 rows: 15 us, 22 with larger tiles).  Operands that
+// are not 16-byte aligned take it too: its loads are plain ones.
 
 constexpr int kBM = 128, kBN = 128, kBK = 64;
 constexpr int kPitch = kBK + 8;  // bf16 elements per LDS row (16-byte pad)
@@ -944,7 +947,8 @@ static void launch_skinny(const uint16_t *A, const int32_t *gather, int64_t a_ro
 
 // ---------------------------------------------------------------------------
 // fp32 GEMM on the vector ALU (64x64 tile, 4x4 outputs per thread), same
-// contract as the bf16 one, for operands that are not 16-byte aligned.
+// contract as the bf16 one, for operands that are not 16-byte aligned and for
+// many rows of 256 columns (44,515 rows: 92 us, 105 on the matrix cores).
 
 constexpr int kFT = 64, kFK = 16;
 

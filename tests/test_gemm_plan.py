@@ -7,6 +7,7 @@ import subprocess
 
 import pytest
 
+import test_gpu_gemm_shapes as shapes
 from conftest import ROOT
 
 TILES = ["32x32", "32x64", "64x64", "96x64", "128x64", "160x64", "192x64", "256x128", "256x256", "plain", "skinny"]
@@ -49,3 +50,34 @@ def test_operands_off_16_bytes_take_the_plain_loads(plan, d):
         assert plan(rows, d, aligned=False) == ("plain", rows)
     for rows in (1, 64, 300, 40000):
         assert plan(rows, d, f32=True, aligned=False) == ("plain", rows)
+
+
+@pytest.mark.parametrize("d,rows,tile,f32", [(*c, False) for c in shapes.BF16 + shapes.SPANS] + [
+    (*c, True) for c in shapes.F32])
+def test_sizes_of_the_gpu_tests_take_the_kernels_they_name(plan, d, rows, tile, f32):
+    assert plan(rows, d, f32)[0] == tile
+
+
+def test_gpu_tests_reach_every_kernel():
+    for cases, kinds in ((shapes.BF16, TILES), (shapes.F32, TILES[:7] + ["plain"]), (shapes.SPANS, TILES)):
+        assert {t for _, _, tile in cases for t in tile.split("+")} == set(kinds)
+    for cases in (shapes.BF16, shapes.SPANS):               # and calls cut in two
+        assert any("+" in tile for _, _, tile in cases)
+
+
+def test_plan_covers_the_rows_and_fits_the_width(plan):
+    """Every call gets all its rows, whole tiles of columns, and a first part of whole row tiles."""
+    for d in range(256, 8193, 256):
+        for rows in (1, 2, 31, 32, 33, 64, 65, 127, 300, 999, 2049, 4097, 10001, 65535, 200003, 8 << 20):
+            for f32 in (False, True):
+                tile, first = plan(rows, d, f32)
+                parts = tile.split("+")
+                assert 0 < first <= rows and (len(parts) == 2) == (first < rows)
+                for t in parts:
+                    if "x" in t:
+                        bm, bn = map(int, t.split("x"))
+                        assert d % bn == 0 and not (f32 and bm == 256)
+                if len(parts) == 2:
+                    assert first % int(parts[0].split("x")[0]) == 0
+                if "skinny" in parts:
+                    assert rows <= 64 and not f32
