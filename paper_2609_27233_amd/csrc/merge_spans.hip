@@ -165,8 +165,8 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_nt_gelu(const uint16_t *__re
 //    k-tile's are read into a second register set while this one is
 //    multiplied, and one barrier per k-tile is enough.
 // K-tiles come through a ring of S LDS stages filled by direct-to-LDS loads
-// (S - 1 k-tiles ahead; 64-160 KB in flight per compute unit, which is what
-// streaming the weights of a small call is bound by).  LDS layout, swizzle
+// (S - 1 k-tiles ahead: 56 to 120 KB in flight per compute unit, of a ring of
+// 64 to 144; streaming the weights of a small call is bound by it).  LDS layout, swizzle
 // and fragment addressing are those of the 256-tile GEMM (below).  fp32 runs
 // the same loop on v_mfma_f32_32x32x2_f32, four per 16-byte fragment.
 //
@@ -613,7 +613,7 @@ template <typename OutT>
 __global__ __launch_bounds__(kLThreads, 1) void gemm256_bf16_nt_gelu(
     const uint16_t *__restrict__ A, const int32_t *__restrict__ gather, int64_t a_rows,
     const uint16_t *__restrict__ B, const uint16_t *__restrict__ bias, OutT *__restrict__ C, int M, int N, int K,
-    int tiles_m, int tiles_n, int per_xcd, int staged, int32_t *err) {
+    int tiles_m, int tiles_n, int per_xcd, int32_t *err) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int wm = w >> 1, wn = w & 1;  // this wave's 128 x 128 block of the tile
@@ -760,7 +760,7 @@ __global__ __launch_bounds__(kLThreads, 1) void gemm256_bf16_nt_gelu(
 
   // 32x32 result layout (swapped): register 4 g + e of tile (i, j) holds
   // C[row 32 i + r32][col 32 j + 8 g + 4 h2 + e]
-  if (!staged) {  // straight from the MFMA layout (grids of a few waves of tiles)
+  if constexpr (sizeof(OutT) == 4) {  // fp32: straight from the MFMA layout (staged in two LDS passes it measured no better)
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
 #pragma unroll
@@ -788,8 +788,9 @@ __global__ __launch_bounds__(kLThreads, 1) void gemm256_bf16_nt_gelu(
   // the MFMA layout, each lane's 8 or 16 bytes go to 32 rows per
   // instruction, and the partial lines reach memory in pieces (4x the
   // output's bytes written).  The swizzle makes the row reads free of bank
-  // conflicts.  Staging serialises the tile's last phase, so it pays when
-  // other workgroups' main loops overlap it: grids of many waves of tiles.
+  // conflicts.  Against direct stores: 17,984 tiles (GEMM1 of the 70B-shaped
+  // batch) much faster; 40 to 640 tiles 5% faster at d = 256 and 512, 1 to 3%
+  // at most others, up to 2% slower for 64 to 128 tiles at d of 4096 and more.
   constexpr int CH = kLN * (int)sizeof(OutT) / 16;               // 16-byte chunks per tile row
   constexpr int HR = kLLdsBytes / (kLN * (int)sizeof(OutT));     // tile rows per LDS pass
   constexpr int EPC = 16 / (int)sizeof(OutT);                    // elements per chunk
@@ -828,17 +829,13 @@ __global__ __launch_bounds__(kLThreads, 1) void gemm256_bf16_nt_gelu(
   }
 }
 
-// Output tiles from which the 256-tile GEMM stages a bf16 epilogue through
-// LDS.  Measured on the four-wave kernel: GEMM1 of the 70B-shaped batch
-// (17,984 tiles) much faster staged (the direct stores wrote 4x the bytes);
-// the second projection of the 16 x 4096 prompt batch (624 tiles) about 1%
-// faster; so every bf16 output is staged (256 tiles is the kernel's
-// minimum).  fp32 output stays direct (two LDS passes measured no better).
-constexpr int kStagedMinTiles = 256;
-
-static bool use_gemm256(int M, int N, int K) {
+// A call of at least a whole wave of 256-tile products (whatever kernels its
+// plan takes): its first stage runs in token-id order, and its second
+// projection leaves bf16 rows for LN_o.  Below, the sort and the rounding of
+// Y would cost more than the traffic they save.
+static bool full_wave_of_tiles(int M, int N, int K) {
   return N % kLN == 0 && K % (2 * kLK) == 0 && K >= 2 * kLK * kLStages &&
-         (int64_t)((M + kLM - 1) / kLM) * (N / kLN) >= 256;
+         (int64_t)((M + kLM - 1) / kLM) * (N / kLN) >= kGemmCus;
 }
 
 template <typename OutT>
@@ -852,9 +849,8 @@ static hipError_t launch_gemm256(const uint16_t *A, const int32_t *gather, int64
   if (e != hipSuccess) return e;
   const int tiles_m = (M + kLM - 1) / kLM, tiles_n = N / kLN;
   const int per_xcd = (tiles_m * tiles_n + 7) / 8;
-  const int staged = sizeof(OutT) == 2 && tiles_m * tiles_n >= kStagedMinTiles;
   hipLaunchKernelGGL(gemm256_bf16_nt_gelu<OutT>, dim3(8 * per_xcd), dim3(kLThreads), kLLdsBytes, stream, A, gather,
-                     a_rows, B, bias, C, M, N, K, tiles_m, tiles_n, per_xcd, staged, err);
+                     a_rows, B, bias, C, M, N, K, tiles_m, tiles_n, per_xcd, err);
   return hipGetLastError();
 }
 
@@ -2111,7 +2107,7 @@ static sm_status pool_and_project(const void *G1, const int32_t *gidx, int64_t g
                               (const uint16_t *)p->Q, (const uint16_t *)p->g_kv, (const uint16_t *)p->beta_kv,
                               p->ln_eps, d, h, (uint16_t *)cbuf, err, stream) != hipSuccess)
       return SM_EHIP;
-    if (use_gemm256(num_spans, d, d)) {
+    if (full_wave_of_tiles(num_spans, d, d)) {
       if (launch_gemm((const uint16_t *)cbuf, nullptr, (int64_t)num_spans, (const uint16_t *)p->W_o,
                       (const uint16_t *)p->b_o, (uint16_t *)ybuf, num_spans, d, d, err, stream) != hipSuccess)
         return SM_EHIP;
@@ -2158,7 +2154,7 @@ SM_API sm_status sm_merge_spans(const void *emb, int64_t emb_rows, const int32_t
   void *g1 = wsb;
   void *cbuf = wsb + align256((size_t)total_rows * d * es);
   float *ybuf = (float *)(wsb + align256((size_t)total_rows * d * es) + align256((size_t)num_spans * d * es));
-  if (dt == SM_BF16 && use_gemm256(total_rows, d, d)) {
+  if (dt == SM_BF16 && full_wave_of_tiles(total_rows, d, d)) {
     // the first stage in token-id order (see sort_count_kernel)
     char *sw = (char *)ybuf + align256((size_t)num_spans * d * 4);
     int32_t *sorted_tok = (int32_t *)sw;
