@@ -81,6 +81,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16(PrefillArgs a) {
   constexpr int SUB = KEYS / 32;           // 32-key score blocks per tile
   constexpr int SPAN = KS * KEYS;          // keys per pass: one tile for each of the KS wave groups
   constexpr int VG = kPfWaves / KS;        // waves per group: 32 VG query vectors per workgroup
+  constexpr bool RAISE = KS > 1 || DH == 128;  // priority around the score products (measured below)
   constexpr int KP = DH + 8;        // K tile row pitch (bf16)
   // V tile rows: 72 elements for 64 keys; 32 keys have no room for padding,
   // so chunk c of row r sits at c ^ (r / 4 % 4) (16 rows of one chunk hit
@@ -280,11 +281,13 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16(PrefillArgs a) {
       // S^T = K . Q^T, one 32-key block at a time: its fragment reads first,
       // then its products.  Raised priority until the V reads are issued: the
       // wave that feeds the matrix unit goes before the SIMD's other wave's
-      // softmax, so the two fall out of step (512 rows after 16384, KS = 4:
-      // 235 -> 217 us with the append; around the second product instead it
-      // measured 243; the 16 x 2458 batch gains 1 to 2% and loses 1% with
-      // the second).
-      __builtin_amdgcn_s_setprio(1);
+      // softmax, so the two fall out of step.  Kernel alone, us without and
+      // with, D = 128: KS = 4, 512 rows after 16384 231, 211; 256 after 4096 at
+      // 28/4 heads 63, 57; KS = 2, 1024 after 8192 180, 178; KS = 1 next to
+      // nothing (16 x 2458 945, 942; 16 x 4096 2371, 2364; 2 x 2048 after 8192
+      // 609, 606).  D = 64: KS = 4 and 2 the same, KS = 1 1.5% slower with it
+      // (8 x 4096 373, 378).  Around the second product instead KS = 4 lost.
+      if constexpr (RAISE) __builtin_amdgcn_s_setprio(1);
       f32x16_t sc[SUB];
 #pragma unroll
       for (int sb = 0; sb < SUB; ++sb) {
@@ -308,7 +311,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16(PrefillArgs a) {
         for (int kst = 0; kst < 2; ++kst)
           vf[rb][kst] = *(const u32x4_t *)(&v_lds[buf * VBUF + v_at(kg * DH + 32 * rb + c32, 2 * kst + h2)]);
 
-      __builtin_amdgcn_s_setprio(0);
+      if constexpr (RAISE) __builtin_amdgcn_s_setprio(0);
 
       // online softmax per query column; register r of block sb holds token
       // t0 + 32 sb + tau(8 (r >> 2) + 4 h2 + (r & 3)).  Masked scores become
