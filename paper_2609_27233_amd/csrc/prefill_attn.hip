@@ -10,7 +10,7 @@
 // One workgroup of eight waves per (request, kv head, block of positions).
 // It holds 256 / KS query vectors: BQ = 256 / KS / G positions x the G query
 // heads of kv head g, so every K/V tile it loads serves all of them; with
-// KS > 1 (calls too small to fill the chip, see pf_key_splits) the waves
+// KS > 1 (calls too small to fill the chip, see prefill_plan.hpp) the waves
 // form KS groups that hold the same vectors and take every KS-th tile of
 // keys, and their softmax states are merged through LDS at the end.  A wave owns 32
 // vectors, the columns of the transposed score blocks
@@ -31,6 +31,7 @@
 // than 2^8.  Any reference gives the same ratios; keeping it mostly fixed
 // skips the rescale of the accumulators on almost every tile.
 #include "common.hpp"
+#include "prefill_plan.hpp"
 
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
@@ -45,7 +46,7 @@ namespace sm {
 
 constexpr int kPfWaves = 8;
 constexpr int kPfThreads = 64 * kPfWaves;
-constexpr int kPfVec = 32 * kPfWaves;       // query vectors per workgroup when its waves do not split the keys
+static_assert(kPfVec == 32 * kPfWaves, "32 query vectors per wave");
 constexpr int kPfMaxPages = 4096;
 constexpr float kPfLog2e = 1.4426950408889634f;
 
@@ -75,8 +76,57 @@ __device__ __forceinline__ int pf_token_of_row(int rho) {
   return (rho & ~15) | (q2 << 2) | (rho & 3);
 }
 
+// What a workgroup works on: kv head g and block qb of a request's rows; the
+// request's first row, row count, sequence and length, and whether they are valid.
+struct PfBlock {
+  int g, qb, r0, m, s, L;
+  bool ok;
+};
+
+__device__ __forceinline__ PfBlock pf_block(const PrefillArgs &a) {
+  // Workgroup -> (request i, kv head g, block qb).  Workgroups are dealt to
+  // the eight XCDs in turn; here the blocks of one (request, head) pair all
+  // land on one XCD, so its L2 fetches the pair's K/V once, and eight pairs
+  // run side by side.  Within a pair the longest blocks go first.
+  const int nqb = a.nqb, P = a.n * a.Hkv, Pfull = P & ~7;
+  const int b = blockIdx.x;
+  int pair, j;
+  if (b < Pfull * nqb) {
+    const int k = b >> 3;
+    pair = (k / nqb) * 8 + (b & 7);
+    j = k - (k / nqb) * nqb;
+  } else {
+    const int b2 = b - Pfull * nqb;
+    pair = Pfull + b2 / nqb;
+    j = b2 - (b2 / nqb) * nqb;
+  }
+  const int qb = nqb - 1 - j, g = pair % a.Hkv, i = pair / a.Hkv;
+  // ---- request checks (uniform) ----
+  const int r0 = a.q_offsets[i], r1 = a.q_offsets[i + 1];
+  const bool rows_ok = r0 >= 0 && r1 >= r0 && r1 <= a.total_rows;  // before any row is addressed
+  const int m = rows_ok ? r1 - r0 : 0;
+  const int s = a.seq_ids[i];
+  int L = 0;
+  bool ok = rows_ok && m <= a.max_rows && s >= 0 && s < a.max_seqs;
+  if (ok) {
+    L = a.lengths[s];
+    ok = L >= 0 && L <= (a.max_blocks << a.bs_log2) && m <= L;
+  }
+  return PfBlock{g, qb, r0, m, s, L, ok};
+}
+
+// LDS of a workgroup: the ring of K and V buffers, which the merge of the wave
+// groups uses again, then the page ids and a flag.
 template <int DH, int KS>
-__global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16(PrefillArgs a) {
+constexpr int pf_lds_bytes() {
+  const int keys = KS == 4 ? 32 : 64, vp = keys == 32 ? 32 : keys + 8;
+  const int ring = 4 * (KS * keys * (DH + 8) + KS * DH * vp);
+  const int merge = KS > 1 ? (kPfWaves * 32 * (DH + 4) + kPfWaves * 64) * 4 : 0;
+  return (ring > merge ? ring : merge) + kPfMaxPages * 4 + 16;
+}
+
+template <int DH, int KS>
+__device__ __forceinline__ void prefill_body(const PrefillArgs &a, const PfBlock &wg, uint8_t *lds) {
   constexpr int KEYS = KS == 4 ? 32 : 64;  // keys per tile
   constexpr int SUB = KEYS / 32;           // 32-key score blocks per tile
   constexpr int SPAN = KS * KEYS;          // keys per pass: one tile for each of the KS wave groups
@@ -95,49 +145,22 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16(PrefillArgs a) {
   constexpr int KTOT = SPAN * KCH, VTOT = KS * DH * VCH;  // 16-byte chunks per pass
   constexpr int KU = (KTOT + kPfThreads - 1) / kPfThreads;  // K chunks per thread and tile
   constexpr int VU = (VTOT + kPfThreads - 1) / kPfThreads;  // V chunks per thread and tile
-  __shared__ int pages[kPfMaxPages];
-  __shared__ int bad_flag;
   constexpr int KBUF = SPAN * KP, VBUF = KS * DH * VP;  // elements of one buffer
   constexpr int RING = 2 * (KBUF + VBUF) * 2;
   constexpr int OPITCH = DH + 4;                        // floats of one vector's outputs in the merge of the groups
   constexpr int MERGE = KS > 1 ? (kPfWaves * 32 * OPITCH + kPfWaves * 64) * 4 : 0;
-  __shared__ __attribute__((aligned(16))) uint8_t smem[RING > MERGE ? RING : MERGE];
-  uint16_t *k_lds = (uint16_t *)smem, *v_lds = k_lds + 2 * KBUF;  // [2][KBUF], [2][KS][DH * VP]
+  constexpr int PAGES = RING > MERGE ? RING : MERGE;
+  static_assert(PAGES + kPfMaxPages * 4 + 16 == pf_lds_bytes<DH, KS>(), "LDS of the workgroup");
+  int *pages = (int *)(lds + PAGES), *bad_flag = pages + kPfMaxPages;
+  uint16_t *k_lds = (uint16_t *)lds, *v_lds = k_lds + 2 * KBUF;  // [2][KBUF], [2][KS][DH * VP]
 
-  // Workgroup -> (request i, kv head g, block qb).  Workgroups are dealt to
-  // the eight XCDs in turn; here the blocks of one (request, head) pair all
-  // land on one XCD, so its L2 fetches the pair's K/V once, and eight pairs
-  // run side by side.  Within a pair the longest blocks go first.
-  const int nqb = a.nqb, P = a.n * a.Hkv, Pfull = P & ~7;
-  const int b = blockIdx.x;
-  int pair, j;
-  if (b < Pfull * nqb) {
-    const int k = b >> 3;
-    pair = (k / nqb) * 8 + (b & 7);
-    j = k - (k / nqb) * nqb;
-  } else {
-    const int b2 = b - Pfull * nqb;
-    pair = Pfull + b2 / nqb;
-    j = b2 - (b2 / nqb) * nqb;
-  }
-  const int qb = nqb - 1 - j, g = pair % a.Hkv, i = pair / a.Hkv;
+  const int g = wg.g, qb = wg.qb, r0 = wg.r0, m = wg.m, s = wg.s, L = wg.L;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int c32 = lane & 31, h2 = lane >> 5;
   const int vg = w % VG, kg = w / VG;  // this wave's vectors and its group's share of the keys
   const int bs_log2 = a.bs_log2, bs = 1 << bs_log2;
 
-  // ---- request checks (uniform) ----
-  const int r0 = a.q_offsets[i], r1 = a.q_offsets[i + 1];
-  const bool rows_ok = r0 >= 0 && r1 >= r0 && r1 <= a.total_rows;  // before any row is addressed
-  const int m = rows_ok ? r1 - r0 : 0;
-  const int s = a.seq_ids[i];
-  int L = 0;
-  bool ok = rows_ok && m <= a.max_rows && s >= 0 && s < a.max_seqs;
-  if (ok) {
-    L = a.lengths[s];
-    ok = L >= 0 && L <= (a.max_blocks << bs_log2) && m <= L;
-  }
-  if (!ok) {  // block 0 reports the request and zeroes its rows
+  if (!wg.ok) {  // block 0 reports the request and zeroes its rows
     if (qb != 0) return;
     if (tid == 0) set_err(a.err, SM_ERR_EINVAL);
     const int per_row = a.G * DH;  // this kv head's query heads
@@ -154,19 +177,19 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16(PrefillArgs a) {
   const int kend = pos0 + nq;     // keys [0, kend) are needed
 
   // ---- page ids of keys [0, kend) into LDS, range-checked ----
-  if (tid == 0) bad_flag = 0;
+  if (tid == 0) *bad_flag = 0;
   __syncthreads();
   const int npg = (kend + bs - 1) >> bs_log2;
   for (int p = tid; p < npg; p += kPfThreads) {
     int blk = a.block_table[(int64_t)s * a.max_blocks + p];
     if (blk < 0 || blk >= a.num_blocks) {
-      bad_flag = 1;
+      *bad_flag = 1;
       blk = 0;
     }
     pages[p] = blk;
   }
   __syncthreads();
-  if (bad_flag) {  // a corrupt block table: this block's rows are zero
+  if (*bad_flag) {  // a corrupt block table: this block's rows are zero
     if (tid == 0) set_err(a.err, SM_ERR_EINVAL);
     const int per_row = a.G * DH;
     for (int e = tid; e < nq * per_row; e += kPfThreads) {
@@ -392,7 +415,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16(PrefillArgs a) {
     // loop ends on a barrier).  Every wave leaves its reference and sum and,
     // scaled to the common reference, its output columns; then wave kg of a
     // group's KS waves adds the KS partials of its DH / KS dims.
-    float *ml = (float *)smem, *po = ml + kPfWaves * 64;  // [wave][32 m, 32 l], [wave][32][OPITCH]
+    float *ml = (float *)lds, *po = ml + kPfWaves * 64;  // [wave][32 m, 32 l], [wave][32][OPITCH]
     const int live = min(KS, (kend + KEYS - 1) / KEYS);   // groups that had a tile at all
     if (h2 == 0) {
       ml[w * 64 + c32] = m_run;
@@ -442,42 +465,33 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16(PrefillArgs a) {
                                                      cvt_bf16x2(o[rb][4 * gg + 2] * inv, o[rb][4 * gg + 3] * inv));
 }
 
+template <int DH, int KS>
+__global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16(PrefillArgs a) {
+  __shared__ __attribute__((aligned(16))) uint8_t lds[pf_lds_bytes<DH, KS>()];
+  prefill_body<DH, KS>(a, pf_block(a), lds);
+}
+
+// For calls of few rows: blocks of KS = 4, but a request of up to kPfFewKeys
+// keys is done sooner by the waves of its vectors alone than by four groups
+// and their merge.  The length is known here only, so the choice is too.  Us
+// alone and split, D = 128: one row of 32/8 heads 1 key 5.6, 6.7; 201 9.2,
+// 9.5; 401 12.5, 12.0; 4097 78, 53; 64 rows of 8/8 heads 64 keys 6.1, 8.3; 264
+// 11.3, 12.0; 364 12.5, 12.4; 564 16.0, 15.1.  D = 64, one row of 16/4: 201
+// 6.9, 7.1; 301 7.6, 7.7; 401 9.3, 8.8.
+constexpr int kPfFewKeys = 320;
+
+template <int DH>
+__global__ __launch_bounds__(kPfThreads, 2) void prefill_few_bf16(PrefillArgs a) {
+  __shared__ __attribute__((aligned(16))) uint8_t lds[pf_lds_bytes<DH, 4>()];
+  static_assert(pf_lds_bytes<DH, 1>() <= pf_lds_bytes<DH, 4>(), "one LDS for both");
+  const PfBlock wg = pf_block(a);
+  if (wg.L <= kPfFewKeys) prefill_body<DH, 1>(a, wg, lds);
+  else prefill_body<DH, 4>(a, wg, lds);
+}
+
 }  // namespace sm
 
 using namespace sm;
-
-// Into how many groups the waves of a workgroup split the keys (KS).  Where
-// the query vectors make fewer workgroups than compute units, KS = 4 or 2
-// makes 4 or 2 times as many, each with a quarter or half of the vectors and
-// its waves over different keys; with the units full it only adds LDS fills
-// (16 x 2458 rows: 894, 1071 and 1663 us for KS = 1, 2, 4).  Measured, us for
-// KS = 1, 2, 4 at 32/8 heads, D = 128: 512 rows after 16384: 429, 274, 229
-// (64, 128, 256 workgroups); 1024 after 8192: 246, 171, 244 (128, ...); 2048
-// after 8192: 317, 355, 498 (256, ...); 256 rows alone: 15.8, 12.4, 11.1.
-//  * A whole prompt's workgroups differ in length (its last rows see all of
-//    it, its first almost nothing), so halving them still pays up to 3/4 of
-//    the units: 1200 rows: 42.5, 32.4, 44.8 (152, ...); not after earlier
-//    context: 1500 after 3000: 142, 145, 179 (192, ...).
-//  * Up to 128 vectors leave half of the waves idle with KS = 1, and a short
-//    context is then done sooner than a merge of groups: 64 rows at 8/8
-//    heads: 6.6, 8.5, 8.7, but after 4096: 76, 69, 59.  The cache's capacity
-//    is all that the host knows of the context.
-// The sizes are averages and bounds (the rows of each request are device
-// data); a grid that a loose max_rows would blow up keeps KS = 1.
-static int pf_key_splits(int n, int H, int G, int total_rows, int max_rows, int64_t capacity) {
-  constexpr int64_t kCus = 256;
-  const int64_t avg = ((int64_t)total_rows + n - 1) / n;
-  auto wgs = [&](int ks, int64_t rows) {
-    const int bq = kPfVec / ks / G;
-    return (rows + bq - 1) / bq * n * H;
-  };
-  if ((int64_t)max_rows * G <= 128 && capacity < 1024) return 1;
-  for (int ks = 4; ks >= 2; ks /= 2)
-    if (wgs(ks, avg) <= kCus && wgs(ks, max_rows) <= 8 * kCus) return ks;
-  if (wgs(1, avg) <= 3 * kCus / 4 && wgs(2, max_rows) <= 8 * kCus && max_rows >= 640 && capacity < 2 * (int64_t)max_rows)
-    return 2;
-  return 1;
-}
 
 SM_API sm_status sm_prefill_attention(const sm_paged_cache *c, const int32_t *seq_ids, int n,
                                       const int32_t *q_offsets, int total_rows, const void *q, int num_q_heads,
@@ -512,7 +526,8 @@ SM_API sm_status sm_prefill_attention(const sm_paged_cache *c, const int32_t *se
   a.Hkv = H;
   a.Hq = num_q_heads;
   a.G = G;
-  const int ks = pf_key_splits(n, H, G, total_rows, max_rows, (int64_t)c->max_blocks_per_seq * bs);
+  const PrefillPlan plan = plan_prefill(n, H, G, total_rows, max_rows, (int64_t)c->max_blocks_per_seq * bs);
+  const int ks = plan.splits;
   a.BQ = kPfVec / ks / G;
   int bl = 0;
   while ((1 << bl) < bs) ++bl;
@@ -529,16 +544,10 @@ SM_API sm_status sm_prefill_attention(const sm_paged_cache *c, const int32_t *se
   if ((int64_t)nqb * n * H > 0x7fffffff) return SM_EINVAL;
   a.nqb = nqb;
   const dim3 grid(nqb * n * H);
-#define SM_PF_LAUNCH(DH, KS) hipLaunchKernelGGL((prefill_bf16<DH, KS>), grid, dim3(kPfThreads), 0, stream, a)
-  if (D == 128) {
-    if (ks == 1) SM_PF_LAUNCH(128, 1);
-    else if (ks == 2) SM_PF_LAUNCH(128, 2);
-    else SM_PF_LAUNCH(128, 4);
-  } else {
-    if (ks == 1) SM_PF_LAUNCH(64, 1);
-    else if (ks == 2) SM_PF_LAUNCH(64, 2);
-    else SM_PF_LAUNCH(64, 4);
-  }
-#undef SM_PF_LAUNCH
+  const auto kernel = D == 128 ? (plan.few ? prefill_few_bf16<128> : ks == 4 ? prefill_bf16<128, 4>
+                                  : ks == 2 ? prefill_bf16<128, 2> : prefill_bf16<128, 1>)
+                               : (plan.few ? prefill_few_bf16<64> : ks == 4 ? prefill_bf16<64, 4>
+                                  : ks == 2 ? prefill_bf16<64, 2> : prefill_bf16<64, 1>);
+  hipLaunchKernelGGL(kernel, grid, dim3(kPfThreads), 0, stream, a);
   return hipGetLastError() == hipSuccess ? SM_OK : SM_EHIP;
 }

@@ -69,25 +69,35 @@ def test_prefill_matches_oracle(orc, case):
     assert e <= TOL[torch.bfloat16]
 
 
-# Hq, H, D, bs, lens, rows per request: the waves in four groups (32-key tiles,
-# 128 keys a pass), two groups (64 and 128), and one, at the edges of tiles and
-# passes, with contexts before the rows and vectors that fill no whole block
+# Hq, H, D, bs, lens, rows per request, and the form that the call takes (which
+# test_prefill_plan.py checks): the waves in four groups (32-key tiles, 128 keys
+# a pass), two groups (64 and 128), or one, at the edges of tiles and passes,
+# with contexts before the rows and vectors that fill no whole block; "few": in
+# four groups or one by each request's length (one up to 320 keys)
 SPLIT_CASES = [
-    (32, 8, 128, 16, [127, 128, 129, 33], [127, 128, 100, 33]),
-    (12, 1, 128, 32, [700, 97, 31, 32], [150, 97, 1, 20]),        # group of 12: 5 positions, 4 vectors idle
-    (16, 1, 64, 512, [1100, 385], [65, 385]),
-    (28, 4, 128, 16, [1301, 1025], [40, 63]),                       # few rows after a long context
-    (8, 8, 128, 64, [512, 300, 511, 400, 129], None),               # two groups
-    (28, 4, 128, 16, [150, 151, 190, 256, 129, 127], [150, 151, 100, 150, 129, 127]),
-    (16, 4, 64, 16, [140] * 9 + [1], None),
-    (64, 8, 128, 16, [670], None),                                   # a whole prompt over 3/4 of the units
-    (64, 8, 64, 32, [258] * 7, [200] * 7),                           # one group
+    (32, 8, 128, 16, [127, 128, 129, 33], [127, 128, 100, 33], 4),
+    (12, 1, 128, 32, [700, 97, 31, 32], [150, 97, 1, 20], 4),     # group of 12: 5 positions, 4 vectors idle
+    (16, 1, 64, 512, [1100, 385], [65, 385], 4),
+    (28, 4, 128, 16, [1301, 1025], [40, 63], 4),                    # few rows after a long context
+    (8, 8, 128, 64, [512, 300, 511, 400, 129], None, 4),
+    (8, 8, 128, 64, [512, 300, 511, 400, 129, 512, 470], None, 2),
+    (28, 4, 128, 16, [150, 151, 190, 256, 129, 127], [150, 151, 100, 150, 129, 127], 2),
+    (16, 4, 64, 16, [140] * 9 + [1], None, 2),
+    (64, 8, 128, 16, [670], None, 2),                                # a whole prompt over 3/4 of the units
+    (64, 8, 64, 32, [258] * 7, [200] * 7, 1),
+    (64, 8, 128, 16, [300, 129, 64, 65, 1, 33, 260, 300, 17], None, 1),
+    (12, 4, 128, 256, [400] * 11, [257] * 11, 1),                    # group of 3: 85 positions, a vector idle
+    (8, 8, 128, 16, [319, 320, 321, 2, 64, 900], [64, 1, 100, 2, 64, 7], "few"),
+    (32, 8, 128, 32, [320, 321, 1500, 1], [32, 9, 5, 1], "few"),
+    (4, 4, 64, 64, [63, 500, 320], [1, 128, 128], "few"),
+    (16, 4, 64, 512, [321, 320, 33, 640], [20, 32, 31, 1], "few"),
+    (12, 1, 128, 16, [320, 400, 0], [10, 9, 0], "few"),
 ]
 
 
 @pytest.mark.parametrize("case", range(len(SPLIT_CASES)))
 def test_prefill_key_split(orc, case):
-    Hq, H, D, bs, lens, ms = SPLIT_CASES[case]
+    Hq, H, D, bs, lens, ms, _ = SPLIT_CASES[case]
     rng = np.random.RandomState(500 + case)
     ms = list(lens) if ms is None else ms
     oc, c = _cache(orc, rng, H, D, bs, lens)
