@@ -132,16 +132,25 @@ __device__ void append_rows_meta(const CacheArgs &c, const int32_t *seq_ids, int
   if (t == 0) *c.free_top = top - total;
 }
 
+// The appending form has one workgroup more, so a flat grid, whose index
+// arithmetic would take the 128 registers of four waves per SIMD to 136 and
+// leave three: hence its bound.  The other form keeps the grid of three
+// dimensions, with which it needs 128 as it is.  1024 rows, d = 4096, HD =
+// 1024, both kernels: 153 us, on a flat grid with three waves 170; 128 rows 28.6
+// and 29.4; appended (with a rollback) 183 and 194, 33.8 and 34.9.
 template <bool APPEND>
-__global__ __launch_bounds__(kPjThreads) void kv_proj_partial_kernel(ProjArgs a, CacheArgs c, const int32_t *seq_ids,
+__global__ __launch_bounds__(kPjThreads, APPEND ? 4 : 1) void kv_proj_partial_kernel(ProjArgs a, CacheArgs c, const int32_t *seq_ids,
                                                                      RowSlot *slots) {
   __shared__ __attribute__((aligned(16))) uint16_t xs[kPjRows][kPjK + 8];
   if (APPEND && blockIdx.x == 0) {  // dispatched first: it runs beside the product
     append_rows_meta(c, seq_ids, a.n, slots);
     return;
   }
-  const int id = blockIdx.x - (APPEND ? 1 : 0), nfb = 2 * a.HD / kPjFeat, nkc = a.d / kPjK;
-  const int fb = id % nfb, kc = id / nfb % nkc, rg = id / (nfb * nkc);
+  int fb = blockIdx.x, kc = blockIdx.y, rg = blockIdx.z;
+  if constexpr (APPEND) {
+    const int id = blockIdx.x - 1, nfb = 2 * a.HD / kPjFeat, nkc = a.d / kPjK;
+    fb = id % nfb, kc = id / nfb % nkc, rg = id / (nfb * nkc);
+  }
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int r = lane & 15, q4 = lane >> 4;
   const int f0 = fb * kPjFeat + 16 * w;  // this wave's 16 features: all K (f0 < HD) or all V
@@ -295,14 +304,14 @@ static sm_status launch_project(const sm_paged_cache *c, const int32_t *seq_ids,
                                 float *part, hipStream_t stream) {
   const int HD = c->num_kv_heads * c->head_dim;
   ProjArgs a{(const uint16_t *)x, (const uint16_t *)p->W_k, (const uint16_t *)p->W_v, part, n, p->d, HD};
-  const int groups = (n + kPjRows - 1) / kPjRows;
-  const dim3 grid(2 * HD / kPjFeat * (p->d / kPjK) * groups + (slots ? 1 : 0));
+  const dim3 grid(2 * HD / kPjFeat, p->d / kPjK, (n + kPjRows - 1) / kPjRows);
   ProjEpiArgs e{(const uint16_t *)x, part, seq_ids, c->lengths, (uint16_t *)K, (uint16_t *)V, slots,
                 n, p->d, HD, c->head_dim, p->d / kPjK, c->max_seqs, p->rms_eps, {}};
   for (int j = 0; j < c->head_dim / 2; ++j) e.inv_freq[j] = pow((double)p->rope_theta, -2.0 * j / c->head_dim);
   const dim3 egrid(2 * HD / kPjThreads, n);
   if (slots) {
-    hipLaunchKernelGGL(kv_proj_partial_kernel<true>, grid, dim3(kPjThreads), 0, stream, a, ca, seq_ids, slots);
+    hipLaunchKernelGGL(kv_proj_partial_kernel<true>, dim3(grid.x * grid.y * grid.z + 1), dim3(kPjThreads), 0,
+                       stream, a, ca, seq_ids, slots);
     hipLaunchKernelGGL(kv_proj_epilogue_kernel<true>, egrid, dim3(kPjThreads), 0, stream, e, ca.Hkv, ca.bs_log2);
   } else {
     hipLaunchKernelGGL(kv_proj_partial_kernel<false>, grid, dim3(kPjThreads), 0, stream, a, ca, seq_ids, slots);
