@@ -954,8 +954,8 @@ def rules_report(sm, L, dev, stream, reps=20):
         "prompt_tokens": T, "spans": S, "reduction": round(removed / T, 4),
         "match_prompt_us": round(t_match * 1e3, 1), "match_prompt_Mtokens_per_s": round(T / (t_match * 1e-3) / 1e6, 1),
         "decode_match_16_seqs_us": round(t_dec * 1e3, 2),
-        "note": "HIP events around back-to-back calls; the prompt scan is 4 launches (longest rule per position, "
-                "per-sequence chain scan, CSR offsets, compaction); latency-bound hash probes into a "
+        "note": "HIP events around back-to-back calls; the prompt scan is 2 launches (longest rule per position "
+                "with each block's map of the chain; the maps' scan, spans and offsets); latency-bound hash probes into a "
                 f"{t.capacity * 20 / 2**20:.0f} MiB table"}
 
 

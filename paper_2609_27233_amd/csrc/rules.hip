@@ -719,6 +719,9 @@ SM_API sm_status sm_rules_lookup(const sm_rule_table *t, const int32_t *grams, i
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// What callers have always been asked for.  The call uses its first part: the
+// lengths (1 B a token), the ids (4 B) and the folds (8 B per 256 and per 1024
+// positions).
 SM_API size_t sm_match_prompt_workspace_bytes(int B, int total_tokens) {
   if (B < 0 || total_tokens < 0) return 0;
   const size_t T = (size_t)total_tokens;

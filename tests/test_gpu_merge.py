@@ -207,7 +207,7 @@ def test_merge_sorted_rows_bad_ids_and_repeat(orc):
 @pytest.mark.parametrize("d,S", [(4096, 16), (3584, 128), (8192, 4)])
 def test_merge_decode_time_batches(orc, d, S):
     """Decode-time merges: one freshly completed span of n = 2..4 tokens per
-    sequence (a few rows: the skinny GEMM path) at the model widths of the
+    sequence (a few rows: the small K-split GEMM tiles) at the model widths of the
     benchmark layers."""
     rng = np.random.RandomState(d + S)
     lens = rng.randint(2, 5, size=S)

@@ -46,7 +46,8 @@ def _oracle(orc, emb_f64, row_idx, offs, params, h, sample):
                                            (torch.bfloat16, 1024, 3000)])
 def test_token_table_rows(dtype, d, vocab):
     """Table rows against GELU(emb W_kv^T + b_kv) computed in float64 on the
-    CPU from the same stored inputs (the skinny, 128- and 256-tile GEMMs)."""
+    CPU from the same stored inputs (K-split GEMM tiles of 32x32 in both types
+    and of 192x64)."""
     g = wl.generator(d + vocab)
     emb = wl.randn((vocab, d), dtype, g, std=0.02)
     params = wl.make_merge_params(d, 4, dtype, g, spread=True)
