@@ -253,7 +253,8 @@ __device__ __forceinline__ uint32_t pack_lens(uint32_t v) {
 }
 
 // 1. longest rule starting at every position (0 = none) and its id; the
-// block's fold.  IN_LDS: the sequence offsets fit kMatchLds (decided by the
+// block's fold.  Positions before the first sequence have theirs in the high
+// four bits, which only match_bad_offsets reads.  IN_LDS: the sequence offsets fit kMatchLds (decided by the
 // host: a pointer to one or the other would make every read a flat one).
 template <bool IN_LDS>
 __global__ __launch_bounds__(kMatchBlock) void match_len_kernel(const i32x4_t *keys, const int32_t *ids, uint32_t mask,
@@ -278,7 +279,10 @@ __global__ __launch_bounds__(kMatchBlock) void match_len_kernel(const i32x4_t *k
     if (off(mid) <= t) lo = mid;
     else hi = mid - 1;
   }
-  const int end = t >= off(0) ? min(off(lo + 1), total) : 0;  // (positions of no sequence match nothing)
+  const int end = min(off(lo + 1), total);
+  // before the first sequence: no part of the chain (a sequence may hold the
+  // position all the same if the offsets are out of order)
+  const bool gap = t < off(0) && lo == 0 && off(0) <= off(1) && off(1) <= total;
   i32x4_t cand[3];
   bool want[3];
 #pragma unroll
@@ -294,10 +298,10 @@ __global__ __launch_bounds__(kMatchBlock) void match_len_kernel(const i32x4_t *k
   const int c = rule_find_longest(keys, ids, mask, cand, want, &id);
   const int len = c >= 0 ? 4 - c : 0;
   if (t < total) {
-    mlen[t] = (int8_t)len;
+    mlen[t] = (int8_t)(gap ? len << 4 : len);
     rid[t] = id;
   }
-  ((uint8_t *)lens)[tid] = (uint8_t)len;
+  ((uint8_t *)lens)[tid] = (uint8_t)(gap ? 0 : len);
   __syncthreads();
   if (tid < 64) {
     const ChainFold f = lane_fold(pack_lens(lens[tid]));
@@ -340,6 +344,9 @@ __device__ void match_bad_offsets(const int8_t *mlen, const int32_t *rid, const 
   __shared__ int red[16], sums[kEmitThreads];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int cap = total / 2, grid = (int)gridDim.x;
+  const int first = seq_offsets[0], second = seq_offsets[1];
+  const int gap = first >= 0 && first <= second && second <= total ? first : 0;  // the folds leave out what is before it
+  auto len_of = [&](int p) { return (mlen[p] & 15) | (mlen[p] >> 4); };
   int base = 0;
   for (int b0 = 0; b0 < B; b0 += kEmitThreads) {
     const int b = b0 + tid;
@@ -355,12 +362,12 @@ __device__ void match_bad_offsets(const int8_t *mlen, const int32_t *rid, const 
     int n = 0;
     for (int p = lo; p < hi;) {
       const uint32_t e = p & (kMatchBlock - 1);
-      if (e < 4 && (p | (kMatchBlock - 1)) < hi) {  // the block to its end, entered at e
+      if (e < 4 && (p | (kMatchBlock - 1)) < hi && (p & -kMatchBlock) >= gap) {  // the block to its end, entered at e
         const ChainFold f = folds[p / kMatchBlock];
         n += (int)byte_at(f.cnt, e);
         p = (p | (kMatchBlock - 1)) + 1 + (int)byte_at(f.map, e);
       } else {
-        const int len = mlen[p];
+        const int len = len_of(p);
         n += len ? 1 : 0;
         p += max(len, 1);
       }
@@ -379,7 +386,7 @@ __device__ void match_bad_offsets(const int8_t *mlen, const int32_t *rid, const 
         uint32_t L = 0;
 #pragma unroll
         for (int j = 0; j < kMatchLane; ++j)
-          if (t0 + j < shi) L |= (uint32_t)mlen[t0 + j] << (4 * j);
+          if (t0 + j < shi) L |= (uint32_t)len_of(t0 + j) << (4 * j);
         const ChainFold f = lane_fold(L);
         const uint32_t incl = wave_map_scan(f.map);
         if (lane == 63) wmap[w] = incl;

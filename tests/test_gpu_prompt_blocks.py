@@ -128,6 +128,35 @@ def test_match_prompt_overlapping_sequences_stay_in_the_outputs():
     assert all(int(v[3000]) == -7 for v in out) and (out[1][:3000] == 2).all() and (out[2][:3000] == 0).all()
 
 
+@pytest.mark.parametrize("offs", [
+    [6005, 300, 5200, 6000],      # the first offset past the tokens: its sequence alone gets no spans
+    [200, 100, 5200, 6000],       # or past the second one
+    [2**31 - 1, 300, 5200, 6000],
+    [-1, 300, 5200, 6000],
+    [6005, 6005, 100, 6000],
+    [300, 400, 0, 6000],          # a good sequence before the first one
+    [2500, 2700, 0, 2500],
+    [2500, 2700, 6000],           # no error: tokens before the first sequence
+])
+def test_match_prompt_bad_first_offset(offs):
+    t = sm.RuleTable(16)
+    sm.rules_build(t, i32([[0, 0, -1, -1]]))
+    B = len(offs) - 1
+    out = [torch.full((3001,), -7, dtype=torch.int32, device=dev()) for _ in range(3)]
+    gs = torch.full((B + 1,), -7, dtype=torch.int32, device=dev())
+    ws = torch.empty(sm.match_prompt_workspace_bytes(B, 6000), dtype=torch.uint8, device=dev())
+    say("match with a bad first offset", offs)
+    sm.match_prompt(t, i32(np.zeros(6000)), i32(offs), *out, gs, ws)
+    torch.cuda.synchronize()
+    good = [0 <= lo <= hi <= 6000 for lo, hi in zip(offs, offs[1:])]
+    starts = [np.arange(lo, hi - 1, 2) if ok else np.arange(0) for ok, lo, hi in zip(good, offs, offs[1:])]
+    want = np.concatenate(starts)[:3000]
+    assert t.error_bits() == (0 if all(good) else sm.ERR_EINVAL)
+    assert gs.cpu().tolist() == [0] + [min(n, 3000) for n in np.cumsum([len(s) for s in starts])]
+    np.testing.assert_array_equal(out[0].cpu().numpy(), np.concatenate([want, np.full(3001 - len(want), -7)]))
+    assert (out[1][:len(want)] == 2).all() and (out[2][:len(want)] == 0).all()
+
+
 PACK = [
     # lengths, longest span
     ([1023, 1, 1024, 1025, 0, 2047, 2, 0], 8),
